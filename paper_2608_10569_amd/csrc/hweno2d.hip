@@ -33,15 +33,42 @@ namespace {
 
 constexpr int HALO = 4;
 
+// Wavefront maximum / minimum by data-parallel-primitive moves (row shifts by
+// 1, 2, 4, 8, then the row broadcasts; lanes without a source keep their own
+// value), read from lane 63.  Every lane of the wavefront takes part.  The
+// cross-lane moves cost a few cycles where a shuffle through LDS takes over a
+// hundred, six times in a row at the end of a block.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = (int)b, hi = (int)(b >> 32);
+    const int l = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
+    const int h = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
+    return __longlong_as_double(((long long)h << 32) | (unsigned)l);
+}
+__device__ __forceinline__ double lane63(double v) {
+    const long long b = __double_as_longlong(v);
+    const int l = __builtin_amdgcn_readlane((int)b, 63);
+    const int h = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double(((long long)h << 32) | (unsigned)l);
+}
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    return v;
+    v = fmax(v, dpp_move<0x111, 0xf>(v));
+    v = fmax(v, dpp_move<0x112, 0xf>(v));
+    v = fmax(v, dpp_move<0x114, 0xf>(v));
+    v = fmax(v, dpp_move<0x118, 0xf>(v));
+    v = fmax(v, dpp_move<0x142, 0xa>(v));
+    v = fmax(v, dpp_move<0x143, 0xc>(v));
+    return lane63(v);
 }
 __device__ __forceinline__ double wave_min(double v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmin(v, __shfl_xor(v, o));
-    return v;
+    v = fmin(v, dpp_move<0x111, 0xf>(v));
+    v = fmin(v, dpp_move<0x112, 0xf>(v));
+    v = fmin(v, dpp_move<0x114, 0xf>(v));
+    v = fmin(v, dpp_move<0x118, 0xf>(v));
+    v = fmin(v, dpp_move<0x142, 0xa>(v));
+    v = fmin(v, dpp_move<0x143, 0xc>(v));
+    return lane63(v);
 }
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
 #pragma unroll
@@ -70,30 +97,6 @@ __device__ __forceinline__ void red_max(unsigned long long* slot, double v) {
     __shared__ double sh[NT / 64];
     red_max<NT>(slot, v, sh);
 }
-// Two minima in one pass (one LDS array per value: a second red_min call
-// right after the first could overwrite slots thread 0 is still reading).
-template <int NT>
-__device__ __forceinline__ void red_min2(unsigned long long* sa, double a, unsigned long long* sb,
-                                         double b) {
-    __shared__ double sh[2][NT / 64];
-    a = wave_min(a);
-    b = wave_min(b);
-    if ((threadIdx.x & 63) == 0) {
-        sh[0][threadIdx.x >> 6] = a;
-        sh[1][threadIdx.x >> 6] = b;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int w = 1; w < NT / 64; ++w) {
-            a = fmin(a, sh[0][w]);
-            b = fmin(b, sh[1][w]);
-        }
-        const unsigned long long ka = dkey(a), kb = dkey(b);
-        if (a < INFINITY && ka < *(volatile HW_GLOBAL unsigned long long*)sa) atomicMin(sa, ka);
-        if (b < INFINITY && kb < *(volatile HW_GLOBAL unsigned long long*)sb) atomicMin(sb, kb);
-    }
-}
 template <int NT>
 __device__ __forceinline__ void red_add(unsigned long long* slot, unsigned long long v,
                                         unsigned long long* sh) {
@@ -110,6 +113,49 @@ template <int NT>
 __device__ __forceinline__ void red_add(unsigned long long* slot, unsigned long long v) {
     __shared__ unsigned long long sh[NT / 64];
     red_add<NT>(slot, v, sh);
+}
+// The reductions of an update kernel in one pass: the largest LF coefficient,
+// and with `stage` (a stage update) the least density and pressure and the
+// inadmissible cells.  Threads 0..2 each look at their slot and issue an
+// atomic only if it would change it (the three looks overlap; looking at the
+// kernel's start instead finds stale values and costs far more atomics than
+// it hides).
+template <int NT>
+__device__ __forceinline__ void reduce_update(Reduce HW_GLOBAL* red, int stage, double bmax,
+                                              double rmin, double pmin, bool bad) {
+    constexpr int NW = NT / 64;
+    __shared__ double sh[3][NW];
+    __shared__ unsigned int shn[NW];
+    const int w = threadIdx.x >> 6;
+    const double b = wave_max(bmax), r = wave_min(rmin), p = wave_min(pmin);
+    const unsigned int n = (unsigned int)__popcll(__ballot(bad));
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][w] = b;
+        sh[1][w] = r;
+        sh[2][w] = p;
+        shn[w] = n;
+    }
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < 3) {
+        double v = sh[t][0];
+#pragma unroll
+        for (int q = 1; q < NW; ++q) v = t == 0 ? fmax(v, sh[t][q]) : fmin(v, sh[t][q]);
+        const unsigned long long k = dkey(v);
+        HW_GLOBAL unsigned long long* s =
+            t == 0 ? &red->beta_key : (t == 1 ? &red->min_rho_key : &red->min_p_key);
+        const unsigned long long slot = *(volatile HW_GLOBAL unsigned long long*)s;
+        if (t == 0) {
+            if (v > -INFINITY && k > slot) atomicMax((unsigned long long*)s, k);
+        } else if (stage > 0 && v < INFINITY && k < slot) {
+            atomicMin((unsigned long long*)s, k);
+        }
+    } else if (t == 3 && stage > 0) {
+        unsigned int v = 0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) v += shn[q];
+        if (v) atomicAdd((unsigned int*)&red->bad[stage], v);
+    }
 }
 template <int NT>
 __device__ __forceinline__ void red_add32(unsigned int* slot, unsigned int v) {
@@ -1123,9 +1169,7 @@ __global__ __launch_bounds__(3 * FX_FACES) void k_flux2(Batch bt) {
         }
         face_grad<d, FULL>(g, pg + 3 + G, cm, sm);
         face_grad<d, FULL>(g, pg + G, cp, sp);
-        flux2c<d, VarMu>(K, Um, sm, fm);
-        flux2c<d, VarMu>(K, Up, sp, fp);
-        beta = fmax(speed2c<d, VarMu>(K, Um, sm), speed2c<d, VarMu>(K, Up, sp));
+        beta = fmax(flux_speed2c<d, VarMu>(K, Um, sm, fm), flux_speed2c<d, VarMu>(K, Up, sp, fp));
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             fs[c] = fm[c] + fp[c];
@@ -1162,6 +1206,98 @@ __global__ __launch_bounds__(3 * FX_FACES) void k_flux2(Batch bt) {
 // the cell's share of the admissibility reductions (stages 1..3; solid cells
 // give none).
 // ---------------------------------------------------------------------------
+// Component c of it: L, R, Bo and T as above.  nw: the new average and moments
+// (stages 1..3) or the residual (stage 0), vh: the modified moments; stored by
+// store_comp, so that a thread with several components issues every load
+// before its first store.
+__device__ __forceinline__ void update_comp(const Grid2& g, const Grid2& gsrc, long long t,
+                                            long long cell, int c, int stage, int i0, int iin,
+                                            double dt, const double* __restrict__ src,
+                                            const double* L, const double* R, const double* Bo,
+                                            const double* T, double* nw, double* vh) {
+    // explicit fused multiply-adds, no automatic contraction: the same
+    // rounding whichever kernel inlines this
+#pragma clang fp contract(off)
+    const double* __restrict__ S0 = gsrc.S[i0];
+    const double* __restrict__ Sin = gsrc.S[iin];
+    const long long nint = (long long)g.nx * g.ny;
+    const long long N = g.ncell;
+    const double idx = g.K.idx, idy = g.K.idy;
+    const double dfx = R[0] - L[0], sfx = L[0] + R[0], dfxe = R[1] - L[1];
+    const double dgy = T[0] - Bo[0], sgy = Bo[0] + T[0], dgyx = T[1] - Bo[1];
+    double Fm[3];
+    Fm[0] = fma(-dfx, idx, -dgy * idy);
+    Fm[1] = fma(g.vf[c * N + cell], idx, fma(-sfx, 0.5 * idx, -dgyx * idy));
+    Fm[2] = fma(g.vf[(4 + c) * N + cell], idy, fma(-dfxe, idx, -sgy * (0.5 * idy)));
+    if (src) {   // prescribed source moments (layout of R; single grid)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) Fm[m] += src[(m * 4 + c) * nint + t];
+    }
+    vh[0] = g.vk[c * N + cell];
+    vh[1] = g.vk[(4 + c) * N + cell];
+    if (stage == 0) {
+#pragma unroll
+        for (int m = 0; m < 3; ++m) nw[m] = Fm[m];
+        return;
+    }
+    const double in0 = Sin[c * N + cell];
+    if (stage == 1) {
+        nw[0] = fma(dt, Fm[0], in0);
+        nw[1] = fma(dt, Fm[1], vh[0]);
+        nw[2] = fma(dt, Fm[2], vh[1]);
+    } else {
+        const double a = stage == 2 ? 0.75 : 1.0 / 3.0;
+        const double bb = stage == 2 ? 0.25 : 2.0 / 3.0;
+        nw[0] = fma(a, S0[c * N + cell], bb * fma(dt, Fm[0], in0));
+        nw[1] = fma(a, g.vn[c * N + cell], bb * fma(dt, Fm[1], vh[0]));
+        nw[2] = fma(a, g.vn[(4 + c) * N + cell], bb * fma(dt, Fm[2], vh[1]));
+    }
+}
+
+__device__ __forceinline__ void store_comp(const Grid2& g, const Grid2& gsrc, long long t,
+                                           long long cell, int c, int stage, int iout,
+                                           double* __restrict__ Rout, double* __restrict__ Vout,
+                                           const double* nw, const double* vh) {
+    const long long nint = (long long)g.nx * g.ny;
+    const long long N = g.ncell;
+    if (stage == 0) {
+#pragma unroll
+        for (int m = 0; m < 3; ++m) Rout[(m * 4 + c) * nint + t] = nw[m];
+        Vout[c * nint + t] = vh[0];
+        Vout[(4 + c) * nint + t] = vh[1];
+        return;
+    }
+    double* __restrict__ Sout = gsrc.S[iout];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) Sout[(m * 4 + c) * N + cell] = nw[m];
+    if (stage == 1) {   // kept for stages 2 and 3
+        g.vn[c * N + cell] = vh[0];
+        g.vn[(4 + c) * N + cell] = vh[1];
+    }
+}
+
+// Solid cell of a masked domain: no residual, keeps the stage input, not
+// checked.  Component c.
+__device__ __forceinline__ void update_solid(const Grid2& g, const Grid2& gsrc, long long t,
+                                             long long cell, int c, int stage, int iin, int iout,
+                                             double* __restrict__ Rout,
+                                             double* __restrict__ Vout) {
+    const double* __restrict__ Sin = gsrc.S[iin];
+    double* __restrict__ Sout = gsrc.S[iout];
+    const long long nint = (long long)g.nx * g.ny;
+    const long long N = g.ncell;
+    if (stage == 0) {
+#pragma unroll
+        for (int m = 0; m < 3; ++m) Rout[(m * 4 + c) * nint + t] = 0.0;
+        Vout[c * nint + t] = 0.0;
+        Vout[(4 + c) * nint + t] = 0.0;
+    } else {
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+            Sout[(m * 4 + c) * N + cell] = Sin[(m * 4 + c) * N + cell];
+    }
+}
+
 template <class FF>
 __device__ __forceinline__ void update_cell(const Grid2& g, const Grid2& gsrc, long long t, int jj,
                                             int ii, int stage, int i0, int iin, int iout,
@@ -1169,85 +1305,31 @@ __device__ __forceinline__ void update_cell(const Grid2& g, const Grid2& gsrc, l
                                             double* __restrict__ Vout,
                                             const double* __restrict__ src, const FF& ff,
                                             double& rmin, double& pmin, unsigned int& bad) {
-    // explicit fused multiply-adds, no automatic contraction: the same
-    // rounding whichever kernel inlines this
-#pragma clang fp contract(off)
-    const double* __restrict__ S0 = gsrc.S[i0];
-    const double* __restrict__ Sin = gsrc.S[iin];
-    double* __restrict__ Sout = gsrc.S[iout];
-    const long long nint = (long long)g.nx * g.ny;
-    const long long N = g.ncell;
     const long long cell = (long long)(jj + HALO) * g.NX + ii + HALO;
     if (gsrc.solid && gsrc.solid[t]) {
-        // solid cell of a masked domain: no residual, keeps the stage input,
-        // not checked
-        if (stage == 0) {
 #pragma unroll
-            for (int q = 0; q < 12; ++q) Rout[q * nint + t] = 0.0;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) Vout[q * nint + t] = 0.0;
-        } else {
-#pragma unroll
-            for (int q = 0; q < 12; ++q) Sout[q * N + cell] = Sin[q * N + cell];
-        }
+        for (int c = 0; c < 4; ++c)
+            update_solid(g, gsrc, t, cell, c, stage, iin, iout, Rout, Vout);
         return;
     }
-    const double idx = g.K.idx, idy = g.K.idy;
-    double Fm[3][4];
+    const double dt = stage > 0 ? g.red->dt : 0.0;
+    double nw[4][3], vh[4][2];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         double L[2], R[2], Bo[2], T[2];
         ff(c, L, R, Bo, T);
-        const double dfx = R[0] - L[0], sfx = L[0] + R[0], dfxe = R[1] - L[1];
-        const double dgy = T[0] - Bo[0], sgy = Bo[0] + T[0], dgyx = T[1] - Bo[1];
-        Fm[0][c] = fma(-dfx, idx, -dgy * idy);
-        Fm[1][c] = fma(g.vf[c * N + cell], idx, fma(-sfx, 0.5 * idx, -dgyx * idy));
-        Fm[2][c] = fma(g.vf[(4 + c) * N + cell], idy, fma(-dfxe, idx, -sgy * (0.5 * idy)));
-    }
-    if (src) {   // prescribed source moments (layout of R; single grid)
-#pragma unroll
-        for (int m = 0; m < 3; ++m)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) Fm[m][c] += src[(m * 4 + c) * nint + t];
-    }
-    if (stage == 0) {
-#pragma unroll
-        for (int m = 0; m < 3; ++m)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) Rout[(m * 4 + c) * nint + t] = Fm[m][c];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) Vout[q * nint + t] = g.vk[q * N + cell];
-        return;
-    }
-    const double dt = g.red->dt;
-    double nw[12];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const double in0 = Sin[c * N + cell];
-        const double in1 = g.vk[c * N + cell];
-        const double in2 = g.vk[(4 + c) * N + cell];
-        if (stage == 1) {
-            nw[c] = fma(dt, Fm[0][c], in0);
-            nw[4 + c] = fma(dt, Fm[1][c], in1);
-            nw[8 + c] = fma(dt, Fm[2][c], in2);
-            g.vn[c * N + cell] = in1;
-            g.vn[(4 + c) * N + cell] = in2;
-        } else {
-            const double a = stage == 2 ? 0.75 : 1.0 / 3.0;
-            const double bb = stage == 2 ? 0.25 : 2.0 / 3.0;
-            nw[c] = fma(a, S0[c * N + cell], bb * fma(dt, Fm[0][c], in0));
-            nw[4 + c] = fma(a, g.vn[c * N + cell], bb * fma(dt, Fm[1][c], in1));
-            nw[8 + c] = fma(a, g.vn[(4 + c) * N + cell], bb * fma(dt, Fm[2][c], in2));
-        }
+        update_comp(g, gsrc, t, cell, c, stage, i0, iin, dt, src, L, R, Bo, T, nw[c], vh[c]);
     }
 #pragma unroll
-    for (int q = 0; q < 12; ++q) Sout[q * N + cell] = nw[q];
-    const double p = pressure2(g.K, nw[0], nw[1], nw[2], nw[3]);
-    rmin = nw[0];
+    for (int c = 0; c < 4; ++c)
+        store_comp(g, gsrc, t, cell, c, stage, iout, Rout, Vout, nw[c], vh[c]);
+    if (stage == 0) return;
+    const double p = pressure2(g.K, nw[0][0], nw[1][0], nw[2][0], nw[3][0]);
+    rmin = nw[0][0];
     pmin = p;
-    bool ok = nw[0] > 0.0 && p > 0.0;
+    bool ok = nw[0][0] > 0.0 && p > 0.0;
 #pragma unroll
-    for (int q = 0; q < 12; ++q) ok = ok && isfinite(nw[q]);
+    for (int q = 0; q < 12; ++q) ok = ok && isfinite(nw[q / 3][q % 3]);
     bad = ok ? 0u : 1u;
 }
 
@@ -1280,10 +1362,7 @@ __global__ __launch_bounds__(256) void k_update2(Batch bt, int stage, int i0, in
         update_cell(g, gsrc, t, jj, ii, stage, i0, iin, iout, Rout, Vout, src, ff, rmin, pmin,
                     bad);
     }
-    if (stage > 0) {
-        red_min2<256>(&g.red->min_rho_key, rmin, &g.red->min_p_key, pmin);
-        red_add32<256>(&g.red->bad[stage], bad);
-    }
+    if (stage > 0) reduce_update<256>(gsrc.red, stage, -INFINITY, rmin, pmin, bad != 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1296,13 +1375,14 @@ __global__ __launch_bounds__(256) void k_update2(Batch bt, int stage, int i0, in
 // Then each thread assembles and updates its cell.  A face on a tile edge is
 // formed by both tiles that share it.  The arithmetic per face and per cell
 // is that of k_flux2 and k_update2, so the two paths give the same bits.
+// Constant viscosity, large launches; the others take k_fluxup2s below.
 // ---------------------------------------------------------------------------
 constexpr int FU_TX = 32, FU_TY = 8;
 
 // Gauss moments (A into o[c * stride], B into o[(4 + c) * stride]) of the
 // flux of the face between cells cm and cp (direction d); returns the LF
 // coefficient (max over the three points and both sides).
-template <int d, bool VarMu, bool FULL>
+template <int d, bool FULL>
 __device__ __forceinline__ double face_flux3(const Grid2& g, long long cm, long long cp,
                                              double* o, int stride) {
     const Consts& K = g.K;
@@ -1320,9 +1400,7 @@ __device__ __forceinline__ double face_flux3(const Grid2& g, long long cm, long 
         }
         face_grad<d, FULL>(g, pg + 3 + G, cm, sm);
         face_grad<d, FULL>(g, pg + G, cp, sp);
-        flux2c<d, VarMu>(K, Um, sm, fm);
-        flux2c<d, VarMu>(K, Up, sp, fp);
-        bg[G] = fmax(speed2c<d, VarMu>(K, Um, sm), speed2c<d, VarMu>(K, Up, sp));
+        bg[G] = fmax(flux_speed2c<d, false>(K, Um, sm, fm), flux_speed2c<d, false>(K, Up, sp, fp));
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             fs[G][c] = fm[c] + fp[c];
@@ -1341,7 +1419,7 @@ __device__ __forceinline__ double face_flux3(const Grid2& g, long long cm, long 
     return beta;
 }
 
-template <bool VarMu, bool FULL>
+template <bool FULL>
 __global__ __launch_bounds__(FU_TX * FU_TY) void k_fluxup2(Batch bt, int stage, int i0, int iin,
                                                            int iout, double* __restrict__ Rout,
                                                            double* __restrict__ Vout,
@@ -1367,7 +1445,7 @@ __global__ __launch_bounds__(FU_TX * FU_TY) void k_fluxup2(Batch bt, int stage, 
         const int ii = ii0 + fc, jj = jj0 + row;
         if (ii < 0 || ii > g.nx || jj >= g.ny) return;
         const long long cp = (long long)(jj + HALO) * g.NX + ii + HALO;
-        bmax = fmax(bmax, face_flux3<0, VarMu, FULL>(g, cp - 1, cp, lx + row * RX + fc, SX));
+        bmax = fmax(bmax, face_flux3<0, FULL>(g, cp - 1, cp, lx + row * RX + fc, SX));
     };
     // y-face below interior cell (ii0 + col, jj0 + fr); fr = FU_TY and jj = ny
     // included
@@ -1375,7 +1453,7 @@ __global__ __launch_bounds__(FU_TX * FU_TY) void k_fluxup2(Batch bt, int stage, 
         const int ii = ii0 + col, jj = jj0 + fr;
         if (ii < 0 || ii >= g.nx || jj > g.ny) return;
         const long long cp = (long long)(jj + HALO) * g.NX + ii + HALO;
-        bmax = fmax(bmax, face_flux3<1, VarMu, FULL>(g, cp - g.NX, cp, ly + fr * FU_TX + col, SY));
+        bmax = fmax(bmax, face_flux3<1, FULL>(g, cp - g.NX, cp, ly + fr * FU_TX + col, SY));
     };
     xface(tx, ty);
     yface(ty, tx);
@@ -1399,11 +1477,139 @@ __global__ __launch_bounds__(FU_TX * FU_TY) void k_fluxup2(Batch bt, int stage, 
         update_cell(g, gsrc, (long long)jj * g.nx + ii, jj, ii, stage, i0, iin, iout, Rout, Vout,
                     src, ff, rmin, pmin, bad);
     }
-    red_max<FU_TX * FU_TY>(&g.red->beta_key, bmax);
-    if (stage > 0) {
-        red_min2<FU_TX * FU_TY>(&g.red->min_rho_key, rmin, &g.red->min_p_key, pmin);
-        red_add32<FU_TX * FU_TY>(&g.red->bad[stage], bad);
+    reduce_update<FU_TX * FU_TY>(gsrc.red, stage, bmax, rmin, pmin, bad != 0);
+}
+
+// The same with less work per thread: tiles of FU_TX x FS_TY cells, and a
+// thread forms the flux at one Gauss point of one face instead of a whole face,
+// then one component of one cell.  Same arithmetic, so the same bits.
+// Small launches are bound by the latency of one block (its chain of loads and
+// divisions), which this cuts: 64^2 15.8 -> 9.9 us, 104x88 14.5 -> 9.5,
+// 500x100 17.4 -> 15.9, 256^2 21.5 -> 21.0, 360^2 32.5 -> 31.8; large ones move
+// at the memory's rate with whole faces (1000x500 116 us, 5.3 TB/s, against
+// 126 here: a third more edge faces are formed twice), so the line lies
+// between 360^2 (540 blocks of the other kernel) and 512^2 (1088 blocks, 64
+// against 69 us).  With mu(T) the power law's registers leave the whole-face
+// kernel two wavefronts per SIMD, and this one is faster at every size (64^2
+// 36 -> 17 us, 1000x500 158 -> 149).
+constexpr int FS_TY = 4, FS_NT = 512;
+constexpr unsigned FS_MAX_BLOCKS = 640;   // of k_fluxup2
+
+// Flux sums of Gauss point G of the face between cells cm and cp (direction d):
+// f- + f+ and U+ - U-; returns the larger wave-speed bound of the two sides.
+template <int d, bool VarMu, bool FULL>
+__device__ __forceinline__ double face_point(const Grid2& g, long long cm, long long cp, int G,
+                                             double* fs, double* du) {
+    const Consts& K = g.K;
+    const long long N = g.ncell;
+    const double* F = d == 0 ? g.xf : g.yf;
+    const int pg = d == 0 ? 0 : 6;
+    double Um[4], Up[4], sm[3], sp[3], fm[4], fp[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        Um[c] = F[((3 + G) * 4 + c) * N + cm];
+        Up[c] = F[(G * 4 + c) * N + cp];
     }
+    face_grad<d, FULL>(g, pg + 3 + G, cm, sm);
+    face_grad<d, FULL>(g, pg + G, cp, sp);
+    const double b = fmax(flux_speed2c<d, VarMu>(K, Um, sm, fm),
+                          flux_speed2c<d, VarMu>(K, Up, sp, fp));
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        fs[c] = fm[c] + fp[c];
+        du[c] = Up[c] - Um[c];
+    }
+    return b;
+}
+
+template <bool VarMu, bool FULL>
+__global__ __launch_bounds__(FS_NT) void k_fluxup2s(Batch bt, int stage, int i0, int iin, int iout,
+                                                    double* __restrict__ Rout,
+                                                    double* __restrict__ Vout,
+                                                    const double* __restrict__ src) {
+    constexpr int RX = FU_TX + 1;                              // x-face columns per row
+    constexpr int NXF = FS_TY * RX, NYF = (FS_TY + 1) * FU_TX, NF = NXF + NYF;
+    constexpr int NT = 3 * NF, NIT = (NT + FS_NT - 1) / FS_NT;
+    __shared__ double shb[NT];        // wave-speed bound per Gauss point and face
+    __shared__ double shf[4][NT];     // flux per component, Gauss point and face
+    __shared__ double shu[4][FS_TY * FU_TX];   // new averages, for the admissibility check
+    __shared__ unsigned char shk[4][FS_TY * FU_TX];
+    const Loc lc = locate(bt);
+    const Grid2& gsrc = bt.g[lc.p];   // arrays indexed at run time are read from here
+    if (!gsrc.st->active) return;
+    const Grid2 g = gsrc;
+    const int tiles_x = (g.nx + HALO + FU_TX - 1) / FU_TX;
+    const int ii0 = (lc.b % tiles_x) * FU_TX - HALO, jj0 = (lc.b / tiles_x) * FS_TY;
+    double fs[NIT][4] = {}, du[NIT][4] = {}, bmax = -INFINITY;
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int t = threadIdx.x + it * FS_NT;
+        const int G = t / NF, f = t - G * NF;
+        if (t >= NT) continue;
+        double b = -INFINITY;
+        if (f < NXF) {   // x-face left of interior cell (ii, jj)
+            const int ii = ii0 + f % RX, jj = jj0 + f / RX;
+            if (ii >= 0 && ii <= g.nx && jj < g.ny) {
+                const long long cp = (long long)(jj + HALO) * g.NX + ii + HALO;
+                b = face_point<0, VarMu, FULL>(g, cp - 1, cp, G, fs[it], du[it]);
+            }
+        } else {         // y-face below it
+            const int ii = ii0 + (f - NXF) % FU_TX, jj = jj0 + (f - NXF) / FU_TX;
+            if (ii >= 0 && ii < g.nx && jj <= g.ny) {
+                const long long cp = (long long)(jj + HALO) * g.NX + ii + HALO;
+                b = face_point<1, VarMu, FULL>(g, cp - g.NX, cp, G, fs[it], du[it]);
+            }
+        }
+        shb[t] = b;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int t = threadIdx.x + it * FS_NT;
+        if (t >= NT) continue;
+        const int f = t % NF;
+        const double beta = fmax(fmax(shb[f], shb[NF + f]), shb[2 * NF + f]);
+        bmax = fmax(bmax, beta);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) shf[c][t] = 0.5 * fma(-beta, du[it][c], fs[it][c]);
+    }
+    __syncthreads();
+    // thread (c, cell): component c of the tile's cell
+    const int c = threadIdx.x / (FS_TY * FU_TX), ct = threadIdx.x % (FS_TY * FU_TX);
+    const int tx = ct % FU_TX, ty = ct / FU_TX;
+    const int ii = ii0 + tx, jj = jj0 + ty;
+    const bool in = ii >= 0 && ii < g.nx && jj < g.ny;
+    const long long t = (long long)jj * g.nx + ii;
+    const bool solid = in && gsrc.solid && gsrc.solid[t];
+    if (in) {
+        const long long cell = (long long)(jj + HALO) * g.NX + ii + HALO;
+        if (solid) {
+            update_solid(g, gsrc, t, cell, c, stage, iin, iout, Rout, Vout);
+        } else {
+            auto mom = [&](int f, double* o) {
+                face_moments(shf[c][f], shf[c][NF + f], shf[c][2 * NF + f], o[0], o[1]);
+            };
+            double L[2], R[2], Bo[2], T[2], nw[3], vh[2];
+            mom(ty * RX + tx, L);
+            mom(ty * RX + tx + 1, R);
+            mom(NXF + ty * FU_TX + tx, Bo);
+            mom(NXF + (ty + 1) * FU_TX + tx, T);
+            update_comp(g, gsrc, t, cell, c, stage, i0, iin, stage > 0 ? g.red->dt : 0.0, src, L,
+                        R, Bo, T, nw, vh);
+            store_comp(g, gsrc, t, cell, c, stage, iout, Rout, Vout, nw, vh);
+            shu[c][ct] = nw[0];
+            shk[c][ct] = isfinite(nw[0]) && isfinite(nw[1]) && isfinite(nw[2]);
+        }
+    }
+    __syncthreads();
+    double rmin = INFINITY, pmin = INFINITY;
+    bool bad = false;
+    if (stage > 0 && c == 0 && in && !solid) {
+        rmin = shu[0][ct];
+        pmin = pressure2(g.K, rmin, shu[1][ct], shu[2][ct], shu[3][ct]);
+        bad = !(rmin > 0.0 && pmin > 0.0 && shk[0][ct] && shk[1][ct] && shk[2][ct] && shk[3][ct]);
+    }
+    reduce_update<FS_NT>(gsrc.red, stage, bmax, rmin, pmin, bad);
 }
 
 __global__ void k_copy_in2(Grid2 g, const double* __restrict__ U, double* __restrict__ S) {
@@ -1626,6 +1832,11 @@ void batch_blocks(const Grid2* hg, int n, const Tiles& t, int* out) {
                            ((g.ny + FU_TY - 1) / FU_TY);
                     per = 1;
                     break;
+                case KB_FLUXUPS:   // tiles of FU_TX x FS_TY cells
+                    work = (long long)((g.nx + HALO + FU_TX - 1) / FU_TX) *
+                           ((g.ny + FS_TY - 1) / FS_TY);
+                    per = 1;
+                    break;
                 default: work = (long long)g.nx * g.ny; break;
             }
             st[p + 1] = st[p] + (int)nblk(work, per);
@@ -1755,25 +1966,26 @@ hipError_t launch_residual2(const BatchL& b, int si, hipStream_t st, Timer* tm) 
     return hipGetLastError();
 }
 
+template <bool VarMu, bool FULL>
+void launch_fluxup2(const BatchL& b, int stage, int i0, int iin, int iout, double* R, double* Vhat,
+                    hipStream_t st, Timer* tm, const double* src) {
+    if (VarMu || b.blocks(KB_FLUXUP) <= FS_MAX_BLOCKS)
+        tlaunch(tm, KC_FLUXUP, k_fluxup2s<VarMu, FULL>, b.blocks(KB_FLUXUPS), FS_NT, st,
+                b.arg(KB_FLUXUPS), stage, i0, iin, iout, R, Vhat, src);
+    else
+        tlaunch(tm, KC_FLUXUP, k_fluxup2<FULL>, b.blocks(KB_FLUXUP), FU_TX * FU_TY, st,
+                b.arg(KB_FLUXUP), stage, i0, iin, iout, R, Vhat, src);
+}
+
 hipError_t launch_update2(const BatchL& b, int stage, int i0, int iin, int iout, double* R,
                           double* Vhat, hipStream_t st, Timer* tm, const double* src) {
     if (b.tiles.flux == 0) {
-        const unsigned nb = b.blocks(KB_FLUXUP);
-        const Batch a = b.arg(KB_FLUXUP);
-        constexpr unsigned NT = FU_TX * FU_TY;
         if (b.full_grad) {
-            if (b.var_mu)
-                tlaunch(tm, KC_FLUXUP, k_fluxup2<true, true>, nb, NT, st, a, stage, i0, iin, iout,
-                        R, Vhat, src);
-            else
-                tlaunch(tm, KC_FLUXUP, k_fluxup2<false, true>, nb, NT, st, a, stage, i0, iin,
-                        iout, R, Vhat, src);
-        } else if (b.var_mu) {
-            tlaunch(tm, KC_FLUXUP, k_fluxup2<true, false>, nb, NT, st, a, stage, i0, iin, iout, R,
-                    Vhat, src);
+            if (b.var_mu) launch_fluxup2<true, true>(b, stage, i0, iin, iout, R, Vhat, st, tm, src);
+            else launch_fluxup2<false, true>(b, stage, i0, iin, iout, R, Vhat, st, tm, src);
         } else {
-            tlaunch(tm, KC_FLUXUP, k_fluxup2<false, false>, nb, NT, st, a, stage, i0, iin, iout,
-                    R, Vhat, src);
+            if (b.var_mu) launch_fluxup2<true, false>(b, stage, i0, iin, iout, R, Vhat, st, tm, src);
+            else launch_fluxup2<false, false>(b, stage, i0, iin, iout, R, Vhat, st, tm, src);
         }
     } else {
         tlaunch(tm, KC_UPDATE, k_update2, b.blocks(KB_CELLS), 256, st, b.arg(KB_CELLS), stage, i0,

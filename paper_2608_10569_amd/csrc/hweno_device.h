@@ -418,10 +418,12 @@ __device__ __forceinline__ void stress_combos(const double* s, double* dc) {
     dc[2] = s[4 + d];
 }
 
-// flux2 at a face point from the three combinations dc of stress_combos.
+// flux2 and speed2 at a face point from the three combinations dc of
+// stress_combos; one viscosity serves both (with mu(T) the power law is most
+// of a point's work).  Returns the speed bound.
 template <int d, bool VarMu = true>
-__device__ __forceinline__ void flux2c(const Consts& K, const double* U, const double* dc,
-                                       double* f) {
+__device__ __forceinline__ double flux_speed2c(const Consts& K, const double* U, const double* dc,
+                                               double* f) {
 #pragma clang fp contract(off)
     const double r = U[0], m = U[1], n = U[2], E = U[3];
     const double ir = rcp(r);
@@ -441,26 +443,16 @@ __device__ __forceinline__ void flux2c(const Consts& K, const double* U, const d
         f[2] = fma(n, v, p) - tnn;
         f[3] = fma(E + p, v, -fma(txy, u, fma(tnn, v, kq * dc[2])));
     }
-}
-
-// speed2 from the three combinations.
-template <int d, bool VarMu = true>
-__device__ __forceinline__ double speed2c(const Consts& K, const double* U, const double* dc) {
-#pragma clang fp contract(off)
-    const double r = U[0], m = U[1], n = U[2], E = U[3];
-    const double ir = rcp(r);
-    const double p = K.gm1 * fma(-0.5 * fma(m, m, n * n), ir, E);
-    const double mu = viscosity<VarMu>(K, r, p);
-    const double tnn = mu * dc[0], txy = mu * dc[1];
-    const double kq = K.gPr * mu;
+    // the wave-speed bound forms its pressure as speed2 does
+    const double ps = K.gm1 * fma(-0.5 * fma(m, m, n * n), ir, E);
     const double un = (d == 0 ? m : n) * ir;
     const double q = kq * dc[2];
-    const double tp = tnn - p;
+    const double tp = tnn - ps;
     const double t2 = fma(tp, tp, txy * txy);
-    const double r2e = r * p * K.igm1;
+    const double r2e = r * ps * K.igm1;
     const double root = sqrt(fma(r * r, q * q, 2.0 * r2e * t2));
     const double bpp = fma(fma(r, fabs(q), root), 0.5 * rcp(r2e), fabs(un));
-    const double ac = fabs(un) + sqrt(K.gamma * p * ir);
+    const double ac = fabs(un) + sqrt(K.gamma * ps * ir);
     return ac >= bpp ? ac : bpp;
 }
 

@@ -204,7 +204,7 @@ inline void tend(Timer* t, hipStream_t st) { if (t) t->end(st); }
 // block of the instance in slot p (start[n] = the launch's block count).
 // ---------------------------------------------------------------------------
 enum { KB_GHOST = 0, KB_RECON, KB_RBAR, KB_GRAD, KB_FLUX0, KB_FLUX1, KB_CELLS,
-       KB_FLUXUP, KB_RGRAD, KB_COUNT };
+       KB_FLUXUP, KB_RGRAD, KB_FLUXUPS, KB_COUNT };
 
 struct Batch {
     const Grid2* g;
@@ -240,7 +240,7 @@ struct BatchL {
     // their first blocks read what is still in L2 and the memory-side cache;
     // the next stage's reconstruction then again runs opposite to them.
     unsigned rev = (1u << KB_RBAR) | (1u << KB_FLUX0) | (1u << KB_FLUX1) | (1u << KB_FLUXUP) |
-                   (1u << KB_RGRAD);
+                   (1u << KB_RGRAD) | (1u << KB_FLUXUPS);
     Batch arg(int k) const {
         return Batch{dg, dstart + k * (n + 1), n, tiles.xcd, (int)((rev >> k) & 1u)};
     }
