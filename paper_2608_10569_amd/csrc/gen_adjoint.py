@@ -42,36 +42,70 @@ class CPrinter(C99CodePrinter):
     def _print_Integer(self, expr):
         return fmt(expr)
 
+    # Powers are products and square roots, and every division is a product with
+    # the device function rcp (the kernels' reciprocal): a call of pow or an
+    # IEEE division per term cost the adjoint kernels most of their time.
     def _print_Pow(self, expr):
         b, e = expr.as_base_exp()
+        if e.is_Rational and e.is_negative:
+            return 'rcp(%s)' % self._print(sp.Pow(b, -e))
         x = '(%s)' % self._print(b)     # the base always in parentheses
-        if e == 2:
-            return '(%s * %s)' % (x, x)
-        if e == -1:
-            return '(1.0 / %s)' % x
-        if e == -2:
-            return '(1.0 / (%s * %s))' % (x, x)
-        if e == 3:
-            return '(%s * %s * %s)' % (x, x, x)
+        if e.is_Integer and 2 <= e <= 8:
+            return '(%s)' % ' * '.join([x] * int(e))
         if e == sp.Rational(1, 2):
             return 'sqrt%s' % x
-        if e == -sp.Rational(1, 2):
-            return '(1.0 / sqrt%s)' % x
-        if e == sp.Rational(3, 2):
-            return '(%s * sqrt%s)' % (x, x)
-        if e == -sp.Rational(3, 2):
-            return '(1.0 / (%s * sqrt%s))' % (x, x)
-        return super()._print_Pow(expr)
+        if (2 * e).is_Integer and 1 < e < 4:
+            return '(%s * sqrt%s)' % (self._print(sp.Pow(b, e - sp.Rational(1, 2))), x)
+        raise ValueError('power %s' % e)
+
+    def _print_Mul(self, expr):
+        num, den = [], []
+        for f in sp.Mul.make_args(expr):
+            b, e = f.as_base_exp()
+            if f.is_Pow and e.is_Rational and e.is_negative:
+                den.append(sp.Pow(b, -e))
+            else:
+                num.append(f)
+        if not den:
+            return super()._print_Mul(expr)
+        n = sp.Mul(*num)
+        d = 'rcp(%s)' % self._print(sp.Mul(*den))
+        if n == 1:
+            return d
+        if n == -1:
+            return '-' + d
+        x = self._print(n)
+        return '%s*%s' % ('(%s)' % x if n.is_Add else x, d)
 
 
 PR = CPrinter()
 
 
+def by_reciprocal(e):
+    """Negative powers of the density as powers of ir = 1 / r and
+    isr = 1 / sqrt(r), so that one reciprocal of each serves an expression."""
+    r = sp.Symbol('r', positive=True)
+    ir, isr = sp.symbols('ir isr', positive=True)
+
+    def sub(p):
+        if p.exp.is_Integer:
+            return ir ** (-p.exp)
+        return ir ** (-p.exp - sp.Rational(1, 2)) * isr
+    return e.replace(lambda p: p.is_Pow and p.base == r and p.exp.is_Rational
+                     and p.exp.is_negative and (2 * p.exp).is_Integer, sub)
+
+
 def emit(targets, exprs, accumulate=True, indent='    '):
     """CSE + C code: target[i] (+)= exprs[i]."""
+    exprs = [by_reciprocal(sp.sympify(e)) for e in exprs]
     reps, red = sp.cse([sp.expand(e) if e.is_polynomial() else e for e in exprs],
                        symbols=sp.numbered_symbols('t'))
     lines = []
+    used = set().union(*[e.free_symbols for e in red], *[v.free_symbols for _, v in reps])
+    if sp.Symbol('isr', positive=True) in used:
+        lines.append('%sconst double isr = rcp(sqrt(r));' % indent)
+    if sp.Symbol('ir', positive=True) in used:
+        lines.append('%sconst double ir = rcp(r);' % indent)
     for sym, val in reps:
         lines.append('%sconst double %s = %s;' % (indent, sym, PR.doprint(val)))
     for t, e in zip(targets, red):

@@ -19,7 +19,7 @@ __device__ inline void hweno2d_vjp(const double* __restrict__ a, const Consts& K
     const double a2 = a[1], a4 = a[3], a5 = a[4], a6 = a[5], a8 = a[7];
     const double sxl = a5 - a4, sxr = a6 - a5, syb = a5 - a2, syt = a8 - a5;
     double w[5] = {G2D_0, G2D_1, G2D_1, G2D_1, G2D_1};
-    double b[5], im[5], tau = 0.0, sig = 0.0, T = 1.0;
+    double b[5], im[5], tau = 0.0, sig = 0.0, iT = 1.0;
     if (!K.linear) {
         b[0] = hweno_gen::sobolev_2d(c0);
         b[1] = sxl * sxl + syb * syb;
@@ -28,16 +28,35 @@ __device__ inline void hweno2d_vjp(const double* __restrict__ a, const Consts& K
         b[4] = sxr * sxr + syt * syt;
         sig = 0.25 * (fabs(b[0] - b[1]) + fabs(b[0] - b[2]) + fabs(b[0] - b[3]) + fabs(b[0] - b[4]));
         tau = sig * sig;
-        double t[5];
-        T = 0.0;
+        // five reciprocals 1/(beta_m + eps) from one, as in hweno2d
+        const double D0 = b[0] + K.eps_weno, D1 = b[1] + K.eps_weno, D2 = b[2] + K.eps_weno,
+                     D3 = b[3] + K.eps_weno, D4 = b[4] + K.eps_weno;
+        const double p01 = D0 * D1, p012 = p01 * D2, p0123 = p012 * D3;
+        const double s34 = D3 * D4, s234 = D2 * s34;
+        const double prod = p0123 * D4;
+        if (prod < 1e300) {
+            const double inv = rcp(prod);
+            im[0] = inv * (D1 * s234);
+            im[1] = inv * (D0 * s234);
+            im[2] = inv * (p01 * s34);
+            im[3] = inv * (p012 * D4);
+            im[4] = inv * p0123;
+        } else {
+            im[0] = 1.0 / D0;
+            im[1] = 1.0 / D1;
+            im[2] = 1.0 / D2;
+            im[3] = 1.0 / D3;
+            im[4] = 1.0 / D4;
+        }
+        double t[5], T = 0.0;
 #pragma unroll
         for (int m = 0; m < 5; ++m) {
-            im[m] = 1.0 / (b[m] + K.eps_weno);
             t[m] = (m ? G2D_1 : G2D_0) * (1.0 + tau * im[m]);
             T += t[m];
         }
+        iT = rcp(T);
 #pragma unroll
-        for (int m = 0; m < 5; ++m) w[m] = t[m] / T;
+        for (int m = 0; m < 5; ++m) w[m] = t[m] * iT;
     }
     const double r0 = w[0] * (1.0 / G2D_0);
     const double q = w[0] * (G2D_1 / G2D_0);
@@ -70,7 +89,7 @@ __device__ inline void hweno2d_vjp(const double* __restrict__ a, const Consts& K
         double taub = 0.0, bb[5];
 #pragma unroll
         for (int m = 0; m < 5; ++m) {
-            const double tb = (wb[m] - ws) / T;
+            const double tb = (wb[m] - ws) * iT;
             const double g = m ? G2D_1 : G2D_0;
             taub += tb * g * im[m];
             bb[m] = -tb * g * tau * im[m] * im[m];
