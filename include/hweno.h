@@ -436,7 +436,8 @@ HWENO_API hweno_status hweno_batch_get_diag(hweno_ctx* ctx, int i, hweno_diag* o
 
 /* Work per block of the tunable kernels and the instance order of a launch. */
 typedef struct hweno_tiles {
-    int recon;      /* cells per block of the characteristic reconstruction: 16 or 32 */
+    int recon;      /* columns of the characteristic reconstruction's 64-cell tiles: 16
+                       (tiles of 16 x 4 cells) or 32 (32 x 2); HWENO-DR: cells per block */
     int grad;       /* cells per block of the gradient reconstruction: 32 or 64; 0:
                        the weak moments (eqs. 3.6-3.8) are formed inside the gradient
                        kernel, per 16 x 4 tile of cells and the ring around it, in

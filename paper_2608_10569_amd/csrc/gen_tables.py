@@ -194,6 +194,8 @@ def main():
     out.append('// cells 1..9 (row-major from (i-1,j-1)), a[9..12] = xi-moments of cells')
     out.append('// 2,4,6,8, a[13..16] = eta-moments of cells 2,4,6,8 -> c[15] in monomial order.')
     out.append('__device__ __forceinline__ void p0_2d(const double* __restrict__ a, double* __restrict__ c) {')
+    # contraction fixed by the source, so that every kernel gets the same bits
+    out.append('#pragma clang fp contract(on)')
     for i, s in enumerate(ins2):
         out.append('    const double %s = a[%d];' % (s, i))
     for k, m in enumerate(MONOS2):

@@ -312,12 +312,357 @@ __global__ void k_ghost2(Batch bt, int sidx, int stage) {
 }
 
 // ---------------------------------------------------------------------------
-// Characteristic reconstruction + positivity limiter.
+// Characteristic reconstruction + positivity limiter (HWENO-GR).
+// Block: a TX x (64 / TX) tile of cells, four wavefronts, one thread per cell
+// in each: wavefront (b, h) works in basis b (0: x-Jacobian, 1: y-Jacobian) on
+// two of its four characteristic fields (h = 0: the acoustic ones 0 and 3,
+// h = 1: fields 1 and 2) and then owns the basis's face points (h = 0) or
+// volume points (h = 1).  Threads work in their basis's own coordinates
+// (normal, tangential), so every wavefront runs the same reconstruction code
+// on a stencil tile that basis 1 reads transposed.  A wavefront evaluates its
+// two fields at all points and hands the values at its partner's points over
+// through LDS; each then forms the four conserved components at its own
+// points in registers.
+// Bound: the 848 bytes per cell it writes (98 us at the 4.9 TB/s a kernel
+// without arithmetic reaches on these planes at 1000x500).  A thread per field
+// and component, which exchanged every value twice through LDS behind ten
+// barriers and formed the basis eight times per cell, took 190 us there,
+// 28 us on 500x100 and 10.5 us on 64^2; this split takes 136, 22.0 and 9.6.  A
+// thread per basis (all four fields, no exchange) needs 256 registers: 136
+// us, but 12.1 us on 64^2.  Four wavefronts per SIMD instead of three spill
+// (193 us).
+// ---------------------------------------------------------------------------
+// Element i (cell offset in bytes) of a plane; base uniform per wavefront.
+__device__ __forceinline__ gdouble& at(gdouble* base, unsigned off) {
+    return *(gdouble*)((HW_GLOBAL char*)base + off);
+}
+
+// Characteristic basis at a cell average in (rho, m_n, m_t, E) ordering.
+struct Basis2 {
+    double un, ut, q2, c, ic, H, b1, b2;
+};
+__device__ __forceinline__ Basis2 basis2(const Consts& K, double r, double mn, double mt,
+                                         double E) {
+#pragma clang fp contract(on)
+    Basis2 e;
+    const double ir = rcp(r);
+    e.un = mn * ir;
+    e.ut = mt * ir;
+    e.q2 = e.un * e.un + e.ut * e.ut;
+    const double p = K.gm1 * (E - 0.5 * r * e.q2);
+    e.c = sqrt(K.gamma * p * ir);
+    e.ic = rcp(e.c);
+    e.H = (E + p) * ir;
+    e.b1 = K.gm1 * e.ic * e.ic;
+    e.b2 = 0.5 * e.b1 * e.q2;
+    return e;
+}
+// Row k of L and column k of R = L^-1 (k uniform).
+__device__ __forceinline__ void field_rows(const Basis2& e, int k, double* L, double* R) {
+#pragma clang fp contract(on)
+    if (k == 1) {
+        L[0] = 1.0 - e.b2; L[1] = e.b1 * e.un; L[2] = e.b1 * e.ut; L[3] = -e.b1;
+        R[0] = 1.0; R[1] = e.un; R[2] = e.ut; R[3] = 0.5 * e.q2;
+    } else if (k == 2) {
+        L[0] = -e.ut; L[1] = 0.0; L[2] = 1.0; L[3] = 0.0;
+        R[0] = 0.0; R[1] = 0.0; R[2] = 1.0; R[3] = e.ut;
+    } else {
+        const double sc = k == 0 ? -e.c : e.c, si = k == 0 ? -e.ic : e.ic;
+        L[0] = 0.5 * (e.b2 - e.un * si);
+        L[1] = 0.5 * (si - e.b1 * e.un);
+        L[2] = -0.5 * e.b1 * e.ut;
+        L[3] = 0.5 * e.b1;
+        R[0] = 1.0; R[1] = e.un + sc; R[2] = e.ut; R[3] = e.H + e.un * sc;
+    }
+}
+
+// The 17 stencil data of the field with left eigenvector L: sh holds 12
+// fields of PL doubles, rows of TW; basis b's normal direction is x (b = 0)
+// or y (b = 1).
+template <int b, int TW, int PL>
+__device__ __forceinline__ void project2(const double* sh, const double* L, double* a) {
+#pragma clang fp contract(on)
+    constexpr int sn = b ? TW : 1, st = b ? 1 : TW;   // strides: normal, tangential
+    constexpr int cm[4] = {0, b ? 2 : 1, b ? 1 : 2, 3};
+    constexpr int mn = b ? 8 : 4, mt = b ? 4 : 8;     // moment fields: normal, tangential
+#pragma unroll
+    for (int s = 0; s < 9; ++s) {
+        const double* q = sh + (s % 3 - 1) * sn + (s / 3 - 1) * st;
+        double acc = L[0] * q[cm[0] * PL];
+#pragma unroll
+        for (int c = 1; c < 4; ++c) acc += L[c] * q[cm[c] * PL];
+        a[s] = acc;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int s = 2 * e + 1;
+        const double* q = sh + (s % 3 - 1) * sn + (s / 3 - 1) * st;
+        double an = L[0] * q[(mn + cm[0]) * PL], at_ = L[0] * q[(mt + cm[0]) * PL];
+#pragma unroll
+        for (int c = 1; c < 4; ++c) {
+            an += L[c] * q[(mn + cm[c]) * PL];
+            at_ += L[c] * q[(mt + cm[c]) * PL];
+        }
+        a[9 + e] = an;
+        a[13 + e] = at_;
+    }
+}
+
+template <int TX, bool VarMu, bool FULL>
+__global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_alpha) {
+    constexpr int TY = 64 / TX, TW = TX + 2, TH = TY + 2, PL = TW * TH;
+    constexpr int NP = (PL + 63) / 64;
+    // handed-over values: per basis and field of a wavefront, 9 volume values
+    // (h = 0) or 6 face values and the moment (h = 1) per cell; the second
+    // fields' share reuses the stencil tile's memory
+    constexpr int XB = 2 * (9 + 7) * 64;   // one field of each of the four wavefronts
+    __shared__ double sh[XB + (XB > 12 * PL ? XB : 12 * PL)];
+    __shared__ double shm[2][4][64];       // [density, pressure][wavefront][cell]
+    double* const tile = sh + XB;
+    const Loc lc = locate(bt);
+    const Grid2& gsrc = bt.g[lc.p];   // arrays indexed at run time are read from here
+    if (!gsrc.st->active) return;
+    const Grid2 g = gsrc;
+    const double* __restrict__ S = gsrc.S[si];
+    const Consts& K = g.K;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = wv >> 1, hh = wv & 1;
+    const long long N = g.ncell;
+    // region: rows 1..NY-2, columns 1..NX-2; tiles start at multiples of TX
+    // columns of the ghosted grid
+    const int tiles_x = (g.NX - 1 + TX - 1) / TX;
+    const int i0 = (lc.b % tiles_x) * TX, j0 = 1 + (lc.b / tiles_x) * TY;
+    const int lx = lane % TX, ly = lane / TX;
+    const int i = i0 + lx, j = j0 + ly;
+    const bool valid = i >= 1 && i <= g.NX - 2 && j <= g.NY - 2;
+    // stencil tile: wavefront wv loads fields 3 wv .. 3 wv + 2, every load
+    // issued before the first LDS write
+    {
+        double v[3][NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
+            const int gj = min(j0 - 1 + r, g.NY - 1), gi = min(max(i0 - 1 + c, 0), g.NX - 1);
+            const unsigned src = 8u * (unsigned)(gj * g.NX + gi);
+#pragma unroll
+            for (int f = 0; f < 3; ++f)
+                if (t < PL) v[f][q] = at((gdouble*)S + (3 * wv + f) * N, src);
+        }
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+#pragma unroll
+            for (int f = 0; f < 3; ++f)
+                if (lane + 64 * q < PL) tile[(3 * wv + f) * PL + lane + 64 * q] = v[f][q];
+    }
+    __syncthreads();
+    const double* T0 = tile + (ly + 1) * TW + lx + 1;
+    // cell average: in the global order (pbar: the same bits in every
+    // wavefront) and in the basis's
+    const double rbar = T0[0];
+    const double pbar = pressure2(K, rbar, T0[PL], T0[2 * PL], T0[3 * PL]);
+    const Basis2 e = basis2(K, rbar, T0[(1 + b) * PL], T0[(2 - b) * PL], T0[3 * PL]);
+    // this wavefront's values of its fields at its own points (the last slot
+    // of h = 0: 6 face values, then the moment)
+    double va[9], vb[9];
+#pragma unroll 1
+    for (int kk = 0; kk < 2; ++kk) {
+        const int k = hh == 0 ? 3 * kk : 1 + kk;
+        double C[15];
+        {
+            double L[4], R[4], a[17];
+            field_rows(e, k, L, R);
+            if (b == 0) project2<0, TW, PL>(T0, L, a);
+            else project2<1, TW, PL>(T0, L, a);
+            hweno2d(a, K, C);
+        }
+        if (kk == 1) __syncthreads();   // every wavefront has read the tile
+        double* X = sh + kk * XB + b * (XB / 2) + lane;
+        double f[7], w[9];
+        eval_xface(C, f);
+        f[6] = moment_xi(C);
+        eval_vol(C, w);
+        if (hh == 0) {
+#pragma unroll
+            for (int q = 0; q < 9; ++q) X[q * 64] = w[q];
+#pragma unroll
+            for (int q = 0; q < 7; ++q) {
+                va[q] = vb[q];
+                vb[q] = f[q];
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 7; ++q) X[(9 + q) * 64] = f[q];
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                va[q] = vb[q];
+                vb[q] = w[q];
+            }
+        }
+    }
+    __syncthreads();
+    // the four conserved components (basis order) at own point o, from the
+    // fields' values x0, x3 (acoustic), x1, x2 there; contraction fixed in the
+    // source here and below, for the same bits in every variant of the kernel
+    auto cons = [&](double x0, double x1, double x2, double x3, double* u) {
+#pragma clang fp contract(off)
+        const double sm = x0 + x3, df = x3 - x0;
+        u[0] = sm + x1;
+        u[1] = fma(e.un, u[0], e.c * df);
+        u[2] = fma(e.ut, u[0], x2);
+        u[3] = fma(e.H, sm, fma(e.un * e.c, df, fma(0.5 * e.q2, x1, e.ut * x2)));
+    };
+    const double* XP = sh + b * (XB / 2) + lane;   // partner's values: + kk * XB
+    // planes of the components and of the volume points in global ordering
+    const int gc[4] = {0, 1 + b, 2 - b, 3};
+    auto gq = [&](int q) { return b ? 3 * (q % 3) + q / 3 : q; };
+    const unsigned off = 8u * (unsigned)(j * g.NX + i);
+    const bool inter = valid && j >= HALO && j < HALO + g.ny && i >= HALO && i < HALO + g.nx;
+    double rmin = INFINITY, pmin = INFINITY;
+    double v[4][6];      // h = 0: the components at the face points
+    if (hh == 0) {
+#pragma unroll
+        for (int o = 0; o < 7; ++o) {
+            double u[4];
+            cons(va[o], XP[(9 + o) * 64], XP[XB + (9 + o) * 64], vb[o], u);
+            if (o < 6) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c][o] = u[c];
+                rmin = fmin(rmin, u[0]);
+                pmin = fmin(pmin, pressure2(K, u[0], u[1], u[2], u[3]));
+            } else if (inter) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) at(g.vk + (b * 4 + gc[c]) * N, off) = u[c];
+            }
+        }
+    } else if (valid) {
+        // volume points (unlimited): wbar of (u, v, e), and the compact data of
+        // the gradient kernel's volume flux (Gauss sum of the convective flux,
+        // velocities and, with mu(T), T / T_ref at the points: the power law's
+        // registers would cost this kernel spills)
+#pragma clang fp contract(off)
+        double sn = 0.0, st = 0.0, se = 0.0, fs[4] = {0.0, 0.0, 0.0, 0.0};
+        gdouble* VC = g.vc + (long long)b * VC_B * N;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            double u[4];
+            cons(XP[q * 64], va[q], vb[q], XP[XB + q * 64], u);
+            const double w = (q / 3 == 1 ? GW1 : GW0) * (q % 3 == 1 ? GW1 : GW0);
+            const double ir = rcp(u[0]);
+            const double un = u[1] * ir, ut = u[2] * ir;
+            sn = fma(w, un, sn);
+            st = fma(w, ut, st);
+            se = fma(w, fma(-0.5, fma(un, un, ut * ut), u[3] * ir), se);
+            const double p = K.gm1 * fma(-0.5, fma(u[1], un, u[2] * ut), u[3]);
+            rmin = fmin(rmin, u[0]);
+            pmin = fmin(pmin, p);
+            fs[0] = fma(w, u[1], fs[0]);
+            fs[1] = fma(w, fma(u[1], un, p), fs[1]);
+            fs[2] = fma(w, u[2] * un, fs[2]);
+            fs[3] = fma(w, (u[3] + p) * un, fs[3]);
+            at(VC + ((b ? 13 : 4) + gq(q)) * N, off) = un;
+            at(VC + ((b ? 4 : 13) + gq(q)) * N, off) = ut;
+            if constexpr (VarMu) at(VC + (22 + gq(q)) * N, off) = (p / u[0]) / K.T_ref;
+            if constexpr (FULL) {   // the reverse mode reads the full volume values
+                gdouble* V = b ? g.yv : g.xv;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) at(V + (gq(q) * 4 + gc[c]) * N, off) = u[c];
+            }
+        }
+        gdouble* WB = g.wb + (long long)b * 3 * N;
+        at(WB + b * N, off) = sn;
+        at(WB + (1 - b) * N, off) = st;
+        at(WB + 2 * N, off) = se;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) at(VC + gc[c] * N, off) = fs[c];
+    }
+    // positivity limiter: theta1 from the least density, theta2 from the least
+    // pressure over the points of both bases ((pbar - eps) / (pbar - p) falls
+    // with p, so its minimum is taken at the least pressure)
+    shm[0][wv][lane] = rmin;
+    shm[1][wv][lane] = pmin;
+    __syncthreads();
+    auto least = [&](int q) {
+        return fmin(fmin(shm[q][0][lane], shm[q][1][lane]), fmin(shm[q][2][lane], shm[q][3][lane]));
+    };
+    rmin = least(0);
+    pmin = least(1);
+    const double eps = fmin(fmin(K.eps_pp, rbar), pbar);
+    double th1 = 1.0;
+    // every wavefront holds the same cells and minima: the branch is taken by
+    // the whole block or not at all
+    if (__ballot(valid && rmin < eps)) {
+        th1 = rmin < eps ? (rbar - eps) / (rbar - rmin) : 1.0;
+        // pressures at the limited densities
+        pmin = INFINITY;
+        if (hh == 0) {
+#pragma unroll
+            for (int o = 0; o < 6; ++o) {
+                v[0][o] = rbar + th1 * (v[0][o] - rbar);
+                pmin = fmin(pmin, pressure2(K, v[0][o], v[1][o], v[2][o], v[3][o]));
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                double u[4];
+                cons(XP[q * 64], va[q], vb[q], XP[XB + q * 64], u);
+                pmin = fmin(pmin, pressure2(K, rbar + th1 * (u[0] - rbar), u[1], u[2], u[3]));
+            }
+        }
+        __syncthreads();   // the unlimited minima have been read
+        shm[1][wv][lane] = pmin;
+        __syncthreads();
+        pmin = least(1);
+    }
+    if (hh != 0) return;
+    const bool acted = valid && (th1 < 1.0 || pmin < eps);
+    if (__ballot(acted)) {
+        if (acted) {
+            const double th2 = pmin < eps ? fmin((pbar - eps) / (pbar - pmin), 1.0) : 1.0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double ub = at((gdouble*)S + gc[c] * N, off);
+#pragma unroll
+                for (int o = 0; o < 6; ++o) v[c][o] = ub + th2 * (v[c][o] - ub);
+            }
+        }
+        const unsigned long long n = __ballot(inter && acted);
+        if (b == 0 && lane == 0 && n)
+            atomicAdd((unsigned long long*)&gsrc.red->pp_cells, (unsigned long long)__popcll(n));
+    }
+    if (valid) {
+        gdouble* F = b ? g.yf : g.xf;
+#pragma unroll
+        for (int o = 0; o < 6; ++o)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) at(F + (o * 4 + gc[c]) * N, off) = v[c][o];
+    }
+    // CFL wave speed over the limited face traces of interior cells
+    if (want_alpha) {
+        double amax = -INFINITY;
+#pragma unroll
+        for (int o = 0; o < 6; ++o) {
+            const double ir = rcp(v[0][o]);
+            const double un = v[1][o] * ir, ut = v[2][o] * ir;
+            const double p = K.gm1 * fma(-0.5, fma(v[1][o], un, v[2][o] * ut), v[3][o]);
+            amax = fmax(amax, fmax(fabs(un), fabs(ut)) + sqrt(K.gamma * p * ir));
+        }
+        amax = wave_max(inter ? amax : -INFINITY);
+        if (lane == 0) {
+            const unsigned long long k = dkey(amax);
+            HW_GLOBAL unsigned long long* slot = &gsrc.red->alpha_key;
+            if (amax > -INFINITY && k > *(volatile HW_GLOBAL unsigned long long*)slot)
+                atomicMax((unsigned long long*)slot, k);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Characteristic reconstruction + positivity limiter, HWENO-DR (eq. (3.5)).
 // Block: 32 cells x 8 threads; thread (b, k) projects onto characteristic
 // field k of basis b (0: x-Jacobian, 1: y-Jacobian), reconstructs it, and
-// after an LDS exchange owns conservative component k of basis b.
-// DR (the comparison scheme HWENO-DR, eq. (3.5)): the thread also
-// differentiates its field's combination in xi and eta at the basis's face
+// after an LDS exchange owns conservative component k of basis b.  The thread
+// also differentiates its field's combination in xi and eta at the basis's face
 // and volume points (weights kept), the derivatives go back to conservative
 // variables through the same exchange, and the viscous gradients
 // s = (u_x, u_y, v_x, v_y, e_x, e_y) are formed with the point values that
@@ -326,8 +671,8 @@ __global__ void k_ghost2(Batch bt, int sidx, int stage) {
 // gradients and the volume-flux quadratures itself, in place of the
 // weak-moment and gradient kernels.
 // ---------------------------------------------------------------------------
-template <int RC_CELLS, bool DR = false, bool VarMu = false, bool FULL = false>
-__global__ __launch_bounds__(8 * RC_CELLS) void k_recon2(Batch bt, int si) {
+template <int RC_CELLS, bool VarMu>
+__global__ __launch_bounds__(8 * RC_CELLS) void k_recon2_dr(Batch bt, int si) {
     // one block = RC_CELLS consecutive cells of one row; the 3-row stencil
     // tile of all 12 fields is staged in LDS first, then the same memory holds
     // the exchange of the 16 outputs of every (basis, field) thread
@@ -489,72 +834,6 @@ __global__ __launch_bounds__(8 * RC_CELLS) void k_recon2(Batch bt, int si) {
             F[o * 4 * N] = ub[k] + th2 * (ut - ub[k]);
         }
     }
-    // HWENO-GR: wbar of (u, v, e) from this basis' unlimited volume values,
-    // and the compact volume data of the gradient kernel's volume flux: the
-    // Gauss sum of this basis' convective flux and the velocities (and
-    // viscosities) at the points.  Thread k takes the volume points q = k,
-    // k+4, k+8; the partial sums meet in LDS.  (HWENO-DR forms its volume
-    // fluxes below and needs none of this.)
-    if constexpr (!DR) {
-        double su = 0.0, sv = 0.0, se = 0.0;
-        double fs[4] = {0.0, 0.0, 0.0, 0.0};
-        double* VC = g.vc + (long long)b * VC_B * N + cell;
-        for (int q = k; q < 9; q += 4) {
-            const int o = 6 + q;
-            const double w = (q / 3 == 1 ? GW1 : GW0) * (q % 3 == 1 ? GW1 : GW0);
-            const double r = comp(b, 0, o), m = comp(b, 1, o), n = comp(b, 2, o);
-            const double E = comp(b, 3, o);
-            const double ir = rcp(r);
-            const double u = m * ir, v = n * ir;
-            const double e = E * ir - 0.5 * (u * u + v * v);
-            su += w * u;
-            sv += w * v;
-            se += w * e;
-            double fc[4], mu;
-            conv2_dir<VarMu>(K, r, m, n, E, u, v, b == 1, fc, mu);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) fs[c] += w * fc[c];
-            if (valid) {
-                VC[(4 + q) * N] = u;
-                VC[(13 + q) * N] = v;
-                if constexpr (VarMu) VC[(22 + q) * N] = mu;
-            }
-        }
-        __syncthreads();   // theta2 and the volume slots of sh are read
-        // the partial sums go to the thread's own volume slots 6..12
-        sh[(bk * 16 + 10) * RC_CELLS + cl] = su;
-        sh[(bk * 16 + 11) * RC_CELLS + cl] = sv;
-        sh[(bk * 16 + 12) * RC_CELLS + cl] = se;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) sh[(bk * 16 + 6 + c) * RC_CELLS + cl] = fs[c];
-        __syncthreads();
-        if (valid && k == 0) {
-            double tu = 0.0, tv = 0.0, te = 0.0;
-#pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                tu += sh[((b * 4 + f) * 16 + 10) * RC_CELLS + cl];
-                tv += sh[((b * 4 + f) * 16 + 11) * RC_CELLS + cl];
-                te += sh[((b * 4 + f) * 16 + 12) * RC_CELLS + cl];
-            }
-            g.wb[(b * 3 + 0) * N + cell] = tu;
-            g.wb[(b * 3 + 1) * N + cell] = tv;
-            g.wb[(b * 3 + 2) * N + cell] = te;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                double acc = 0.0;
-#pragma unroll
-                for (int f = 0; f < 4; ++f) acc += sh[((b * 4 + f) * 16 + 6 + c) * RC_CELLS + cl];
-                VC[c * N] = acc;
-            }
-        }
-        if constexpr (FULL) {   // the reverse mode reads the full volume values
-            if (valid) {
-                double* V = (b == 0 ? g.xv : g.yv) + k * N + cell;
-#pragma unroll
-                for (int q = 0; q < 9; ++q) V[q * 4 * N] = U[6 + q];
-            }
-        }
-    }
     if (inter) g.vk[(b * 4 + k) * N + cell] = U[15];
     // CFL wave speed over the limited face traces of interior cells; thread k
     // takes the face points o = k, k+4
@@ -575,118 +854,116 @@ __global__ __launch_bounds__(8 * RC_CELLS) void k_recon2(Batch bt, int si) {
             amax = fmax(amax, sp);
         }
     }
-    if constexpr (DR) {
-        // thread k converts the points o = k, k+4, k+8, k+12 of basis b:
-        // gather the four components of the point values (limited on the
-        // faces) and of their two derivatives from the exchange
-        double P[4][4], Dx[4][4], Dy[4][4];
+    // thread k converts the points o = k, k+4, k+8, k+12 of basis b:
+    // gather the four components of the point values (limited on the
+    // faces) and of their two derivatives from the exchange
+    double P[4][4], Dx[4][4], Dy[4][4];
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-            const int o = k + 4 * s4;
+    for (int s4 = 0; s4 < 4; ++s4) {
+        const int o = k + 4 * s4;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (o < 15) {
-                    const double x = comp(b, c, o);
-                    const double ut = c == 0 ? rbar + th1 * (x - rbar) : x;
-                    P[s4][c] = o < 6 ? ub[c] + th2 * (ut - ub[c]) : x;
-                } else {
-                    P[s4][c] = 1.0;
-                }
+        for (int c = 0; c < 4; ++c) {
+            if (o < 15) {
+                const double x = comp(b, c, o);
+                const double ut = c == 0 ? rbar + th1 * (x - rbar) : x;
+                P[s4][c] = o < 6 ? ub[c] + th2 * (ut - ub[c]) : x;
+            } else {
+                P[s4][c] = 1.0;
             }
         }
-        // the derivatives of this field's combination in xi, then eta, at the
-        // 15 points; back to conservative component k through the exchange
-        // (as the values), then a second exchange hands each thread the four
-        // components at its points
+    }
+    // the derivatives of this field's combination in xi, then eta, at the
+    // 15 points; back to conservative component k through the exchange
+    // (as the values), then a second exchange hands each thread the four
+    // components at its points
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+        double dv[15];
+        {
+            double D[15];
+            if (dir == 0) dxi_coeffs(C, D);
+            else deta_coeffs(C, D);
+            if (b == 0) eval_xface(D, dv);
+            else eval_yface(D, dv);
+            eval_vol(D, dv + 6);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int o = 0; o < 15; ++o) sh[(bk * 16 + o) * RC_CELLS + cl] = dv[o];
+        __syncthreads();
+        const double h = dir == 0 ? K.idx : K.idy;
+#pragma unroll
+        for (int o = 0; o < 15; ++o) {
+            double acc = 0.0;
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+                acc += Rr[f] * sh[((b * 4 + f) * 16 + o) * RC_CELLS + cl];
+            dv[o] = acc * h;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int o = 0; o < 15; ++o) sh[(bk * 16 + o) * RC_CELLS + cl] = dv[o];
+        __syncthreads();
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) {
+            const int o = min(k + 4 * s4, 14);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double x = sh[((b * 4 + c) * 16 + o) * RC_CELLS + cl];
+                if (dir == 0) Dx[s4][c] = x;
+                else Dy[s4][c] = x;
+            }
+        }
+    }
+    // faces of interior cells read the gradients of the cells on both
+    // sides; volume fluxes are needed in interior cells only
+    const bool ring = valid && j >= HALO - 1 && j <= HALO + g.ny && i >= HALO - 1 &&
+                      i <= HALO + g.nx;
+    double vfs[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4) {
+        const int o = k + 4 * s4;
+        if (o >= 15 || !ring) continue;
+        const double ir = rcp(P[s4][0]);
+        const double u = P[s4][1] * ir, v = P[s4][2] * ir, eo = P[s4][3] * ir;
+        double sg[6];
 #pragma unroll
         for (int dir = 0; dir < 2; ++dir) {
-            double dv[15];
-            {
-                double D[15];
-                if (dir == 0) dxi_coeffs(C, D);
-                else deta_coeffs(C, D);
-                if (b == 0) eval_xface(D, dv);
-                else eval_yface(D, dv);
-                eval_vol(D, dv + 6);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int o = 0; o < 15; ++o) sh[(bk * 16 + o) * RC_CELLS + cl] = dv[o];
-            __syncthreads();
-            const double h = dir == 0 ? K.idx : K.idy;
-#pragma unroll
-            for (int o = 0; o < 15; ++o) {
-                double acc = 0.0;
-#pragma unroll
-                for (int f = 0; f < 4; ++f)
-                    acc += Rr[f] * sh[((b * 4 + f) * 16 + o) * RC_CELLS + cl];
-                dv[o] = acc * h;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int o = 0; o < 15; ++o) sh[(bk * 16 + o) * RC_CELLS + cl] = dv[o];
-            __syncthreads();
-#pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4) {
-                const int o = min(k + 4 * s4, 14);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const double x = sh[((b * 4 + c) * 16 + o) * RC_CELLS + cl];
-                    if (dir == 0) Dx[s4][c] = x;
-                    else Dy[s4][c] = x;
-                }
-            }
+            const double* D = dir == 0 ? Dx[s4] : Dy[s4];
+            const double ul = (D[1] - u * D[0]) * ir;
+            const double vl = (D[2] - v * D[0]) * ir;
+            const double el = (D[3] - eo * D[0]) * ir - u * ul - v * vl;
+            sg[0 + dir] = ul;
+            sg[2 + dir] = vl;
+            sg[4 + dir] = el;
         }
-        // faces of interior cells read the gradients of the cells on both
-        // sides; volume fluxes are needed in interior cells only
-        const bool ring = valid && j >= HALO - 1 && j <= HALO + g.ny && i >= HALO - 1 &&
-                          i <= HALO + g.nx;
-        double vfs[4] = {0.0, 0.0, 0.0, 0.0};
+        if (o < 6) {
+            const int p = b * 6 + o;
+            double dc[3];
+            if (b == 0) stress_combos<0>(sg, dc);
+            else stress_combos<1>(sg, dc);
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-            const int o = k + 4 * s4;
-            if (o >= 15 || !ring) continue;
-            const double ir = rcp(P[s4][0]);
-            const double u = P[s4][1] * ir, v = P[s4][2] * ir, eo = P[s4][3] * ir;
-            double sg[6];
+            for (int z = 0; z < 3; ++z) g.gf[(p * 3 + z) * N + cell] = dc[z];
+        } else {
+            const int q = o - 6;
+            const double w = (q / 3 == 1 ? GW1 : GW0) * (q % 3 == 1 ? GW1 : GW0);
+            double f[4];
+            flux2_dir<VarMu>(K, P[s4], sg, b == 1, f);
 #pragma unroll
-            for (int dir = 0; dir < 2; ++dir) {
-                const double* D = dir == 0 ? Dx[s4] : Dy[s4];
-                const double ul = (D[1] - u * D[0]) * ir;
-                const double vl = (D[2] - v * D[0]) * ir;
-                const double el = (D[3] - eo * D[0]) * ir - u * ul - v * vl;
-                sg[0 + dir] = ul;
-                sg[2 + dir] = vl;
-                sg[4 + dir] = el;
-            }
-            if (o < 6) {
-                const int p = b * 6 + o;
-                double dc[3];
-                if (b == 0) stress_combos<0>(sg, dc);
-                else stress_combos<1>(sg, dc);
-#pragma unroll
-                for (int z = 0; z < 3; ++z) g.gf[(p * 3 + z) * N + cell] = dc[z];
-            } else {
-                const int q = o - 6;
-                const double w = (q / 3 == 1 ? GW1 : GW0) * (q % 3 == 1 ? GW1 : GW0);
-                double f[4];
-                flux2_dir<VarMu>(K, P[s4], sg, b == 1, f);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) vfs[c] += w * f[c];
-            }
+            for (int c = 0; c < 4; ++c) vfs[c] += w * f[c];
         }
-        __syncthreads();
+    }
+    __syncthreads();
 #pragma unroll
-        for (int c = 0; c < 4; ++c) sh[(bk * 16 + c) * RC_CELLS + cl] = vfs[c];
-        __syncthreads();
-        if (inter && k == 0) {
+    for (int c = 0; c < 4; ++c) sh[(bk * 16 + c) * RC_CELLS + cl] = vfs[c];
+    __syncthreads();
+    if (inter && k == 0) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                double acc = 0.0;
+        for (int c = 0; c < 4; ++c) {
+            double acc = 0.0;
 #pragma unroll
-                for (int f = 0; f < 4; ++f) acc += sh[((b * 4 + f) * 16 + c) * RC_CELLS + cl];
-                g.vf[(b * 4 + c) * N + cell] = acc;
-            }
+            for (int f = 0; f < 4; ++f) acc += sh[((b * 4 + f) * 16 + c) * RC_CELLS + cl];
+            g.vf[(b * 4 + c) * N + cell] = acc;
         }
     }
     // the block reductions use moment slots of the exchange: past the
@@ -887,7 +1164,7 @@ __device__ __forceinline__ void grad_body(const Grid2& g, double* shv, const dou
     const bool inter = valid && j >= HALO && j < HALO + g.ny && i >= HALO && i < HALO + g.nx;
     // volume-flux quadratures of interior cells: the reconstruction kernel
     // left the Gauss sum of the convective flux and the velocities (and
-    // viscosities) at the points; the viscous part is summed here over the
+    // temperatures) at the points; the viscous part is summed here over the
     // cell's 6 threads, 2 directions x 9 points, 3 points each (thread s:
     // direction s / 3, points 3 (s % 3) .. 3 (s % 3) + 2), and the partial
     // sums meet in LDS.  The point data are loaded before the barrier.
@@ -900,7 +1177,7 @@ __device__ __forceinline__ void grad_body(const Grid2& g, double* shv, const dou
         for (int qq = 0; qq < 3; ++qq) {
             pu[qq] = VC[(4 + q0 + qq) * N];
             pv[qq] = VC[(13 + q0 + qq) * N];
-            pm[qq] = VarMu ? VC[(22 + q0 + qq) * N] : K.mu_ref;
+            pm[qq] = VarMu ? viscosity_T(K, VC[(22 + q0 + qq) * N]) : K.mu_ref;
         }
     }
 #pragma unroll
@@ -1801,8 +2078,11 @@ void batch_blocks(const Grid2* hg, int n, const Tiles& t, int* out) {
             int per = 256;
             switch (k) {
                 case KB_GHOST: work = (long long)(g.ny + g.NX) * 2 * HALO; break;
-                case KB_RECON:   // row segments of t.recon cells
-                    work = (long long)(g.NY - 2) * ((g.NX - 2 + t.recon - 1) / t.recon);
+                case KB_RECON:   // tiles of t.recon x (64 / t.recon) cells, aligned to
+                                 // ghosted columns; HWENO-DR: row segments of t.recon cells
+                    work = g.K.dr ? (long long)(g.NY - 2) * ((g.NX - 2 + t.recon - 1) / t.recon)
+                                  : (long long)((g.NX - 1 + t.recon - 1) / t.recon) *
+                                        ((g.NY - 2 + 64 / t.recon - 1) / (64 / t.recon));
                     per = 1;
                     break;
                 case KB_RBAR:    // tiles of RB_TX x RB_TY cells, aligned to ghosted columns
@@ -1907,31 +2187,35 @@ void launch_flux2(const BatchL& b, hipStream_t st) {
     }
 }
 
-hipError_t launch_residual2(const BatchL& b, int si, hipStream_t st, Timer* tm) {
+// full_grad: the reverse mode also stores the full volume values.
+template <int TX>
+void launch_recon2(const BatchL& b, int si, int alpha, hipStream_t st, Timer* tm) {
+    const unsigned n = b.blocks(KB_RECON);
+    const Batch a = b.arg(KB_RECON);
+    if (b.full_grad) {
+        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, true>, n, 256, st, a, si, alpha);
+        else tlaunch(tm, KC_RECON, k_recon2<TX, false, true>, n, 256, st, a, si, alpha);
+    } else {
+        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, false>, n, 256, st, a, si, alpha);
+        else tlaunch(tm, KC_RECON, k_recon2<TX, false, false>, n, 256, st, a, si, alpha);
+    }
+}
+
+hipError_t launch_residual2(const BatchL& b, int si, hipStream_t st, Timer* tm, bool alpha) {
     const unsigned nr = b.blocks(KB_RECON), ng = b.blocks(KB_GRAD);
     const Batch ar = b.arg(KB_RECON);
     if (b.dr) {   // HWENO-DR: gradients and volume fluxes come with the reconstruction
         if (b.tiles.recon == 16) {
-            if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<16, true, true>, nr, 128, st, ar, si);
-            else tlaunch(tm, KC_RECON, k_recon2<16, true, false>, nr, 128, st, ar, si);
+            if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2_dr<16, true>, nr, 128, st, ar, si);
+            else tlaunch(tm, KC_RECON, k_recon2_dr<16, false>, nr, 128, st, ar, si);
         } else {
-            if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<32, true, true>, nr, 256, st, ar, si);
-            else tlaunch(tm, KC_RECON, k_recon2<32, true, false>, nr, 256, st, ar, si);
-        }
-    } else if (b.full_grad) {   // the reverse mode also stores the full volume values
-        if (b.tiles.recon == 16) {
-            if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<16, false, true, true>, nr, 128, st, ar, si);
-            else tlaunch(tm, KC_RECON, k_recon2<16, false, false, true>, nr, 128, st, ar, si);
-        } else {
-            if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<32, false, true, true>, nr, 256, st, ar, si);
-            else tlaunch(tm, KC_RECON, k_recon2<32, false, false, true>, nr, 256, st, ar, si);
+            if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2_dr<32, true>, nr, 256, st, ar, si);
+            else tlaunch(tm, KC_RECON, k_recon2_dr<32, false>, nr, 256, st, ar, si);
         }
     } else if (b.tiles.recon == 16) {
-        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<16, false, true>, nr, 128, st, ar, si);
-        else tlaunch(tm, KC_RECON, k_recon2<16>, nr, 128, st, ar, si);
+        launch_recon2<16>(b, si, alpha, st, tm);
     } else {
-        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<32, false, true>, nr, 256, st, ar, si);
-        else tlaunch(tm, KC_RECON, k_recon2<32>, nr, 256, st, ar, si);
+        launch_recon2<32>(b, si, alpha, st, tm);
     }
     if (!b.dr && !b.full_grad && b.tiles.grad == 0) {
         // HWENO-GR, weak moments formed inside the gradient kernel

@@ -632,9 +632,11 @@ hweno_status ghost(hweno_ctx* c, int si, int stage = -1) {
     return dev(hw::launch_ghost1(c->g1, c->S1[si], c->stream, c->tm()));
 }
 
-// b: the 2D launch list to use (the stage sets of keep_stages); default the grid's
-hweno_status residual(hweno_ctx* c, int si, const hw::BatchL* b = nullptr) {
-    if (c->dim() == 2) return dev(hw::launch_residual2(b ? *b : c->bl, si, c->stream, c->tm()));
+// b: the 2D launch list to use (the stage sets of keep_stages); default the
+// grid's.  alpha: the CFL wave speed is wanted (2D)
+hweno_status residual(hweno_ctx* c, int si, const hw::BatchL* b = nullptr, bool alpha = true) {
+    if (c->dim() == 2)
+        return dev(hw::launch_residual2(b ? *b : c->bl, si, c->stream, c->tm(), alpha));
     return dev(hw::launch_residual1(c->g1, c->S1[si], c->stream, c->tm()));
 }
 
@@ -751,10 +753,10 @@ hweno_status batch_step(const hw::BatchL& b, hipStream_t st) {
     TRY(dev(hw::launch_dt2(b, st)));
     TRY(dev(hw::launch_update2(b, 1, 0, 0, 1, nullptr, nullptr, st, nullptr)));
     TRY(dev(hw::launch_ghost2(b, 1, st, nullptr)));
-    TRY(dev(hw::launch_residual2(b, 1, st, nullptr)));
+    TRY(dev(hw::launch_residual2(b, 1, st, nullptr, false)));
     TRY(dev(hw::launch_update2(b, 2, 0, 1, 2, nullptr, nullptr, st, nullptr)));
     TRY(dev(hw::launch_ghost2(b, 2, st, nullptr)));
-    TRY(dev(hw::launch_residual2(b, 2, st, nullptr)));
+    TRY(dev(hw::launch_residual2(b, 2, st, nullptr, false)));
     TRY(dev(hw::launch_update2(b, 3, 0, 2, 1, nullptr, nullptr, st, nullptr)));
     return dev(hw::launch_commit2(b, st));
 }
@@ -1308,10 +1310,10 @@ hweno_status step(hweno_ctx* c, double dt, const double* const* src, hweno_diag*
             TRY(dev(hw::launch_set_dt(c->red, cur_dt, c->stream)));
         TRY(update(c, 1, a, a, b, nullptr, nullptr, src1));
         TRY(ghost(c, b, staged ? 1 : -1));
-        TRY(residual(c, b));
+        TRY(residual(c, b, nullptr, false));
         TRY(update(c, 2, a, b, s2, nullptr, nullptr, src2));
         TRY(ghost(c, s2, staged ? 2 : -1));
-        TRY(residual(c, s2));
+        TRY(residual(c, s2, nullptr, false));
         TRY(update(c, 3, a, s2, b, nullptr, nullptr, src3));
         TRY(read_reduce(c, &r));
         if (restarts == 0 && r.bad[0] != 0) return HWENO_E_NONFINITE;

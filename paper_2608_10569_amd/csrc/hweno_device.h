@@ -79,10 +79,14 @@ __device__ __forceinline__ Consts grad_consts(const Consts& K) {
 // mu(T) = mu_ref (T / T_ref)^mu_exp.  VarMu = false builds code that serves
 // constant viscosity only (mu_exp = 0 in every instance of a launch): the
 // power law, and the registers its code needs, stay out of such kernels.
+// viscosity_T: x = T / T_ref.
+__device__ __forceinline__ double viscosity_T(const Consts& K, double x) {
+    return K.mu_exp == 0.0 ? K.mu_ref : K.mu_ref * pow(x, K.mu_exp);
+}
 template <bool VarMu = true>
 __device__ __forceinline__ double viscosity(const Consts& K, double rho, double p) {
     if (!VarMu || K.mu_exp == 0.0) return K.mu_ref;
-    return K.mu_ref * pow((p / rho) / K.T_ref, K.mu_exp);
+    return viscosity_T(K, (p / rho) / K.T_ref);
 }
 
 // ---------------------------------------------------------------------------
@@ -158,8 +162,12 @@ __device__ __forceinline__ void deval1d(const double* __restrict__ C, double* __
 // monomial index of xi^a eta^b
 #define MI(a, b) ((((a) + (b)) * ((a) + (b) + 1)) / 2 + (b))
 
+// contract(on) here and in the evaluators below: products and sums are fused as
+// the source groups them, whichever kernel inlines this, so that the kernels'
+// variants agree bit for bit.
 __device__ __forceinline__ void hweno2d(const double* __restrict__ a, const Consts& K,
                                         double* __restrict__ C) {
+#pragma clang fp contract(on)
     double c0[15];
     hweno_gen::p0_2d(a, c0);
     const double a2 = a[1], a4 = a[3], a5 = a[4], a6 = a[5], a8 = a[7];
@@ -219,6 +227,7 @@ __device__ __forceinline__ void hweno2d(const double* __restrict__ a, const Cons
 // Values on the x-faces: out[0..2] at (-1/2, eta_G), out[3..5] at (1/2, eta_G),
 // eta_G = (-s, 0, s).
 __device__ __forceinline__ void eval_xface(const double* __restrict__ C, double* __restrict__ out) {
+#pragma clang fp contract(on)
     // E_b, O_b: even / odd parts in xi at |xi| = 1/2, for each power b of eta
     const double E0 = C[MI(0, 0)] + 0.25 * C[MI(2, 0)] + 0.0625 * C[MI(4, 0)];
     const double O0 = 0.5 * C[MI(1, 0)] + 0.125 * C[MI(3, 0)];
@@ -244,6 +253,7 @@ __device__ __forceinline__ void eval_xface(const double* __restrict__ C, double*
 
 // Values on the y-faces: out[0..2] at (xi_G, -1/2), out[3..5] at (xi_G, 1/2).
 __device__ __forceinline__ void eval_yface(const double* __restrict__ C, double* __restrict__ out) {
+#pragma clang fp contract(on)
     const double E0 = C[MI(0, 0)] + 0.25 * C[MI(0, 2)] + 0.0625 * C[MI(0, 4)];
     const double O0 = 0.5 * C[MI(0, 1)] + 0.125 * C[MI(0, 3)];
     const double E1 = C[MI(1, 0)] + 0.25 * C[MI(1, 2)];
@@ -268,6 +278,7 @@ __device__ __forceinline__ void eval_yface(const double* __restrict__ C, double*
 
 // Values at the 3x3 tensor Gauss points: out[3*h + g] at (xi_g, eta_h).
 __device__ __forceinline__ void eval_vol(const double* __restrict__ C, double* __restrict__ out) {
+#pragma clang fp contract(on)
     // r_a(eta): polynomial in xi with coefficients depending on eta
     double rm[5], r0[5], rp[5];
 #pragma unroll
@@ -315,9 +326,11 @@ __device__ __forceinline__ void deta_coeffs(const double* __restrict__ C, double
 
 // Scaled first moments over the own cell: int p xi, int p eta.
 __device__ __forceinline__ double moment_xi(const double* __restrict__ C) {
+#pragma clang fp contract(on)
     return C[MI(1, 0)] * (1.0 / 12.0) + C[MI(1, 2)] * (1.0 / 144.0) + C[MI(3, 0)] * (1.0 / 80.0);
 }
 __device__ __forceinline__ double moment_eta(const double* __restrict__ C) {
+#pragma clang fp contract(on)
     return C[MI(0, 1)] * (1.0 / 12.0) + C[MI(2, 1)] * (1.0 / 144.0) + C[MI(0, 3)] * (1.0 / 80.0);
 }
 
@@ -480,25 +493,9 @@ __device__ __forceinline__ void flux2_dir(const Consts& K, const double* U, cons
     f[3] = fma(E + p, un, -fma(tnx, u, fma(tny, v, kq * qd)));
 }
 
-// The two parts of flux2_dir at a volume point, for a volume quadrature
-// split between two kernels: the convective flux (and the point's
-// viscosity) from the reconstructed state, given u = m / rho and v = n / rho
-// as flux2_dir forms them; and the viscous part of components 1..3 from the
-// velocities, that viscosity and the six gradients s.  Their sum is
-// flux2_dir's flux up to rounding.
-template <bool VarMu>
-__device__ __forceinline__ void conv2_dir(const Consts& K, double r, double m, double n, double E,
-                                          double u, double v, bool dy, double* f, double& mu) {
-#pragma clang fp contract(off)
-    const double p = K.gm1 * fma(-0.5, fma(m, u, n * v), E);
-    mu = viscosity<VarMu>(K, r, p);
-    const double un = dy ? v : u;
-    f[0] = dy ? n : m;
-    f[1] = fma(m, un, (dy ? 0.0 : p));
-    f[2] = fma(n, un, (dy ? p : 0.0));
-    f[3] = (E + p) * un;
-}
-
+// The viscous part of flux2_dir's components 1..3 at a volume point, from the
+// velocities, the viscosity and the six gradients s (the reconstruction kernel
+// sums the convective part).
 __device__ __forceinline__ void visc2_dir(const Consts& K, double u, double v, double mu,
                                           const double* s, bool dy, double* f) {
 #pragma clang fp contract(off)

@@ -39,6 +39,7 @@ __device__ __forceinline__ double sobolev_1d(const double* __restrict__ c) {
 // cells 1..9 (row-major from (i-1,j-1)), a[9..12] = xi-moments of cells
 // 2,4,6,8, a[13..16] = eta-moments of cells 2,4,6,8 -> c[15] in monomial order.
 __device__ __forceinline__ void p0_2d(const double* __restrict__ a, double* __restrict__ c) {
+#pragma clang fp contract(on)
     const double a1 = a[0];
     const double a2 = a[1];
     const double a3 = a[2];

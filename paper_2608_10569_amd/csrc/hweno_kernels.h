@@ -64,7 +64,7 @@ struct InstState {
 };
 
 // Compact volume data per basis: the convective flux sum and the point
-// velocities and viscosities the gradient kernel's viscous volume flux needs.
+// velocities and temperatures the gradient kernel's viscous volume flux needs.
 constexpr int VC_B = 31;
 
 // Pointers and sizes of one 2D grid's workspace (all arrays SoA over the
@@ -82,8 +82,8 @@ struct Grid2 {
                    // for the reverse mode (full_grad), which reads them
     gdouble* yv;   // 36: y-basis volume values (likewise)
     gdouble* vc;   // 2 * VC_B: per basis b (x for f, y for g), at b * VC_B: the
-                   // Gauss sum of the convective flux (4), then u, v and mu at
-                   // the nine volume points (9 each; mu only with mu(T))
+                   // Gauss sum of the convective flux (4), then u, v and T / T_ref at
+                   // the nine volume points (9 each; the latter only with mu(T))
     gdouble* wb;   // 6:  wbar of (u, v, e) from x-basis, then from y-basis
     gdouble* vk;   // 8:  modified moments of the current input (hat-v 0..3, hat-w 4..7)
     gdouble* vn;   // 8:  modified moments of U^n (kept for stages 2 and 3)
@@ -216,7 +216,8 @@ struct Batch {
 
 // Work per block of the tunable kernels (cells, cells, faces).
 struct Tiles {
-    int recon = 32;   // 16 or 32
+    int recon = 32;   // 16 or 32 (columns of the reconstruction's 64-cell tiles; HWENO-DR:
+                      // cells per block)
     int grad = 32;    // 32 or 64; 0: weak moments formed in the gradient kernel
                       // (tiles of 16 x 4 cells)
     int flux = 0;     // 64 or 128; 0: face fluxes formed inside the update kernel
@@ -260,7 +261,10 @@ hipError_t launch_ghost2(const BatchL& b, int si, hipStream_t st, Timer* tm, int
 // Mirror fill of the solid cells next to the fluid of a single masked grid
 // (before the box halo); `g` is the device descriptor, n its nsolid.
 hipError_t launch_solid2(const Grid2* g, int n, int si, hipStream_t st);
-hipError_t launch_residual2(const BatchL& b, int si, hipStream_t st, Timer* tm);
+// alpha: the reconstruction also reduces the CFL wave speed (stage 1 and single
+// residuals; nothing reads it after the later stages)
+hipError_t launch_residual2(const BatchL& b, int si, hipStream_t st, Timer* tm,
+                            bool alpha = true);
 // stage 0: write R (12) and Vhat (8) in interior layout (single grid);
 // stage 1..3: RK update S[iout] from S[i0] (U^n) and S[iin] (stage input);
 // src (single grid, may be null): source moments added to the residual
