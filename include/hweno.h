@@ -372,7 +372,8 @@ HWENO_API hweno_status hweno_take_mu_bar(hweno_ctx* ctx, double* mu_bar);
  * 0 ghost fill, 1 characteristic reconstruction + limiter, 2 weak-derivative
  * moments, 3 gradient reconstruction + volume flux, 4 face fluxes, 5 stage
  * update / assembly, 6 a whole batched run (hweno_batch_run), 7 face fluxes
- * fused with the stage update / assembly (tiles.flux = 0). */
+ * fused with the stage update / assembly (tiles.flux = 0); on 1D grids a
+ * whole stage, which is one kernel, in class 7. */
 typedef struct hweno_timing {
     double ms[8];                       /* summed elapsed milliseconds */
     unsigned long long launches[8];     /* timed launches */

@@ -63,6 +63,10 @@ struct hweno_ctx {
     // the reverse mode's recomputed stages
     double* S1[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     hw::Grid1 g1{};
+    // reduction slots red[1 + k] of the 1D steps, used in turn: a step's last
+    // kernel resets the slots of the next (red_clean[k]: they are reset)
+    int red_turn = 0;
+    bool red_clean[2] = {false, false};
     // reverse mode (single 2D grid; 1D grid)
     hw::AdjWs adj{};
     hw::AdjWs1 adj1{};
@@ -239,7 +243,8 @@ size_t layout(hweno_ctx* c, char* base) {
         g.gr = take(8 * m);
         g.fh = take(3 * m);
         g.vf = take(3 * m);
-        c->red = reinterpret_cast<hw::Reduce*>(take_bytes(sizeof(hw::Reduce)));
+        g.fr = take(6 * m);
+        c->red = reinterpret_cast<hw::Reduce*>(take_bytes(3 * sizeof(hw::Reduce)));
         g.red = (HW_GLOBAL hw::Reduce*)c->red;
         // reverse-mode workspace (the first three arrays zero-filled by every
         // adjoint call, in one region)
@@ -640,13 +645,47 @@ hweno_status residual(hweno_ctx* c, int si, const hw::BatchL* b = nullptr, bool 
     return dev(hw::launch_residual1(c->g1, c->S1[si], c->stream, c->tm()));
 }
 
+// 2D
 hweno_status update(hweno_ctx* c, int stage, int i0, int iin, int iout, double* R, double* V,
                     const double* src = nullptr, const hw::BatchL* b = nullptr) {
-    if (c->dim() == 2)
-        return dev(hw::launch_update2(b ? *b : c->bl, stage, i0, iin, iout, R, V, c->stream,
-                                      c->tm(), src));
-    return dev(hw::launch_update1(c->g1, stage, c->S1[i0], c->S1[iin], c->S1[iout], R, V,
-                                  c->stream, c->tm(), src));
+    return dev(hw::launch_update2(b ? *b : c->bl, stage, i0, iin, iout, R, V, c->stream, c->tm(),
+                                  src));
+}
+
+// Whether the n doubles at a and the m doubles at b share memory.
+bool overlap(const double* a, size_t n, const double* b, size_t m) {
+    return a < b + m && b < a + n;
+}
+
+// A 1D stage whose input is a ghosted state S of grid g (stage 0: the residual
+// into R and V).
+hw::Stage1 stage1(const hw::Grid1& g, int stage, const double* S) {
+    hw::Stage1 a{};
+    a.stage = stage;
+    a.in = S;
+    a.plane = g.NX;
+    a.first = HALO;
+    return a;
+}
+
+// Residual of a 1D grid at the caller's state U (D1 layout) with the
+// reduction slots g.red; `S` is a ghosted buffer for the case that an output
+// shares memory with U.
+hweno_status residual1(const hw::Grid1& g, const double* U, double* S, double* R, double* V,
+                       hipStream_t st, hw::Timer* tm) {
+    const size_t n = (size_t)g.nx;
+    hw::Stage1 a = stage1(g, 0, S);
+    if (overlap(U, 6 * n, R, 6 * n) || overlap(U, 6 * n, V, 3 * n)) {
+        TRY(dev(hw::launch_copy_in1(g, U, S, st)));
+    } else {
+        a.in = U;
+        a.plane = g.nx;
+        a.first = 0;
+    }
+    a.R = R;
+    a.V = V;
+    TRY(dev(hw::launch_reset((hw::Reduce*)g.red, st)));
+    return dev(hw::launch_stage1(g, a, st, tm));
 }
 
 hweno_status reset(hweno_ctx* c) {
@@ -654,8 +693,8 @@ hweno_status reset(hweno_ctx* c) {
     return dev(hw::launch_reset(c->red, c->stream));
 }
 
-hweno_status read_reduce(hweno_ctx* c, hw::Reduce* r) {
-    TRY(dev(hipMemcpyAsync(r, c->red, sizeof(hw::Reduce), hipMemcpyDeviceToHost, c->stream)));
+hweno_status read_reduce(hweno_ctx* c, const hw::Reduce* red, hw::Reduce* r) {
+    TRY(dev(hipMemcpyAsync(r, red, sizeof(hw::Reduce), hipMemcpyDeviceToHost, c->stream)));
     TRY(dev(hipStreamSynchronize(c->stream)));
     if (c->timer.on) c->timer.collect();
     return HWENO_OK;
@@ -892,6 +931,7 @@ HWENO_API hweno_status hweno_set_workspace(hweno_ctx* c, void* p, size_t bytes) 
     layout(c, c->ws);
     c->has_state = false;
     c->state_checked = false;
+    c->red_clean[0] = c->red_clean[1] = false;
     c->cur = 0;
     std::fill(c->have.begin(), c->have.end(), 0);
     if (c->dim() == 2) {
@@ -1097,15 +1137,18 @@ HWENO_API hweno_status hweno_residual(hweno_ctx* c, const double* U, double* R, 
     GUARD_BEGIN
     if (!c || !U || !R || !V || c->batch) return HWENO_E_INVAL;
     if (!c->ws) return HWENO_E_WORKSPACE;
-    if (c->dim() == 2) TRY(dev(hw::launch_copy_in2(g2(c), U, g2(c).S[2], c->stream)));
-    else TRY(dev(hw::launch_copy_in1(c->g1, U, c->S1[2], c->stream)));
-    TRY(reset(c));
-    TRY(ghost(c, 2));
-    TRY(residual(c, 2));
-    TRY(update(c, 0, 2, 2, 2, R, V));
+    if (c->dim() == 2) {
+        TRY(dev(hw::launch_copy_in2(g2(c), U, g2(c).S[2], c->stream)));
+        TRY(reset(c));
+        TRY(ghost(c, 2));
+        TRY(residual(c, 2));
+        TRY(update(c, 0, 2, 2, 2, R, V));
+    } else {
+        TRY(residual1(c->g1, U, c->S1[2], R, V, c->stream, c->tm()));
+    }
     if (diag) {
         hw::Reduce r;
-        TRY(read_reduce(c, &r));
+        TRY(read_reduce(c, c->red, &r));
         fill_diag(c->t, r, diag, 0, false);
         diag->dt = 0.0;
         diag->min_rho = diag->min_p = NAN;
@@ -1163,28 +1206,15 @@ size_t static_layout2(hw::Grid2& g, char* base, hw::Grid2** dgrid, hw::InstState
     return off;
 }
 
-// The same for a 1D grid: reduction slots, one ghosted state, intermediates.
+// The same for a 1D grid: reduction slots and one ghosted state (every
+// intermediate of the one-launch stage is in registers).  The size returned is
+// the documented limit's, which counts 38 more planes.
 size_t static_layout1(hw::Grid1& g, char* base, double** S) {
-    size_t off = 0;
-    auto take_bytes = [&](size_t nb) -> char* {
-        char* p = base ? base + off : nullptr;
-        off += up(nb);
-        return p;
-    };
-    auto take = [&](size_t nd) -> hw::gdouble* {
-        return (hw::gdouble*)take_bytes(nd * sizeof(double));
-    };
-    const size_t m = (size_t)g.NX;
-    g.red = (HW_GLOBAL hw::Reduce*)take_bytes(sizeof(hw::Reduce));
-    *S = (double*)take(6 * m);
-    g.pts = take(12 * m);
-    g.wb = take(2 * m);
-    g.vk = take(3 * m);
-    g.vn = take(3 * m);
-    g.rb = take(4 * m);
-    g.gr = take(8 * m);
-    g.fh = take(3 * m);
-    g.vf = take(3 * m);
+    const size_t m = (size_t)g.NX * sizeof(double);
+    g.red = (HW_GLOBAL hw::Reduce*)base;
+    *S = base ? reinterpret_cast<double*>(base + up(sizeof(hw::Reduce))) : nullptr;
+    size_t off = up(sizeof(hw::Reduce)) + up(6 * m);
+    for (size_t k : {12, 2, 3, 3, 4, 8, 3, 3}) off += up(k * m);
     return off;
 }
 
@@ -1243,11 +1273,7 @@ HWENO_API hweno_status hweno_residual_noalloc(hweno_ctx* c, const double* U, dou
         TRY(dev(hw::static_scratch(&base)));
         static_layout1(g, static_cast<char*>(base), &S);
         red = (hw::Reduce*)g.red;
-        TRY(dev(hw::launch_copy_in1(g, U, S, st)));
-        TRY(dev(hw::launch_reset(red, st)));
-        TRY(dev(hw::launch_ghost1(g, S, st, nullptr)));
-        TRY(dev(hw::launch_residual1(g, S, st, nullptr)));
-        TRY(dev(hw::launch_update1(g, 0, S, S, S, R, V, st, nullptr)));
+        TRY(residual1(g, U, S, R, V, st, nullptr));
     }
     if (diag) {
         hw::Reduce r;
@@ -1264,6 +1290,42 @@ HWENO_API hweno_status hweno_residual_noalloc(hweno_ctx* c, const double* U, dou
 }  // extern "C"
 
 namespace {
+
+// One attempt of a 1D step of size dt (or by the step rule) from S1[0] into
+// S1[1]: three launches.  U1 lives only inside the second.
+hweno_status attempt1(hweno_ctx* c, bool auto_dt, double dt, double cfl_h, double visc, double t_left, bool check,
+                      const double* const* src, hw::Reduce* r) {
+    const int k = c->red_turn;
+    c->red_turn = 1 - k;
+    hw::Grid1 g = c->g1;
+    hw::Reduce* red = c->red + 1 + k;
+    g.red = (HW_GLOBAL hw::Reduce*)red;
+    if (!c->red_clean[k]) TRY(dev(hw::launch_reset(red, c->stream)));
+    c->red_clean[0] = c->red_clean[1] = false;
+    hw::Stage1 a = stage1(g, 1, c->S1[0]);
+    a.check = check ? 1 : 0;
+    a.src = src ? src[0] : nullptr;
+    TRY(dev(hw::launch_stage1(g, a, c->stream, c->tm())));
+    a = stage1(g, 2, nullptr);
+    a.S0 = c->S1[0];
+    a.out = c->S1[2];
+    a.auto_dt = auto_dt ? 1 : 0;
+    a.dt = dt;
+    a.cfl_h = cfl_h;
+    a.visc_dt = visc;
+    a.t_left = t_left;
+    a.src = src ? src[1] : nullptr;
+    TRY(dev(hw::launch_stage1(g, a, c->stream, c->tm())));
+    a = stage1(g, 3, c->S1[2]);
+    a.S0 = c->S1[0];
+    a.out = c->S1[1];
+    a.src = src ? src[2] : nullptr;
+    a.clear = c->red + 1 + (1 - k);
+    TRY(dev(hw::launch_stage1(g, a, c->stream, c->tm())));
+    TRY(read_reduce(c, red, r));
+    c->red_clean[1 - k] = true;
+    return HWENO_OK;
+}
 
 // One SSP-RK3 step of a single grid (eq. (2.12)); src[k] (may be null) are
 // source moments added to the residual of stage k+1; `staged`: the ghost fill
@@ -1285,9 +1347,9 @@ hweno_status step(hweno_ctx* c, double dt, const double* const* src, hweno_diag*
         return HWENO_OK;
     }
     const int max_halvings = (src || staged) ? 0 : c->i0().opt.max_halvings;
-    // state buffers: 2D by index into Grid2::S (the current one is `cur`);
-    // 1D by index into S1 with S1[0] current
-    const int a = two ? c->cur : 0, b = two ? 1 - c->cur : 1, s2 = 2;
+    // 2D state buffers by index into Grid2::S (the current one is `cur`); 1D
+    // steps take S1[0] to S1[1]
+    const int a = c->cur, b = 1 - c->cur, s2 = 2;
     const double* src1 = src ? src[0] : nullptr;
     const double* src2 = src ? src[1] : nullptr;
     const double* src3 = src ? src[2] : nullptr;
@@ -1295,27 +1357,30 @@ hweno_status step(hweno_ctx* c, double dt, const double* const* src, hweno_diag*
     int restarts = 0;
     hw::Reduce r;
     for (;;) {
-        TRY(reset(c));
         // the input state is checked once: the output of an accepted step
         // already passed the same test in the stage-3 update
-        if (restarts == 0 && !c->state_checked) {
-            if (two) TRY(dev(hw::launch_check2(c->bl, a, c->stream)));
-            else TRY(dev(hw::launch_check1(c->g1, c->S1[0], c->stream)));
+        const bool check = restarts == 0 && !c->state_checked;
+        if (!two) {
+            TRY(attempt1(c, auto_dt && restarts == 0, cur_dt, cfl_h, visc, t_left, check, src,
+                         &r));
+        } else {
+            TRY(reset(c));
+            if (check) TRY(dev(hw::launch_check2(c->bl, a, c->stream)));
+            TRY(ghost(c, a, staged ? 0 : -1));
+            TRY(residual(c, a));
+            if (auto_dt && restarts == 0)
+                TRY(dev(hw::launch_dt(c->red, cfl_h, visc, t_left, c->stream)));
+            else
+                TRY(dev(hw::launch_set_dt(c->red, cur_dt, c->stream)));
+            TRY(update(c, 1, a, a, b, nullptr, nullptr, src1));
+            TRY(ghost(c, b, staged ? 1 : -1));
+            TRY(residual(c, b, nullptr, false));
+            TRY(update(c, 2, a, b, s2, nullptr, nullptr, src2));
+            TRY(ghost(c, s2, staged ? 2 : -1));
+            TRY(residual(c, s2, nullptr, false));
+            TRY(update(c, 3, a, s2, b, nullptr, nullptr, src3));
+            TRY(read_reduce(c, c->red, &r));
         }
-        TRY(ghost(c, a, staged ? 0 : -1));
-        TRY(residual(c, a));
-        if (auto_dt && restarts == 0)
-            TRY(dev(hw::launch_dt(c->red, cfl_h, visc, t_left, c->stream)));
-        else
-            TRY(dev(hw::launch_set_dt(c->red, cur_dt, c->stream)));
-        TRY(update(c, 1, a, a, b, nullptr, nullptr, src1));
-        TRY(ghost(c, b, staged ? 1 : -1));
-        TRY(residual(c, b, nullptr, false));
-        TRY(update(c, 2, a, b, s2, nullptr, nullptr, src2));
-        TRY(ghost(c, s2, staged ? 2 : -1));
-        TRY(residual(c, s2, nullptr, false));
-        TRY(update(c, 3, a, s2, b, nullptr, nullptr, src3));
-        TRY(read_reduce(c, &r));
         if (restarts == 0 && r.bad[0] != 0) return HWENO_E_NONFINITE;
         if (!(r.dt > 0.0) || !std::isfinite(r.dt)) return HWENO_E_NONFINITE;
         if (r.bad[1] == 0 && r.bad[2] == 0 && r.bad[3] == 0) break;
@@ -1459,13 +1524,14 @@ HWENO_API hweno_status hweno_rk_step_vjp(hweno_ctx* c, const double* U0, double 
         const int ia = 2, ib = 3, ic = 4;
         TRY(dev(hw::launch_copy_in1(c->g1, U0, c->S1[ia], c->stream)));
         TRY(reset(c));
-        TRY(dev(hw::launch_set_dt(c->red, dt, c->stream)));
-        TRY(ghost(c, ia));
-        TRY(residual(c, ia));
-        TRY(update(c, 1, ia, ia, ib, nullptr, nullptr));
-        TRY(ghost(c, ib));
-        TRY(residual(c, ib));
-        TRY(update(c, 2, ia, ib, ic, nullptr, nullptr));
+        hw::Stage1 sa = stage1(c->g1, 1, c->S1[ia]);
+        TRY(dev(hw::launch_stage1(c->g1, sa, c->stream, c->tm())));
+        sa = stage1(c->g1, 2, nullptr);
+        sa.S0 = c->S1[ia];
+        sa.u1 = c->S1[ib];
+        sa.out = c->S1[ic];
+        sa.dt = dt;
+        TRY(dev(hw::launch_stage1(c->g1, sa, c->stream, c->tm())));
         auto vjp_at1 = [&](int si, const double* Rb, const double* Vb, double rs, double vs,
                            double* out, int acc) {
             TRY(reset(c));

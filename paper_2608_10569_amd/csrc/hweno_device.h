@@ -595,6 +595,24 @@ __device__ __forceinline__ void eig2_rows(const Consts& K, const double* Ub, int
     }
 }
 
+// The value of lane l - 1 (left) or l + 1 (right) of the wavefront; the end
+// lanes keep their own.  Every lane takes part.
+#if defined(__HIP_DEVICE_COMPILE__)
+template <int CTRL>
+__device__ __forceinline__ double lane_move(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = (int)b, hi = (int)(b >> 32);
+    const int l = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+    const int h = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    return __longlong_as_double(((long long)h << 32) | (unsigned)l);
+}
+__device__ __forceinline__ double from_left(double v) { return lane_move<0x138>(v); }
+__device__ __forceinline__ double from_right(double v) { return lane_move<0x130>(v); }
+#else
+__device__ __forceinline__ double from_left(double v) { return v; }
+__device__ __forceinline__ double from_right(double v) { return v; }
+#endif
+
 // ---------------------------------------------------------------------------
 // Order-preserving maps of doubles to unsigned 64-bit keys (for atomic
 // max / min of doubles of any sign).

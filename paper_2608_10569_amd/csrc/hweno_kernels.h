@@ -119,12 +119,13 @@ struct Grid1 {
     gdouble* gr;   // 8: gradients at the LGL points (p*2 + w)
     gdouble* fh;   // 3: face flux at i+1/2
     gdouble* vf;   // 3: volume flux quadrature
+    gdouble* fr;   // 6: residual of U^n, from the step's first kernel to its second
     HW_GLOBAL Reduce* red;
 };
 
 // Optional per-kernel timing with HIP events on the launch stream.  Kernel
 // classes: 0 ghost, 1 recon, 2 rbar, 3 grad, 4 flux, 5 update, 6 other,
-// 7 face fluxes fused with the update.
+// 7 face fluxes fused with the update (1D: a whole stage).
 enum { KC_GHOST = 0, KC_RECON, KC_RBAR, KC_GRAD, KC_FLUX, KC_UPDATE, KC_OTHER, KC_FLUXUP,
        KC_COUNT };
 
@@ -283,11 +284,27 @@ hipError_t launch_set_dt(Reduce* red, double dt, hipStream_t st);
 hipError_t launch_copy_in1(const Grid1& g, const double* U, double* S, hipStream_t st);
 hipError_t launch_copy_out1(const Grid1& g, const double* S, double* U, hipStream_t st);
 hipError_t launch_ghost1(const Grid1& g, double* S, hipStream_t st, Timer* tm);
+// the residual's intermediates (HWENO-GR), for the reverse mode
 hipError_t launch_residual1(const Grid1& g, const double* S, hipStream_t st, Timer* tm);
-hipError_t launch_update1(const Grid1& g, int stage, const double* S0, const double* Sin,
-                          double* Sout, double* R, double* Vhat, hipStream_t st, Timer* tm,
-                          const double* src = nullptr);
-hipError_t launch_check1(const Grid1& g, const double* S, hipStream_t st);
+// A whole 1D stage in one launch (every intermediate in registers).  Stage 0 writes R and Vhat; stage 1 keeps the residual of U^n
+// and its modified moments (g.fr, g.vn), the wave speeds and the input check;
+// stage 2 forms the step size and U1 from them; stages 2 and 3 write `out`.
+struct Stage1 {
+    int stage;
+    const double* in;      // stage input, planes of `plane` doubles, cell 0 of the interior at
+    long long plane;       // `first` (the ghosted layout or a caller's interior layout)
+    int first;
+    const double* S0;      // U^n, ghosted layout (stages 2, 3)
+    double* out;           // ghosted layout (stages 2, 3)
+    double* u1;            // stage 2: U1 as well (interior cells of the ghosted layout), or null
+    double *R, *V;         // stage 0
+    const double* src;     // source moments added to the residual, or null
+    int auto_dt;           // stage 2: dt by the step rule, or as given
+    double dt, cfl_h, visc_dt, t_left;
+    int check;             // stage 1: count inadmissible input cells
+    Reduce* clear;         // stage 3: reduction slots to reset for the next step, or null
+};
+hipError_t launch_stage1(const Grid1& g, const Stage1& a, hipStream_t st, Timer* tm);
 
 // Library-owned device scratch of the allocation-free residual entry point:
 // one file-scope array per device (its size is fixed at build time and it

@@ -33,7 +33,8 @@ EXPORTS = ('hweno_default_options', 'hweno_create', 'hweno_destroy', 'hweno_work
            'hweno_autotune')
 
 #: kernel classes of hweno_timing ('batch' = a whole hweno_batch_run graph,
-#: 'fluxup' = face fluxes fused with the update, tiles flux = 0)
+#: 'fluxup' = face fluxes fused with the update, tiles flux = 0; 1D: a whole
+#: stage)
 KERNEL_CLASSES = ('ghost', 'recon', 'rbar', 'grad', 'flux', 'update', 'batch', 'fluxup')
 
 
