@@ -28,7 +28,9 @@
  *    caller owns every pointer it passes; the library keeps none after a
  *    call returns, except the workspace given to hweno_set_workspace.
  *  - The library allocates no device memory.  All scratch lives in a
- *    caller-provided workspace of hweno_workspace_bytes() bytes.
+ *    caller-provided workspace of hweno_workspace_bytes() bytes.  A single
+ *    grid's context keeps one page of pinned host memory from its first
+ *    hweno_set_workspace to hweno_destroy.
  *  - Calls are ordered on the HIP stream set with hweno_set_stream (default:
  *    the null stream).  hweno_rk_step and hweno_residual with a non-NULL
  *    diag synchronise that stream once; other calls are asynchronous.
