@@ -372,7 +372,8 @@ HWENO_API hweno_status hweno_take_mu_bar(hweno_ctx* ctx, double* mu_bar);
  * counted); classes 4 and 6 record them on the stream around their launches.
  * Classes:
  * 0 ghost fill, 1 characteristic reconstruction + limiter, 2 weak-derivative
- * moments, 3 gradient reconstruction + volume flux, 4 face fluxes, 5 stage
+ * moments as a kernel of their own (reverse mode), 3 gradient reconstruction
+ * (else with the weak moments) + volume flux, 4 face fluxes, 5 stage
  * update / assembly, 6 a whole batched run (hweno_batch_run), 7 face fluxes
  * fused with the stage update / assembly (tiles.flux = 0); on 1D grids a
  * whole stage, which is one kernel, in class 7. */
@@ -441,12 +442,11 @@ HWENO_API hweno_status hweno_batch_get_diag(hweno_ctx* ctx, int i, hweno_diag* o
 typedef struct hweno_tiles {
     int recon;      /* columns of the characteristic reconstruction's 64-cell tiles: 16
                        (tiles of 16 x 4 cells) or 32 (32 x 2); HWENO-DR: cells per block */
-    int grad;       /* cells per block of the gradient reconstruction: 32 or 64; 0:
-                       the weak moments (eqs. 3.6-3.8) are formed inside the gradient
-                       kernel, per 16 x 4 tile of cells and the ring around it, in
-                       LDS instead of through HBM (same results; the reverse mode's
-                       forward launches keep the separate kernels, whose weak
-                       moments the adjoint reads) */
+    int grad;       /* cells per block of the gradient reconstruction in the reverse
+                       mode's forward launches, which leave the weak moments (eqs.
+                       3.6-3.8) in memory for the adjoint: 64, or 32 (also for 0).
+                       All other launches form the weak moments inside the gradient
+                       kernel, per tile of 32 cells and the ring around it */
     int flux;       /* faces per block of the face-flux kernels: 64 or 128; 0: no
                        separate flux kernels -- the update kernel forms the fluxes
                        of each 32 x 8 tile of cells in LDS (same results) */
@@ -463,10 +463,9 @@ HWENO_API hweno_status hweno_set_tiles(hweno_ctx* ctx, const hweno_tiles* tiles)
 /* Autotuner: times `reps` residual evaluations (each with a stage update) of
  * the current state(s) for each candidate tile of every tunable kernel, keeps
  * the fastest per kernel (for the face fluxes: split or fused into the
- * update, by the time of fluxes plus update; for the weak moments and the
- * gradients: split or fused, by the time of both), then the faster block order
- * and (batches) the faster instance order, and sets them; `chosen` may be
- * NULL.  Needs the state(s) set; leaves them unchanged.  Synchronises. */
+ * update, by the time of fluxes plus update; grad stays as set), then the
+ * faster block order and (batches) the faster instance order, and sets them;
+ * `chosen` may be NULL.  Needs the state(s) set; leaves them unchanged.  Synchronises. */
 HWENO_API hweno_status hweno_autotune(hweno_ctx* ctx, int reps, hweno_tiles* chosen);
 
 #ifdef __cplusplus

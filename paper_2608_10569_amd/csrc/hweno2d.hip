@@ -1110,169 +1110,199 @@ __global__ __launch_bounds__(RB_TX * RB_TY) void k_rbar2(Batch bt) {
 }
 
 // ---------------------------------------------------------------------------
-// Gradient reconstruction (eq. (3.9)) on halo ring 1; block 32 or 64 cells
-// x 6 (thread s = 2*w + l reconstructs d w / d x_l).  Interior cells also
-// form the volume-flux quadratures of eq. (3.2).
+// Gradient reconstruction (eq. (3.9)) on halo ring 1, and on interior cells
+// the volume-flux quadratures of eq. (3.2).
 // ---------------------------------------------------------------------------
-// Gradient reconstruction of component s = 2 w + l of one cell from its 17
-// stencil data a (eq. (3.9)), the face gradients it stores, and on interior
-// cells the volume-flux quadrature of eq. (3.2).  The block has NC cells x 6
-// components (cell cl, component s); shv holds 6 x 9 x NC doubles of LDS.
+// The fluxes need the six gradients only in the combinations of
+// stress_combos, each of a pair of them: (u_x, v_y), (v_x, u_y) and (e_x, e_y).
+// A wavefront takes one pair k of 32 cells: its lower 32 lanes reconstruct the
+// x-derivative and its upper 32 lanes the y-derivative; the halves then trade
+// point values by lane swaps, and each lane forms its pair's combination at
+// the six face points of its own direction and its pair's part of the volume
+// flux of that direction.  So a block (NC cells, three wavefronts per 32) meets
+// in LDS only for the energy component's sum (and the viscosities with mu(T)).
+// A thread per component, exchanging every point value through LDS behind
+// seven barriers, held this kernel to 105 us per stage at 1000x500.
+constexpr int GW_MU = 9 * 64;   // LDS doubles per three wavefronts with mu(T)
+
+// Component (2 w + l) of lane half l of pair k, as variable w of (u, v, e).
+__device__ __forceinline__ int pair_var(int k, int l) { return k == 2 ? 2 : (k ^ l); }
+
+// The two values of a pair from one value per half: afterwards x holds the
+// lower half's x (low lanes) or y (high lanes), y the upper half's.
+__device__ __forceinline__ void swap_halves(double& x, double& y) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x),
+                                                     (unsigned)__double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x),
+                                                     (unsigned)__double2hiint(y), false, false);
+    x = __hiloint2double((int)hi[0], (int)lo[0]);
+    y = __hiloint2double((int)hi[1], (int)lo[1]);
+#endif
+}
+
+// Stencil data a (17) of the lane's component -> gradients, their stores, and
+// the volume flux.  k: the wavefront's pair (uniform); g3: which three
+// wavefronts of the block; shm: NC / 32 * (3 * 64 (+ GW_MU)) doubles of LDS.
 // Every thread of the block calls it (it holds barriers).
-template <int NC, bool VarMu, bool FULL>
-__device__ __forceinline__ void grad_body(const Grid2& g, double* shv, const double* a, int cl,
-                                          int s, bool valid, int j, int i) {
+template <bool VarMu, bool FULL>
+__device__ __forceinline__ void grad_body(const Grid2& g, double* shm, const double* a, int k,
+                                          bool valid, int j, int i) {
+#pragma clang fp contract(off)
     const Consts& K = g.K;
     const long long N = g.ncell;
-    const long long cell = (long long)j * g.NX + i;
+    const unsigned off = 8u * (unsigned)(j * g.NX + i);
+    const int lane = threadIdx.x & 63;
+    const int hi = lane >> 5;
+    const bool inter = valid && j >= HALO && j < HALO + g.ny && i >= HALO && i < HALO + g.nx;
+    // the pair's factor in the energy flux: the velocity normal to the face for
+    // the normal stress, tangential for the shear, gamma / Pr for e
+    gdouble* VC = g.vc + (hi ? VC_B : 0) * N;
+    double pv[9];
+    if (k < 2) {
+        gdouble* VV = VC + ((k ^ hi) == 0 ? 4 : 13) * N;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) pv[q] = at(VV + q * N, off);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) pv[q] = K.gPr;
+    }
     double C[15];
     hweno2d(a, grad_consts(K), C);
-    double fo[12], vo[9];
-    eval_xface(C, fo);
-    eval_yface(C, fo + 6);
-    eval_vol(C, vo);
+    double fx[6], fy[6], va[9], vb[9];
+    eval_xface(C, fx);
+    eval_yface(C, fy);
+    eval_vol(C, va);
     if constexpr (FULL) {
         if (valid) {
+            const int s = 2 * pair_var(k, hi) + hi;
 #pragma unroll
-            for (int p = 0; p < 12; ++p) g.gf[(p * 6 + s) * N + cell] = fo[p];
-        }
-    } else {
-        // the face fluxes need three combinations of the six gradients per
-        // face point (stress_combos): the x-face points, then the y-face
-        // points, meet in LDS, and thread s forms outputs s, s + 6, s + 12 of
-        // the 18 of each half
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-#pragma unroll
-            for (int q = 0; q < 6; ++q) shv[(s * 6 + q) * NC + cl] = fo[half * 6 + q];
-            __syncthreads();
-            if (valid) {
-#pragma unroll
-                for (int r = 0; r < 3; ++r) {
-                    const int o = s + 6 * r, q = o / 3, z = o % 3;
-                    double sq[6], dc[3];
-#pragma unroll
-                    for (int c = 0; c < 6; ++c) sq[c] = shv[(c * 6 + q) * NC + cl];
-                    if (half == 0) stress_combos<0>(sq, dc);
-                    else stress_combos<1>(sq, dc);
-                    g.gf[((half * 6 + q) * 3 + z) * N + cell] = dc[z];
-                }
+            for (int p = 0; p < 6; ++p) {
+                at(g.gf + (p * 6 + s) * N, off) = fx[p];
+                at(g.gf + ((6 + p) * 6 + s) * N, off) = fy[p];
             }
-            __syncthreads();
         }
     }
-    const bool inter = valid && j >= HALO && j < HALO + g.ny && i >= HALO && i < HALO + g.nx;
-    // volume-flux quadratures of interior cells: the reconstruction kernel
-    // left the Gauss sum of the convective flux and the velocities (and
-    // temperatures) at the points; the viscous part is summed here over the
-    // cell's 6 threads, 2 directions x 9 points, 3 points each (thread s:
-    // direction s / 3, points 3 (s % 3) .. 3 (s % 3) + 2), and the partial
-    // sums meet in LDS.  The point data are loaded before the barrier.
-    const bool dy = s >= 3;
-    const int q0 = 3 * (s % 3);
-    const double* VC = g.vc + (long long)(dy ? VC_B : 0) * N + cell;
-    double pu[3], pv[3], pm[3];
-    if (inter) {
+    // the pair's combination from the values of the lane's own direction and
+    // the other one (stress_combos)
+    const double co = k == 0 ? 4.0 / 3.0 : 1.0, ct = k == 0 ? -(2.0 / 3.0) : 1.0;
+    auto combo = [&](double x, double y) {
+        const double own = hi ? y : x, oth = hi ? x : y;
+        return fma(co, own, ct * (k == 2 ? 0.0 : oth));
+    };
+    if constexpr (!FULL) {
 #pragma unroll
-        for (int qq = 0; qq < 3; ++qq) {
-            pu[qq] = VC[(4 + q0 + qq) * N];
-            pv[qq] = VC[(13 + q0 + qq) * N];
-            pm[qq] = VarMu ? viscosity_T(K, VC[(22 + q0 + qq) * N]) : K.mu_ref;
+        for (int p = 0; p < 6; ++p) {
+            swap_halves(fx[p], fy[p]);
+            const double v = combo(fx[p], fy[p]);
+            if (valid) at(g.gf + ((hi * 6 + p) * 3 + k) * N, off) = v;
         }
     }
+    // volume flux: viscous part of direction hi from this pair, at the points
+    // of that direction's basis (the reconstruction kernel left the Gauss sum
+    // of the convective flux and the velocities and temperatures)
+    double mu[9];
+    if constexpr (VarMu) {   // three of the nine points per wavefront
+        double* M = shm + 3 * 64;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) shv[(s * 9 + q) * NC + cl] = vo[q];
+        for (int q = 0; q < 3; ++q)
+            if (inter) M[(3 * k + q) * 64 + lane] = viscosity_T(K, at(VC + (22 + 3 * k + q) * N, off));
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 9; ++q) mu[q] = M[q * 64 + lane];
+    }
+    double am = 0.0, ae = 0.0;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        vb[q] = va[q];
+        swap_halves(va[q], vb[q]);
+        const double w = (q / 3 == 1 ? GW1 : GW0) * (q % 3 == 1 ? GW1 : GW0);
+        const double t = (VarMu ? mu[q] : K.mu_ref) * combo(va[q], vb[q]);
+        am = fma(w, t, am);
+        ae = fma(w, t * pv[q], ae);
+    }
+    shm[k * 64 + lane] = ae;
     __syncthreads();
-    double acc[3] = {0.0, 0.0, 0.0};
-    if (inter) {
-#pragma unroll
-        for (int qq = 0; qq < 3; ++qq) {
-            const int q = q0 + qq;
-            const double wq = (q / 3 == 1 ? GW1 : GW0) * (q % 3 == 1 ? GW1 : GW0);
-            double sq[6], f[3];
-#pragma unroll
-            for (int z = 0; z < 6; ++z) sq[z] = shv[(z * 9 + q) * NC + cl];
-            visc2_dir(K, pu[qq], pv[qq], pm[qq], sq, dy, f);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) acc[c] += wq * f[c];
-        }
-    }
-    __syncthreads();   // every read of the gradient values is done
-#pragma unroll
-    for (int c = 0; c < 3; ++c) shv[(s * 3 + c) * NC + cl] = acc[c];
-    __syncthreads();
-    if (inter && s < 2) {
-        const double* VS = g.vc + (long long)s * VC_B * N + cell;
-        g.vf[(s * 4) * N + cell] = VS[0];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const double t0 = shv[((3 * s + 0) * 3 + c) * NC + cl];
-            const double t1 = shv[((3 * s + 1) * 3 + c) * NC + cl];
-            const double t2 = shv[((3 * s + 2) * 3 + c) * NC + cl];
-            g.vf[(s * 4 + 1 + c) * N + cell] = VS[(1 + c) * N] + (t0 + t1 + t2);
-        }
+    if (!inter) return;
+    const int d = hi;
+    if (k < 2) {
+        // the normal stress enters the momentum along the direction
+        const int c = k ^ d;
+        at(g.vf + (d * 4 + 1 + c) * N, off) = at(VC + (1 + c) * N, off) - am;
+    } else {
+        at(g.vf + d * 4 * N, off) = at(VC, off);
+        at(g.vf + (d * 4 + 3) * N, off) =
+            at(VC + 3 * N, off) - (shm[lane] + shm[64 + lane] + shm[128 + lane]);
     }
 }
 
-
-template <int GR_CELLS, bool VarMu, bool FULL>
+// The gradient kernel of the reverse mode, which reads the weak moments itself
+// (k_rbar2 leaves them in memory) and all six gradients: GR_CELLS cells per block.
+template <int GR_CELLS, bool VarMu>
 __global__ __launch_bounds__(6 * GR_CELLS) void k_grad2(Batch bt) {
-    __shared__ double shv[6 * 9 * GR_CELLS];
+    constexpr int SH = 3 * 64 + (VarMu ? GW_MU : 0);
+    __shared__ double shm[GR_CELLS / 32 * SH];
     const Loc lc = locate(bt);
     const Grid2& gsrc = bt.g[lc.p];   // arrays indexed at run time are read from here
     if (!gsrc.st->active) return;
     const Grid2 g = gsrc;
-    const Consts& K = g.K;
-    const int tid = threadIdx.x;
-    const int cl = tid % GR_CELLS;
-    const int s = tid / GR_CELLS;
-    const int w = s >> 1, l = s & 1;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int k = wv % 3, l = (threadIdx.x >> 5) & 1, w = pair_var(k, l);
     const int wc = g.NX - 6;
-    const long long nreg = (long long)wc * (g.NY - 6);
-    const long long cid = (long long)lc.b * GR_CELLS + cl;
+    const int nreg = wc * (g.NY - 6);
+    const int cid = lc.b * GR_CELLS + wv / 3 * 32 + (threadIdx.x & 31);
     const bool valid = cid < nreg;
     int j = 3, i = 3;
     if (valid) {
-        j = 3 + (int)(cid / wc);
-        i = 3 + (int)(cid % wc);
+        j = 3 + cid / wc;
+        i = 3 + cid % wc;
     }
     const long long N = g.ncell;
-    const long long cell = (long long)j * g.NX + i;
-    const double* R0 = g.rb + ((l * 3 + w) * 3 + 0) * N;
-    const double* R1 = g.rb + ((l * 3 + w) * 3 + 1) * N;
-    const double* R2 = g.rb + ((l * 3 + w) * 3 + 2) * N;
+    gdouble* R = g.rb + (l * 3 + w) * 3 * N;
+    const unsigned off = 8u * (unsigned)(j * g.NX + i), row = 8u * (unsigned)g.NX;
     double a[17];
 #pragma unroll
-    for (int q = 0; q < 9; ++q)
-        a[q] = R0[cell + (long long)(q / 3 - 1) * g.NX + (q % 3 - 1)];
+    for (int q = 0; q < 9; ++q) a[q] = at(R, off + (q / 3 - 1) * row + 8u * (q % 3 - 1));
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int q = 2 * e + 1;
-        const long long nb = cell + (long long)(q / 3 - 1) * g.NX + (q % 3 - 1);
-        a[9 + e] = R1[nb];
-        a[13 + e] = R2[nb];
+        const unsigned nb = off + (q / 3 - 1) * row + 8u * (q % 3 - 1);
+        a[9 + e] = at(R + N, nb);
+        a[13 + e] = at(R + 2 * N, nb);
     }
-    grad_body<GR_CELLS, VarMu, FULL>(g, shv, a, cl, s, valid, j, i);
+    grad_body<VarMu, true>(g, shm + wv / 3 * SH, a, k, valid, j, i);
 }
 
 // ---------------------------------------------------------------------------
 // Weak moments and gradient reconstruction in one kernel (HWENO-GR, face
-// gradients in the three combinations).  A block takes RG_TX x RG_TY cells of
+// gradients in the three combinations).  A block takes TX x TY = 32 cells of
 // the gradient region and forms the weak moments of those cells and of the
 // ring around them in LDS (the ring is formed again by the neighbouring
 // tiles): first the interface data of every face of the ring's cells, then
 // their 18 weak moments, then the gradient reconstruction reads its 3x3
 // stencils from LDS.  Same arithmetic as k_rbar2 followed by k_grad2, without
 // the weak moments' round trip through HBM.
+// Bound: memory (54 planes read, 44 more of the volume points, 44 written;
+// the ring's share of the first comes from the caches).  Blocks of three
+// wavefronts overlap one's loads with another's arithmetic; 64 cells per block
+// cost 204 us per stage at 1000x500.  Against the two kernels (with the same
+// gradient body; sum of both, us): 64x64 11.9 -> 6.6, 500x100 22.9 -> 18.6,
+// 256x256 27.7 -> 22.4, 512x512 93 -> 82, 1000x500 180 -> 172, 2048x1024 700 -> 697.
+// Tiles 8x4 have the smaller ring, 16x2 the longer rows: up to RG_MAX_BLOCKS
+// blocks of 16x2 the ring decides (64x64 6.6 against 7.1 us, 400x400, 5226
+// blocks, 44.8 against 45.9), beyond, where the planes no longer stay in the
+// caches, the rows (512x512, 8481 blocks, 87 against 82; 1000x500 187 against 172).
 // ---------------------------------------------------------------------------
-constexpr int RG_TX = 16, RG_TY = 4, RG_CELLS = RG_TX * RG_TY;
-constexpr int RG_RX = RG_TX + 2, RG_RY = RG_TY + 2;                   // tile + ring
-constexpr int RG_NXF = RG_RY * (RG_RX + 1), RG_NYF = (RG_RY + 1) * RG_RX;   // faces
-constexpr int RG_LDS_A = 6 * (RG_NXF + RG_NYF) + 18 * RG_RY * RG_RX;
-constexpr int RG_LDS = RG_LDS_A > 54 * RG_CELLS ? RG_LDS_A : 54 * RG_CELLS;
+constexpr int RG_CELLS = 32;
+constexpr unsigned RG_MAX_BLOCKS = 6144;
 
-template <bool VarMu>
+template <int TX, int TY, bool VarMu>
 __global__ __launch_bounds__(6 * RG_CELLS) void k_rgrad2(Batch bt) {
+    constexpr int RG_TX = TX, RG_TY = TY;
+    constexpr int RG_RX = RG_TX + 2, RG_RY = RG_TY + 2;                         // tile + ring
+    constexpr int RG_NXF = RG_RY * (RG_RX + 1), RG_NYF = (RG_RY + 1) * RG_RX;   // faces
+    constexpr int RG_LDS = 6 * (RG_NXF + RG_NYF) + 18 * RG_RY * RG_RX;
+    static_assert(TX * TY == RG_CELLS && RG_LDS >= 3 * 64 + GW_MU, "three wavefronts per tile");
     // phase 1: hx[6][RY][RX + 1] and hy[6][RY + 1][RX] (W0 for w = 0..2, then
     // W1), rbs[18][RY][RX] (index (l * 3 + w) * 3 + moment); phase 2: the
     // gradient body's exchange over the same memory
@@ -1289,6 +1319,16 @@ __global__ __launch_bounds__(6 * RG_CELLS) void k_rgrad2(Batch bt) {
     const int i0 = 3 + (lc.b % tiles_x) * RG_TX;   // first cell of the tile
     const int j0 = 3 + (lc.b / tiles_x) * RG_TY;
     constexpr int NT = 6 * RG_CELLS;
+    // w-bar of the ring's cells, one task per (cell, l, w), asked for ahead of
+    // the faces
+    constexpr int NR = RG_RY * RG_RX, NQ = (6 * NR + NT - 1) / NT;
+    double wb[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int t = threadIdx.x + q * NT, rc = t % NR;
+        const int j = min(j0 - 1 + rc / RG_RX, g.NY - 3), i = min(i0 - 1 + rc % RG_RX, g.NX - 3);
+        if (t < 6 * NR) wb[q] = g.wb[(t / NR) * N + (long long)j * g.NX + i];
+    }
     // interface data of the faces of the ring's cells (j0 - 1 + r, i0 - 1 + c);
     // cells of weak moments lie in rows and columns 2 .. N - 3
     for (int t = threadIdx.x; t < RG_NXF + RG_NYF; t += NT) {
@@ -1324,13 +1364,14 @@ __global__ __launch_bounds__(6 * RG_CELLS) void k_rgrad2(Batch bt) {
         }
     }
     __syncthreads();
-    // weak moments of the ring's cells: one task per (cell, l, w)
-    for (int t = threadIdx.x; t < 6 * RG_RY * RG_RX; t += NT) {
-        const int lw = t / (RG_RY * RG_RX), rc = t % (RG_RY * RG_RX);
+    // weak moments of the ring's cells
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int t = threadIdx.x + q * NT;
+        const int lw = t / NR, rc = t % NR;
         const int l = lw / 3, w = lw % 3;
         const int r = rc / RG_RX, c = rc % RG_RX;
-        const int j = j0 - 1 + r, i = i0 - 1 + c;
-        if (j > g.NY - 3 || i > g.NX - 3) continue;
+        if (t >= 6 * NR || j0 - 1 + r > g.NY - 3 || i0 - 1 + c > g.NX - 3) continue;
         double W0lo, W0hi, W1lo, W1hi;
         if (l == 0) {
             const int f = r * (RG_RX + 1) + c;
@@ -1346,16 +1387,16 @@ __global__ __launch_bounds__(6 * RG_CELLS) void k_rgrad2(Batch bt) {
             W1hi = hy[(3 + w) * RG_NYF + f + RG_RX];
         }
         double m[3];
-        cell_wmom(W0lo, W0hi, W1lo, W1hi, g.wb[(l * 3 + w) * N + (long long)j * g.NX + i],
+        cell_wmom(W0lo, W0hi, W1lo, W1hi, wb[q],
                   l ? g.K.idy : g.K.idx, l, m);
 #pragma unroll
         for (int k = 0; k < 3; ++k) rbs[(lw * 3 + k) * (RG_RY * RG_RX) + rc] = m[k];
     }
     __syncthreads();
-    // gradient reconstruction: cell cl of the tile, component s = 2 w + l
-    const int cl = threadIdx.x % RG_CELLS;
-    const int s = threadIdx.x / RG_CELLS;
-    const int w = s >> 1, l = s & 1;
+    // gradient reconstruction: cell cl of the tile, variable w, direction l
+    const int cl = threadIdx.x & 31;
+    const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = (threadIdx.x >> 5) & 1, w = pair_var(k, l);
     const int ty = cl / RG_TX, tx = cl % RG_TX;
     const int j = j0 + ty, i = i0 + tx;
     const bool valid = j <= g.NY - 4 && i <= g.NX - 4;
@@ -1374,7 +1415,7 @@ __global__ __launch_bounds__(6 * RG_CELLS) void k_rgrad2(Batch bt) {
         a[13 + e] = valid ? R[2 * RG_RY * RG_RX + o] : 0.0;
     }
     __syncthreads();   // the weak moments are in registers; the exchange reuses the LDS
-    grad_body<RG_CELLS, VarMu, false>(g, lds, a, cl, s, valid, valid ? j : 3, valid ? i : 3);
+    grad_body<VarMu, false>(g, lds, a, k, valid, valid ? j : 3, valid ? i : 3);
 }
 
 // The two Gauss moments of a face flux that the assembly of eq. (3.2) takes
@@ -2090,13 +2131,16 @@ void batch_blocks(const Grid2* hg, int n, const Tiles& t, int* out) {
                            ((g.NY - 4 + RB_TY - 1) / RB_TY);
                     per = 1;
                     break;
-                case KB_GRAD:    // the split kernel (32 cells per block with the fused one chosen)
+                case KB_GRAD:
                     work = (long long)(g.NX - 6) * (g.NY - 6);
-                    per = t.grad ? t.grad : 32;
+                    per = t.grad == 64 ? 64 : 32;
                     break;
-                case KB_RGRAD:   // tiles of RG_TX x RG_TY cells of the gradient region
-                    work = (long long)((g.NX - 6 + RG_TX - 1) / RG_TX) *
-                           ((g.NY - 6 + RG_TY - 1) / RG_TY);
+                case KB_RGRAD:   // tiles of 16 x 2 cells of the gradient region
+                    work = (long long)((g.NX - 6 + 15) / 16) * ((g.NY - 6 + 1) / 2);
+                    per = 1;
+                    break;
+                case KB_RGRADS:   // tiles of 8 x 4 cells
+                    work = (long long)((g.NX - 6 + 7) / 8) * ((g.NY - 6 + 3) / 4);
                     per = 1;
                     break;
                 case KB_FLUX0:   // none when the update kernel forms the fluxes
@@ -2201,6 +2245,16 @@ void launch_recon2(const BatchL& b, int si, int alpha, hipStream_t st, Timer* tm
     }
 }
 
+template <bool VarMu>
+void launch_rgrad2(const BatchL& b, hipStream_t st, Timer* tm) {
+    if (b.blocks(KB_RGRAD) <= RG_MAX_BLOCKS)
+        tlaunch(tm, KC_GRAD, k_rgrad2<8, 4, VarMu>, b.blocks(KB_RGRADS), 6 * RG_CELLS, st,
+                b.arg(KB_RGRADS));
+    else
+        tlaunch(tm, KC_GRAD, k_rgrad2<16, 2, VarMu>, b.blocks(KB_RGRAD), 6 * RG_CELLS, st,
+                b.arg(KB_RGRAD));
+}
+
 hipError_t launch_residual2(const BatchL& b, int si, hipStream_t st, Timer* tm, bool alpha) {
     const unsigned nr = b.blocks(KB_RECON), ng = b.blocks(KB_GRAD);
     const Batch ar = b.arg(KB_RECON);
@@ -2217,29 +2271,18 @@ hipError_t launch_residual2(const BatchL& b, int si, hipStream_t st, Timer* tm, 
     } else {
         launch_recon2<32>(b, si, alpha, st, tm);
     }
-    if (!b.dr && !b.full_grad && b.tiles.grad == 0) {
-        // HWENO-GR, weak moments formed inside the gradient kernel
-        const Batch ag = b.arg(KB_RGRAD);
-        if (b.var_mu) tlaunch(tm, KC_GRAD, k_rgrad2<true>, b.blocks(KB_RGRAD), 6 * RG_CELLS, st, ag);
-        else tlaunch(tm, KC_GRAD, k_rgrad2<false>, b.blocks(KB_RGRAD), 6 * RG_CELLS, st, ag);
-    } else if (!b.dr) {   // HWENO-GR: weak-derivative moments, then their reconstruction
+    if (!b.dr && !b.full_grad) {   // HWENO-GR: gradients from the weak moments
+        if (b.var_mu) launch_rgrad2<true>(b, st, tm);
+        else launch_rgrad2<false>(b, st, tm);
+    } else if (!b.dr) {   // the reverse mode reads the weak moments and all six gradients
         tlaunch(tm, KC_RBAR, k_rbar2, b.blocks(KB_RBAR), RB_TX * RB_TY, st, b.arg(KB_RBAR));
         const Batch ag = b.arg(KB_GRAD);
-        if (b.full_grad) {   // the reverse mode reads all six gradients (and the adjoint
-                             // the weak moments)
-            if (b.tiles.grad == 64) {
-                if (b.var_mu) tlaunch(tm, KC_GRAD, k_grad2<64, true, true>, ng, 384, st, ag);
-                else tlaunch(tm, KC_GRAD, k_grad2<64, false, true>, ng, 384, st, ag);
-            } else {
-                if (b.var_mu) tlaunch(tm, KC_GRAD, k_grad2<32, true, true>, ng, 192, st, ag);
-                else tlaunch(tm, KC_GRAD, k_grad2<32, false, true>, ng, 192, st, ag);
-            }
-        } else if (b.tiles.grad == 64) {
-            if (b.var_mu) tlaunch(tm, KC_GRAD, k_grad2<64, true, false>, ng, 384, st, ag);
-            else tlaunch(tm, KC_GRAD, k_grad2<64, false, false>, ng, 384, st, ag);
+        if (b.tiles.grad == 64) {
+            if (b.var_mu) tlaunch(tm, KC_GRAD, k_grad2<64, true>, ng, 384, st, ag);
+            else tlaunch(tm, KC_GRAD, k_grad2<64, false>, ng, 384, st, ag);
         } else {
-            if (b.var_mu) tlaunch(tm, KC_GRAD, k_grad2<32, true, false>, ng, 192, st, ag);
-            else tlaunch(tm, KC_GRAD, k_grad2<32, false, false>, ng, 192, st, ag);
+            if (b.var_mu) tlaunch(tm, KC_GRAD, k_grad2<32, true>, ng, 192, st, ag);
+            else tlaunch(tm, KC_GRAD, k_grad2<32, false>, ng, 192, st, ag);
         }
     }
     if (b.tiles.flux == 0) return hipGetLastError();   // fluxes formed by the update kernel

@@ -282,7 +282,7 @@ size_t layout(hweno_ctx* c, char* base) {
         g.wb = take(6 * m);
         g.vk = take(8 * m);
         g.vn = take(8 * m);
-        g.rb = take(18 * m);
+        g.rb = c->batch ? nullptr : take(18 * m);   // the reverse mode's
         g.gf = take((c->batch ? 36 : 72) * m);
         g.vf = take(8 * m);
         g.fx = take(8 * m);
@@ -1222,7 +1222,7 @@ size_t static_layout2(hw::Grid2& g, char* base, hw::Grid2** dgrid, hw::InstState
     g.wb = take(6 * m);
     g.vk = take(8 * m);
     g.vn = take(8 * m);
-    g.rb = take(18 * m);
+    g.rb = take(18 * m);   // not read here: the size is the documented limit's
     g.gf = take(36 * m);
     g.vf = take(8 * m);
     g.fx = take(8 * m);
@@ -1917,9 +1917,10 @@ HWENO_API hweno_status hweno_autotune(hweno_ctx* c, int reps, hweno_tiles* chose
         c->timer.reset();
         return HWENO_OK;
     };
-    // candidate 2 differs in the flux path (fused into the update) and in the
-    // gradient kernel (weak moments formed inside it)
-    const hw::Tiles cand[3] = {{16, 32, 64, 1}, {32, 64, 128, 1}, {16, 0, 0, 1}};
+    // candidate 2 differs in the flux path (fused into the update); the
+    // gradient tile is the reverse mode's and stays
+    const int grad = c->tiles.grad;
+    const hw::Tiles cand[3] = {{16, grad, 64, 1}, {32, grad, 128, 1}, {16, grad, 0, 1}};
     double ms[3][hw::KC_COUNT];
     for (int q = 0; q < 3; ++q) {
         c->tiles = cand[q];
@@ -1932,12 +1933,7 @@ HWENO_API hweno_status hweno_autotune(hweno_ctx* c, int reps, hweno_tiles* chose
         fu[q] = ms[q][hw::KC_FLUX] + ms[q][hw::KC_UPDATE] + ms[q][hw::KC_FLUXUP];
     hw::Tiles best;
     best.recon = ms[0][hw::KC_RECON] <= ms[1][hw::KC_RECON] ? cand[0].recon : cand[1].recon;
-    // weak moments + gradients: the split kernels (32 or 64 cells) or the fused one
-    int gq = 0;
-    for (int q = 1; q < 3; ++q)
-        if (ms[q][hw::KC_RBAR] + ms[q][hw::KC_GRAD] < ms[gq][hw::KC_RBAR] + ms[gq][hw::KC_GRAD])
-            gq = q;
-    best.grad = cand[gq].grad;
+    best.grad = grad;
     const int fq = fu[2] < std::min(fu[0], fu[1]) ? 2 : (fu[0] <= fu[1] ? 0 : 1);
     best.flux = cand[fq].flux;
     c->tiles = best;

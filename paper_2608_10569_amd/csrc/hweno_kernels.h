@@ -87,7 +87,7 @@ struct Grid2 {
     gdouble* wb;   // 6:  wbar of (u, v, e) from x-basis, then from y-basis
     gdouble* vk;   // 8:  modified moments of the current input (hat-v 0..3, hat-w 4..7)
     gdouble* vn;   // 8:  modified moments of U^n (kept for stages 2 and 3)
-    gdouble* rb;   // 18: weak moments ((l*3 + w)*3 + mom)
+    gdouble* rb;   // 18: weak moments ((l*3 + w)*3 + mom), for the reverse mode
     gdouble* gf;   // gradients at the face points, p 0..5 x-face, 6..11 y-face: 36, the
                    // three combinations of stress_combos (p*3 + z), or with the
                    // reverse mode's full_grad 72, the six gradients (p*6 + s)
@@ -205,7 +205,7 @@ inline void tend(Timer* t, hipStream_t st) { if (t) t->end(st); }
 // block of the instance in slot p (start[n] = the launch's block count).
 // ---------------------------------------------------------------------------
 enum { KB_GHOST = 0, KB_RECON, KB_RBAR, KB_GRAD, KB_FLUX0, KB_FLUX1, KB_CELLS,
-       KB_FLUXUP, KB_RGRAD, KB_FLUXUPS, KB_COUNT };
+       KB_FLUXUP, KB_RGRAD, KB_RGRADS, KB_FLUXUPS, KB_COUNT };
 
 struct Batch {
     const Grid2* g;
@@ -219,8 +219,7 @@ struct Batch {
 struct Tiles {
     int recon = 32;   // 16 or 32 (columns of the reconstruction's 64-cell tiles; HWENO-DR:
                       // cells per block)
-    int grad = 32;    // 32 or 64; 0: weak moments formed in the gradient kernel
-                      // (tiles of 16 x 4 cells)
+    int grad = 32;    // the reverse mode's gradient kernel: 64, else 32 cells per block
     int flux = 0;     // 64 or 128; 0: face fluxes formed inside the update kernel
     int xcd = 1;      // 1: each XCD takes a contiguous range of a launch's blocks
 };
@@ -242,7 +241,7 @@ struct BatchL {
     // their first blocks read what is still in L2 and the memory-side cache;
     // the next stage's reconstruction then again runs opposite to them.
     unsigned rev = (1u << KB_RBAR) | (1u << KB_FLUX0) | (1u << KB_FLUX1) | (1u << KB_FLUXUP) |
-                   (1u << KB_RGRAD) | (1u << KB_FLUXUPS);
+                   (1u << KB_RGRAD) | (1u << KB_RGRADS) | (1u << KB_FLUXUPS);
     Batch arg(int k) const {
         return Batch{dg, dstart + k * (n + 1), n, tiles.xcd, (int)((rev >> k) & 1u)};
     }
