@@ -371,7 +371,8 @@ HWENO_API hweno_status hweno_take_mu_bar(hweno_ctx* ctx, double* mu_bar);
  * start and end of its execution (hipExtLaunchKernel: the dispatch is not
  * counted); classes 4 and 6 record them on the stream around their launches.
  * Classes:
- * 0 ghost fill, 1 characteristic reconstruction + limiter, 2 weak-derivative
+ * 0 ghost fill (small launches form the ghost cells in the reconstruction and
+ * run the fill only while this class is recorded), 1 characteristic reconstruction + limiter, 2 weak-derivative
  * moments as a kernel of their own (reverse mode), 3 gradient reconstruction
  * (else with the weak moments) + volume flux, 4 face fluxes, 5 stage
  * update / assembly, 6 a whole batched run (hweno_batch_run), 7 face fluxes

@@ -233,6 +233,27 @@ __device__ __forceinline__ void x_ghost(const Grid2& g, const Side& sd, const do
     for (int q = 0; q < 12; ++q) v[q] = sd.sign[q] * S[q * g.ncell + src];
 }
 
+__device__ __forceinline__ double flip_sign(double v, unsigned neg) {
+    return __hiloint2double(__double2hiint(v) ^ (int)(neg << 31), __double2loint(v));
+}
+
+// Prescribed average of ghost cell (j, i) whose rules lead to an inflow side
+// (its first moments are zero); gs: the descriptor in memory.
+__device__ __forceinline__ void inflow_at(const Grid2& gs, int j, int i, int stage, double* st) {
+    const bool yg = j < HALO || j >= HALO + gs.ny;
+    const Side& sy = gs.side[j < HALO ? 2 : 3];
+    const Side& sx = gs.side[i < HALO ? 0 : 1];
+    const bool y = yg && sy.kind == 2;
+    // on a y side the ghost columns take the profile's end states; on an x side
+    // the ghost rows take their source row's, with the y side's signs
+    const int k = y ? min(max(i - HALO, 0), gs.nx - 1)
+                    : (yg ? ghost_src(sy.kind, j, gs.ny) : j) - HALO;
+    double v[12];
+    inflow_values(y ? sy : sx, k, y ? gs.nx : gs.ny, stage, v);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) st[c] = yg && !y ? sy.sign[c] * v[c] : v[c];
+}
+
 // Walls inside the grid (masked domains): solid cell = mirror image of a fluid
 // cell across the nearest wall face, with the box walls' parities (Remark 4.1);
 // a cell listed with source -1 holds the prescribed state with zero first
@@ -408,8 +429,8 @@ __device__ __forceinline__ void project2(const double* sh, const double* L, doub
     }
 }
 
-template <int TX, bool VarMu, bool FULL>
-__global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_alpha) {
+template <int TX, bool VarMu, bool FULL, bool GH>
+__global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_alpha, int gst) {
     constexpr int TY = 64 / TX, TW = TX + 2, TH = TY + 2, PL = TW * TH;
     constexpr int NP = (PL + 63) / 64;
     // handed-over values: per basis and field of a wavefront, 9 volume values
@@ -418,6 +439,7 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
     constexpr int XB = 2 * (9 + 7) * 64;   // one field of each of the four wavefronts
     __shared__ double sh[XB + (XB > 12 * PL ? XB : 12 * PL)];
     __shared__ double shm[2][4][64];       // [density, pressure][wavefront][cell]
+    __shared__ double shu[4][64];          // GH: cell averages, for the limiter
     double* const tile = sh + XB;
     const Loc lc = locate(bt);
     const Grid2& gsrc = bt.g[lc.p];   // arrays indexed at run time are read from here
@@ -440,14 +462,63 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
     // issued before the first LDS write
     {
         double v[3][NP];
+        if constexpr (!GH) {
 #pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
-            const int gj = min(j0 - 1 + r, g.NY - 1), gi = min(max(i0 - 1 + c, 0), g.NX - 1);
-            const unsigned src = 8u * (unsigned)(gj * g.NX + gi);
+            for (int q = 0; q < NP; ++q) {
+                const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
+                const int gj = min(j0 - 1 + r, g.NY - 1), gi = min(max(i0 - 1 + c, 0), g.NX - 1);
+                const unsigned src = 8u * (unsigned)(gj * g.NX + gi);
 #pragma unroll
-            for (int f = 0; f < 3; ++f)
-                if (t < PL) v[f][q] = at((gdouble*)S + (3 * wv + f) * N, src);
+                for (int f = 0; f < 3; ++f)
+                    if (t < PL) v[f][q] = at((gdouble*)S + (3 * wv + f) * N, src);
+            }
+        } else {
+            // no fill has written the ghost cells: they are read from their
+            // source cells, sources and signs without branches (index gi of a
+            // ghost cell has source ga * gi + gb); prescribed states (inflow)
+            // replace theirs afterwards
+            int ga[4], gb[4];
+#pragma unroll
+            for (int sd = 0; sd < 4; ++sd) {
+                const int kind = g.rule[sd] & 15, n = sd < 2 ? g.nx : g.ny;
+                ga[sd] = kind == 0 ? 1 : (kind == 1 ? 0 : -1);
+                if (sd & 1) gb[sd] = kind == 0 ? -n : (kind == 1 ? HALO + n - 1 : 2 * (HALO + n) - 1);
+                else gb[sd] = kind == 0 ? n : (kind == 1 ? HALO : 2 * HALO - 1);
+            }
+            unsigned in = 0;
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
+                const int gj = min(j0 - 1 + r, g.NY - 1), gi = min(max(i0 - 1 + c, 0), g.NX - 1);
+                const bool yl = gj < HALO, yh = gj >= HALO + g.ny;
+                const bool xl = gi < HALO, xh = gi >= HALO + g.nx;
+                const int sj = (yl ? ga[2] : (yh ? ga[3] : 1)) * gj + (yl ? gb[2] : (yh ? gb[3] : 0));
+                const int si = (xl ? ga[0] : (xh ? ga[1] : 1)) * gi + (xl ? gb[0] : (xh ? gb[1] : 0));
+                const unsigned ry = yl ? g.rule[2] : (yh ? g.rule[3] : 0u);
+                const unsigned rx = xl ? g.rule[0] : (xh ? g.rule[1] : 0u);
+                in |= ((ry | rx) >> 31) << q;
+                const unsigned src = 8u * (unsigned)(sj * g.NX + si);
+                const unsigned neg = (ry ^ rx) >> (4 + 3 * wv);
+#pragma unroll
+                for (int f = 0; f < 3; ++f)
+                    if (t < PL)
+                        v[f][q] = flip_sign(at((gdouble*)S + (3 * wv + f) * N, src), neg >> f & 1u);
+            }
+            if (__ballot(in != 0)) {
+#pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
+                    const int gj = min(j0 - 1 + r, g.NY - 1);
+                    const int gi = min(max(i0 - 1 + c, 0), g.NX - 1);
+                    double st[4];
+                    if (t < PL && (in >> q & 1)) {
+                        inflow_at(gsrc, gj, gi, gst, st);
+#pragma unroll
+                        for (int f = 0; f < 3; ++f)   // wavefront 0: fields 0-2, 1: 3-5, ...
+                            v[f][q] = wv == 0 ? st[f] : (wv == 1 && f == 0 ? st[3] : 0.0);
+                    }
+                }
+            }
         }
 #pragma unroll
         for (int q = 0; q < NP; ++q)
@@ -457,6 +528,7 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
     }
     __syncthreads();
     const double* T0 = tile + (ly + 1) * TW + lx + 1;
+    if constexpr (GH) shu[wv][lane] = T0[wv * PL];
     // cell average: in the global order (pbar: the same bits in every
     // wavefront) and in the basis's
     const double rbar = T0[0];
@@ -621,7 +693,8 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
             const double th2 = pmin < eps ? fmin((pbar - eps) / (pbar - pmin), 1.0) : 1.0;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const double ub = at((gdouble*)S + gc[c] * N, off);
+                const double ub =
+                    GH ? shu[gc[c]][lane] : at((gdouble*)S + gc[c] * N, off);
 #pragma unroll
                 for (int o = 0; o < 6; ++o) v[c][o] = ub + th2 * (v[c][o] - ub);
             }
@@ -2233,15 +2306,18 @@ void launch_flux2(const BatchL& b, hipStream_t st) {
 
 // full_grad: the reverse mode also stores the full volume values.
 template <int TX>
-void launch_recon2(const BatchL& b, int si, int alpha, hipStream_t st, Timer* tm) {
+void launch_recon2(const BatchL& b, int si, int alpha, int gst, hipStream_t st, Timer* tm) {
     const unsigned n = b.blocks(KB_RECON);
     const Batch a = b.arg(KB_RECON);
     if (b.full_grad) {
-        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, true>, n, 256, st, a, si, alpha);
-        else tlaunch(tm, KC_RECON, k_recon2<TX, false, true>, n, 256, st, a, si, alpha);
+        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, true, false>, n, 256, st, a, si, alpha, gst);
+        else tlaunch(tm, KC_RECON, k_recon2<TX, false, true, false>, n, 256, st, a, si, alpha, gst);
+    } else if (gst == GHOSTS_FILLED) {
+        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, false, false>, n, 256, st, a, si, alpha, gst);
+        else tlaunch(tm, KC_RECON, k_recon2<TX, false, false, false>, n, 256, st, a, si, alpha, gst);
     } else {
-        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, false>, n, 256, st, a, si, alpha);
-        else tlaunch(tm, KC_RECON, k_recon2<TX, false, false>, n, 256, st, a, si, alpha);
+        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, false, true>, n, 256, st, a, si, alpha, gst);
+        else tlaunch(tm, KC_RECON, k_recon2<TX, false, false, true>, n, 256, st, a, si, alpha, gst);
     }
 }
 
@@ -2255,7 +2331,7 @@ void launch_rgrad2(const BatchL& b, hipStream_t st, Timer* tm) {
                 b.arg(KB_RGRAD));
 }
 
-hipError_t launch_residual2(const BatchL& b, int si, hipStream_t st, Timer* tm, bool alpha) {
+hipError_t launch_residual2(const BatchL& b, int si, int gst, hipStream_t st, Timer* tm, bool alpha) {
     const unsigned nr = b.blocks(KB_RECON), ng = b.blocks(KB_GRAD);
     const Batch ar = b.arg(KB_RECON);
     if (b.dr) {   // HWENO-DR: gradients and volume fluxes come with the reconstruction
@@ -2267,9 +2343,9 @@ hipError_t launch_residual2(const BatchL& b, int si, hipStream_t st, Timer* tm, 
             else tlaunch(tm, KC_RECON, k_recon2_dr<32, false>, nr, 256, st, ar, si);
         }
     } else if (b.tiles.recon == 16) {
-        launch_recon2<16>(b, si, alpha, st, tm);
+        launch_recon2<16>(b, si, alpha, gst, st, tm);
     } else {
-        launch_recon2<32>(b, si, alpha, st, tm);
+        launch_recon2<32>(b, si, alpha, gst, st, tm);
     }
     if (!b.dr && !b.full_grad) {   // HWENO-GR: gradients from the weak moments
         if (b.var_mu) launch_rgrad2<true>(b, st, tm);

@@ -641,12 +641,27 @@ hweno_status ghost(hweno_ctx* c, int si, int stage = -1) {
     return dev(hw::launch_ghost1(c->g1, c->S1[si], c->stream, c->tm()));
 }
 
-// b: the 2D launch list to use (the stage sets of keep_stages); default the
-// grid's.  alpha: the CFL wave speed is wanted (2D)
-hweno_status residual(hweno_ctx* c, int si, const hw::BatchL* b = nullptr, bool alpha = true) {
+// Residual at a state whose ghost cells are filled.  b: the 2D launch list to
+// use (the stage sets of keep_stages); default the grid's.
+hweno_status residual(hweno_ctx* c, int si, const hw::BatchL* b = nullptr) {
     if (c->dim() == 2)
-        return dev(hw::launch_residual2(b ? *b : c->bl, si, c->stream, c->tm(), alpha));
+        return dev(hw::launch_residual2(b ? *b : c->bl, si, hw::GHOSTS_FILLED, c->stream,
+                                        c->tm()));
     return dev(hw::launch_residual1(c->g1, c->S1[si], c->stream, c->tm()));
+}
+
+// 2D residual at a state whose ghost cells are not filled: by a launch of their
+// own, also while that is timed, or in the reconstruction (the walls inside the
+// grid here).  alpha: the CFL wave speed is wanted.
+hweno_status eval2(hweno_ctx* c, int si, int stage = -1, bool alpha = true) {
+    hw::Timer* tm = c->tm();
+    if (!c->bl.forms_ghosts() || (tm && (tm->mask >> hw::KC_GHOST & 1u))) {
+        TRY(ghost(c, si, stage));
+        stage = hw::GHOSTS_FILLED;
+    } else if (!c->batch && !c->sdst_host.empty()) {
+        TRY(dev(hw::launch_solid2(c->dg, (int)c->sdst_host.size(), si, c->stream)));
+    }
+    return dev(hw::launch_residual2(c->bl, si, stage, c->stream, tm, alpha));
 }
 
 // 2D
@@ -794,7 +809,13 @@ hweno_ctx* make_ctx(int n, const hweno_grid* grids, const hweno_physics* phys,
             g.NY = g.ny + 2 * HALO;
             g.ncell = (long long)g.NX * g.NY;
             g.K = make_consts(c->in[p]);
-            for (int s = 0; s < 4; ++s) make_side(c->in[p], s, g.side[s]);
+            for (int s = 0; s < 4; ++s) {
+                make_side(c->in[p], s, g.side[s]);
+                g.rule[s] = (unsigned)g.side[s].kind;
+                for (int q = 0; q < 12; ++q)
+                    if (g.side[s].sign[q] < 0.0) g.rule[s] |= 16u << q;
+                if (g.side[s].kind == HWENO_BC_INFLOW) g.rule[s] |= 1u << 31;
+            }
             hw::InstState& st = c->hst[p];
             rule(c->in[p], &st.cfl_h, &st.visc_dt);
             st.t_final = opts[p].t_final;
@@ -812,16 +833,18 @@ hweno_ctx* make_ctx(int n, const hweno_grid* grids, const hweno_physics* phys,
 // One step of every active instance of a batch (eq. (2.12) with the step rule
 // on the device); recorded into a graph by hweno_batch_run.
 hweno_status batch_step(const hw::BatchL& b, hipStream_t st) {
+    auto eval = [&](int si, bool alpha) {
+        const bool own = b.forms_ghosts();
+        if (!own) TRY(dev(hw::launch_ghost2(b, si, st, nullptr)));
+        return dev(hw::launch_residual2(b, si, own ? -1 : hw::GHOSTS_FILLED, st, nullptr, alpha));
+    };
     TRY(dev(hw::launch_reset2(b, st)));
-    TRY(dev(hw::launch_ghost2(b, 0, st, nullptr)));
-    TRY(dev(hw::launch_residual2(b, 0, st, nullptr)));
+    TRY(eval(0, true));
     TRY(dev(hw::launch_dt2(b, st)));
     TRY(dev(hw::launch_update2(b, 1, 0, 0, 1, nullptr, nullptr, st, nullptr)));
-    TRY(dev(hw::launch_ghost2(b, 1, st, nullptr)));
-    TRY(dev(hw::launch_residual2(b, 1, st, nullptr, false)));
+    TRY(eval(1, false));
     TRY(dev(hw::launch_update2(b, 2, 0, 1, 2, nullptr, nullptr, st, nullptr)));
-    TRY(dev(hw::launch_ghost2(b, 2, st, nullptr)));
-    TRY(dev(hw::launch_residual2(b, 2, st, nullptr, false)));
+    TRY(eval(2, false));
     TRY(dev(hw::launch_update2(b, 3, 0, 2, 1, nullptr, nullptr, st, nullptr)));
     return dev(hw::launch_commit2(b, st));
 }
@@ -1168,8 +1191,7 @@ HWENO_API hweno_status hweno_residual(hweno_ctx* c, const double* U, double* R, 
     if (c->dim() == 2) {
         TRY(dev(hw::launch_copy_in2(g2(c), U, g2(c).S[2], c->stream)));
         TRY(reset(c));
-        TRY(ghost(c, 2));
-        TRY(residual(c, 2));
+        TRY(eval2(c, 2));
         TRY(update(c, 0, 2, 2, 2, R, V));
     } else {
         TRY(residual1(c->g1, U, c->S1[2], R, V, c->stream, c->tm()));
@@ -1289,8 +1311,9 @@ HWENO_API hweno_status hweno_residual_noalloc(hweno_ctx* c, const double* U, dou
         bl.dr = c->i0().opt.gradients != 0;
         TRY(dev(hw::launch_copy_in2(g, U, g.S[0], st)));
         TRY(dev(hw::launch_reset2(bl, st)));
-        TRY(dev(hw::launch_ghost2(bl, 0, st, nullptr)));
-        TRY(dev(hw::launch_residual2(bl, 0, st, nullptr)));
+        const bool own = bl.forms_ghosts();
+        if (!own) TRY(dev(hw::launch_ghost2(bl, 0, st, nullptr)));
+        TRY(dev(hw::launch_residual2(bl, 0, own ? -1 : hw::GHOSTS_FILLED, st, nullptr)));
         TRY(dev(hw::launch_update2(bl, 0, 0, 0, 0, R, V, st, nullptr)));
         red = (hw::Reduce*)g.red;
     } else {
@@ -1394,18 +1417,15 @@ hweno_status step(hweno_ctx* c, double dt, const double* const* src, hweno_diag*
         } else {
             TRY(reset(c));
             if (check) TRY(dev(hw::launch_check2(c->bl, a, c->stream)));
-            TRY(ghost(c, a, staged ? 0 : -1));
-            TRY(residual(c, a));
+            TRY(eval2(c, a, staged ? 0 : -1));
             if (auto_dt && restarts == 0)
                 TRY(dev(hw::launch_dt(c->red, cfl_h, visc, t_left, c->stream)));
             else
                 TRY(dev(hw::launch_set_dt(c->red, cur_dt, c->stream)));
             TRY(update(c, 1, a, a, b, nullptr, nullptr, src1));
-            TRY(ghost(c, b, staged ? 1 : -1));
-            TRY(residual(c, b, nullptr, false));
+            TRY(eval2(c, b, staged ? 1 : -1, false));
             TRY(update(c, 2, a, b, s2, nullptr, nullptr, src2));
-            TRY(ghost(c, s2, staged ? 2 : -1));
-            TRY(residual(c, s2, nullptr, false));
+            TRY(eval2(c, s2, staged ? 2 : -1, false));
             TRY(update(c, 3, a, s2, b, nullptr, nullptr, src3));
             TRY(read_reduce(c, c->red, &r));
         }
@@ -1896,8 +1916,7 @@ HWENO_API hweno_status hweno_autotune(hweno_ctx* c, int reps, hweno_tiles* chose
     // there); ms per kernel class
     auto one = [&]() -> hweno_status {
         TRY(reset(c));
-        TRY(ghost(c, si));
-        TRY(residual(c, si));
+        TRY(eval2(c, si));
         TRY(dev(hw::launch_dt2(c->bl, c->stream)));
         return update(c, 1, si, si, 2, nullptr, nullptr);
     };

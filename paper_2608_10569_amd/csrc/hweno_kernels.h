@@ -74,6 +74,9 @@ struct Grid2 {
     long long ncell;          // NX * NY
     Consts K;
     Side side[4];
+    // side[k] in one word: kind (bits 0-3), fields its ghost cells negate (bits
+    // 4-15), inflow (bit 31)
+    unsigned rule[4];
     gdouble* S[4];  // 12 each: ghosted states (current, stage outputs, scratch)
     HW_GLOBAL InstState* st;
     gdouble* xf;   // 24: x-face traces (p*4 + c), p 0..2 left face, 3..5 right face
@@ -224,6 +227,18 @@ struct Tiles {
     int xcd = 1;      // 1: each XCD takes a contiguous range of a launch's blocks
 };
 
+// Ghost cells of a residual's input: filled by launch_ghost2, or formed by the
+// reconstruction as it loads them (any other value: the stage of the inflow
+// profiles to take, -1: none).
+constexpr int GHOSTS_FILLED = -2;
+// Up to this many blocks of the reconstruction it forms them: a launch less
+// per stage.  Step of three stages with the fill as a launch and without, us:
+// 64x64 (108 blocks) 114 and 100, 160x160 152 and 138, 500x100 204 and 195,
+// 256x256 (1161 blocks) 241 and 233, 400x400 (2639) 404 and 407, 512x512 690
+// and 699, 1000x500 1317 and 1340: the index arithmetic of every tile costs
+// the reconstruction 3 us at 64x64 and 15 of 136 at 1000x500.
+constexpr unsigned GHOST_MAX_BLOCKS = 2048;
+
 struct BatchL {
     const Grid2* dg = nullptr;     // device, n instances in schedule order
     const int* dstart = nullptr;   // device, KB_COUNT x (n + 1)
@@ -246,6 +261,10 @@ struct BatchL {
         return Batch{dg, dstart + k * (n + 1), n, tiles.xcd, (int)((rev >> k) & 1u)};
     }
     unsigned blocks(int k) const { return (unsigned)hstart[k * (n + 1) + n]; }
+    // HWENO-DR and the reverse mode (which reads them) need filled ghost cells
+    bool forms_ghosts() const {
+        return !dr && !full_grad && blocks(KB_RECON) <= GHOST_MAX_BLOCKS;
+    }
 };
 
 // Block prefix tables of every kernel class for the instances hg[0..n) (in
@@ -263,7 +282,7 @@ hipError_t launch_ghost2(const BatchL& b, int si, hipStream_t st, Timer* tm, int
 hipError_t launch_solid2(const Grid2* g, int n, int si, hipStream_t st);
 // alpha: the reconstruction also reduces the CFL wave speed (stage 1 and single
 // residuals; nothing reads it after the later stages)
-hipError_t launch_residual2(const BatchL& b, int si, hipStream_t st, Timer* tm,
+hipError_t launch_residual2(const BatchL& b, int si, int gst, hipStream_t st, Timer* tm,
                             bool alpha = true);
 // stage 0: write R (12) and Vhat (8) in interior layout (single grid);
 // stage 1..3: RK update S[iout] from S[i0] (U^n) and S[iin] (stage input);
