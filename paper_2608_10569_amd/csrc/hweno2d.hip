@@ -430,7 +430,8 @@ __device__ __forceinline__ void project2(const double* sh, const double* L, doub
 }
 
 template <int TX, bool VarMu, bool FULL, bool GH>
-__global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_alpha, int gst) {
+__global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_alpha, int gst,
+                                                 const double* U) {
     constexpr int TY = 64 / TX, TW = TX + 2, TH = TY + 2, PL = TW * TH;
     constexpr int NP = (PL + 63) / 64;
     // handed-over values: per basis and field of a wavefront, 9 volume values
@@ -445,7 +446,11 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
     const Grid2& gsrc = bt.g[lc.p];   // arrays indexed at run time are read from here
     if (!gsrc.st->active) return;
     const Grid2 g = gsrc;
-    const double* __restrict__ S = gsrc.S[si];
+    // GH: the input may be the caller's interior array U (plane and row sizes
+    // pl and nr, interior cell (0, 0) first)
+    const double* __restrict__ S = GH && U ? U : gsrc.S[si];
+    const long long pl = GH && U ? (long long)g.nx * g.ny : g.ncell;
+    const int nr = GH && U ? g.nx : g.NX, n0 = GH && U ? HALO * (g.nx + 1) : 0;
     const Consts& K = g.K;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -497,12 +502,12 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
                 const unsigned ry = yl ? g.rule[2] : (yh ? g.rule[3] : 0u);
                 const unsigned rx = xl ? g.rule[0] : (xh ? g.rule[1] : 0u);
                 in |= ((ry | rx) >> 31) << q;
-                const unsigned src = 8u * (unsigned)(sj * g.NX + si);
+                const unsigned src = 8u * (unsigned)(sj * nr + si - n0);
                 const unsigned neg = (ry ^ rx) >> (4 + 3 * wv);
 #pragma unroll
                 for (int f = 0; f < 3; ++f)
                     if (t < PL)
-                        v[f][q] = flip_sign(at((gdouble*)S + (3 * wv + f) * N, src), neg >> f & 1u);
+                        v[f][q] = flip_sign(at((gdouble*)S + (3 * wv + f) * pl, src), neg >> f & 1u);
             }
             if (__ballot(in != 0)) {
 #pragma unroll
@@ -2049,15 +2054,17 @@ __global__ __launch_bounds__(256) void k_check2(Batch bt, int si) {
     red_add32<256>(&g.red->bad[0], bad);
 }
 
+__device__ __forceinline__ void reset_reduce(Reduce* r) {
+    r->alpha_key = dkey(-INFINITY);
+    r->beta_key = dkey(-INFINITY);
+    r->pp_cells = 0;
+    r->min_rho_key = dkey(INFINITY);
+    r->min_p_key = dkey(INFINITY);
+    r->bad[0] = r->bad[1] = r->bad[2] = r->bad[3] = 0;
+}
+
 __global__ void k_reset(Reduce* r) {
-    if (threadIdx.x == 0) {
-        r->alpha_key = dkey(-INFINITY);
-        r->beta_key = dkey(-INFINITY);
-        r->pp_cells = 0;
-        r->min_rho_key = dkey(INFINITY);
-        r->min_p_key = dkey(INFINITY);
-        r->bad[0] = r->bad[1] = r->bad[2] = r->bad[3] = 0;
-    }
+    if (threadIdx.x == 0) reset_reduce(r);
 }
 
 __global__ void k_dt(Reduce* r, double cfl_h, double visc_dt, double t_left) {
@@ -2079,16 +2086,23 @@ __global__ void k_set_dt(Reduce* r, double dt) {
 }
 
 // Per-instance kernels of a batch: thread p serves the instance in slot p.
+// Places the descriptors of an allocation-free call and resets its reductions:
+// one launch, the descriptors its arguments (three copies from pageable memory
+// and a reset, before).
+__global__ __launch_bounds__(256) void k_place2(Place2 a) {
+    auto put = [&](void* to, const void* from, int bytes) {
+        for (int k = threadIdx.x; k < bytes / 4; k += 256)
+            ((unsigned*)to)[k] = ((const unsigned*)from)[k];
+    };
+    put(a.dg, &a.g, sizeof(a.g));
+    put(a.dst, &a.st, sizeof(a.st));
+    put(a.dstart, a.start, sizeof(a.start));
+    if (threadIdx.x == 0) reset_reduce((Reduce*)a.g.red);
+}
+
 __global__ void k_reset2(const Grid2* __restrict__ gs, int n) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    Reduce* r = gs[p].red;
-    r->alpha_key = dkey(-INFINITY);
-    r->beta_key = dkey(-INFINITY);
-    r->pp_cells = 0;
-    r->min_rho_key = dkey(INFINITY);
-    r->min_p_key = dkey(INFINITY);
-    r->bad[0] = r->bad[1] = r->bad[2] = r->bad[3] = 0;
+    if (p < n) reset_reduce((Reduce*)gs[p].red);
 }
 
 // Trial step of the time-step rule from the stage-1 wave speed, halved once
@@ -2306,18 +2320,19 @@ void launch_flux2(const BatchL& b, hipStream_t st) {
 
 // full_grad: the reverse mode also stores the full volume values.
 template <int TX>
-void launch_recon2(const BatchL& b, int si, int alpha, int gst, hipStream_t st, Timer* tm) {
+void launch_recon2(const BatchL& b, int si, int alpha, int gst, const double* U, hipStream_t st,
+                   Timer* tm) {
     const unsigned n = b.blocks(KB_RECON);
     const Batch a = b.arg(KB_RECON);
     if (b.full_grad) {
-        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, true, false>, n, 256, st, a, si, alpha, gst);
-        else tlaunch(tm, KC_RECON, k_recon2<TX, false, true, false>, n, 256, st, a, si, alpha, gst);
+        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, true, false>, n, 256, st, a, si, alpha, gst, U);
+        else tlaunch(tm, KC_RECON, k_recon2<TX, false, true, false>, n, 256, st, a, si, alpha, gst, U);
     } else if (gst == GHOSTS_FILLED) {
-        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, false, false>, n, 256, st, a, si, alpha, gst);
-        else tlaunch(tm, KC_RECON, k_recon2<TX, false, false, false>, n, 256, st, a, si, alpha, gst);
+        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, false, false>, n, 256, st, a, si, alpha, gst, U);
+        else tlaunch(tm, KC_RECON, k_recon2<TX, false, false, false>, n, 256, st, a, si, alpha, gst, U);
     } else {
-        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, false, true>, n, 256, st, a, si, alpha, gst);
-        else tlaunch(tm, KC_RECON, k_recon2<TX, false, false, true>, n, 256, st, a, si, alpha, gst);
+        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, false, true>, n, 256, st, a, si, alpha, gst, U);
+        else tlaunch(tm, KC_RECON, k_recon2<TX, false, false, true>, n, 256, st, a, si, alpha, gst, U);
     }
 }
 
@@ -2331,7 +2346,8 @@ void launch_rgrad2(const BatchL& b, hipStream_t st, Timer* tm) {
                 b.arg(KB_RGRAD));
 }
 
-hipError_t launch_residual2(const BatchL& b, int si, int gst, hipStream_t st, Timer* tm, bool alpha) {
+hipError_t launch_residual2(const BatchL& b, int si, int gst, hipStream_t st, Timer* tm, bool alpha,
+                            const double* U) {
     const unsigned nr = b.blocks(KB_RECON), ng = b.blocks(KB_GRAD);
     const Batch ar = b.arg(KB_RECON);
     if (b.dr) {   // HWENO-DR: gradients and volume fluxes come with the reconstruction
@@ -2343,9 +2359,9 @@ hipError_t launch_residual2(const BatchL& b, int si, int gst, hipStream_t st, Ti
             else tlaunch(tm, KC_RECON, k_recon2_dr<32, false>, nr, 256, st, ar, si);
         }
     } else if (b.tiles.recon == 16) {
-        launch_recon2<16>(b, si, alpha, gst, st, tm);
+        launch_recon2<16>(b, si, alpha, gst, U, st, tm);
     } else {
-        launch_recon2<32>(b, si, alpha, gst, st, tm);
+        launch_recon2<32>(b, si, alpha, gst, U, st, tm);
     }
     if (!b.dr && !b.full_grad) {   // HWENO-GR: gradients from the weak moments
         if (b.var_mu) launch_rgrad2<true>(b, st, tm);
@@ -2394,6 +2410,11 @@ hipError_t launch_update2(const BatchL& b, int stage, int i0, int iin, int iout,
         tlaunch(tm, KC_UPDATE, k_update2, b.blocks(KB_CELLS), 256, st, b.arg(KB_CELLS), stage, i0,
                 iin, iout, R, Vhat, src);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_place2(const Place2& a, hipStream_t st) {
+    k_place2<<<1, 256, 0, st>>>(a);
     return hipGetLastError();
 }
 

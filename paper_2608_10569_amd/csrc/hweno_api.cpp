@@ -126,9 +126,6 @@ struct hweno_ctx {
     // allocation-free residual (hweno_residual_noalloc): the descriptors it
     // copies into the library's static scratch, kept here so that the copies
     // read host memory that outlives the call
-    hw::Grid2 sgrid{};
-    hw::InstState sstate{};
-    int sstart[2 * hw::KB_COUNT] = {};
     hw::Timer* tm() { return timer.on ? &timer : nullptr; }
     const Inst& i0() const { return in[0]; }
     int dim() const { return in[0].grid.dim; }
@@ -650,12 +647,18 @@ hweno_status residual(hweno_ctx* c, int si, const hw::BatchL* b = nullptr) {
     return dev(hw::launch_residual1(c->g1, c->S1[si], c->stream, c->tm()));
 }
 
-// 2D residual at a state whose ghost cells are not filled: by a launch of their
-// own, also while that is timed, or in the reconstruction (the walls inside the
-// grid here).  alpha: the CFL wave speed is wanted.
+// Whether a 2D residual's ghost cells are filled by a launch of their own (also
+// while that is timed) or formed in the reconstruction.
+bool fills_ghosts(hweno_ctx* c) {
+    const hw::Timer* tm = c->tm();
+    return !c->bl.forms_ghosts() || (tm && (tm->mask >> hw::KC_GHOST & 1u));
+}
+
+// 2D residual at a state whose ghost cells are not filled (nor the walls inside
+// the grid).  alpha: the CFL wave speed is wanted.
 hweno_status eval2(hweno_ctx* c, int si, int stage = -1, bool alpha = true) {
     hw::Timer* tm = c->tm();
-    if (!c->bl.forms_ghosts() || (tm && (tm->mask >> hw::KC_GHOST & 1u))) {
+    if (fills_ghosts(c)) {
         TRY(ghost(c, si, stage));
         stage = hw::GHOSTS_FILLED;
     } else if (!c->batch && !c->sdst_host.empty()) {
@@ -1189,9 +1192,13 @@ HWENO_API hweno_status hweno_residual(hweno_ctx* c, const double* U, double* R, 
     if (!c || !U || !R || !V || c->batch) return HWENO_E_INVAL;
     if (!c->ws) return HWENO_E_WORKSPACE;
     if (c->dim() == 2) {
-        TRY(dev(hw::launch_copy_in2(g2(c), U, g2(c).S[2], c->stream)));
         TRY(reset(c));
-        TRY(eval2(c, 2));
+        if (fills_ghosts(c) || !c->sdst_host.empty()) {
+            TRY(dev(hw::launch_copy_in2(g2(c), U, g2(c).S[2], c->stream)));
+            TRY(eval2(c, 2));
+        } else {
+            TRY(dev(hw::launch_residual2(c->bl, 2, -1, c->stream, c->tm(), true, U)));
+        }
         TRY(update(c, 0, 2, 2, 2, R, V));
     } else {
         TRY(residual1(c->g1, U, c->S1[2], R, V, c->stream, c->tm()));
@@ -1283,7 +1290,9 @@ HWENO_API hweno_status hweno_residual_noalloc(hweno_ctx* c, const double* U, dou
     hipStream_t st = c->stream;
     hw::Reduce* red = nullptr;
     if (c->dim() == 2) {
-        hw::Grid2 g = c->hg[0];
+        hw::Place2 pl;
+        hw::Grid2& g = pl.g;
+        g = c->hg[0];
         hw::Grid2* dg = nullptr;
         hw::InstState* dst = nullptr;
         int* dstart = nullptr;
@@ -1292,28 +1301,28 @@ HWENO_API hweno_status hweno_residual_noalloc(hweno_ctx* c, const double* U, dou
         void* base = nullptr;
         TRY(dev(hw::static_scratch(&base)));
         static_layout2(g, static_cast<char*>(base), &dg, &dst, &dstart);
-        c->sgrid = g;
-        c->sstate = hw::InstState{};
-        c->sstate.active = 1;
-        hw::batch_blocks(&c->sgrid, 1, c->tiles, c->sstart);
-        TRY(dev(hipMemcpyAsync(dg, &c->sgrid, sizeof(hw::Grid2), hipMemcpyHostToDevice, st)));
-        TRY(dev(hipMemcpyAsync(dst, &c->sstate, sizeof(hw::InstState), hipMemcpyHostToDevice,
-                               st)));
-        TRY(dev(hipMemcpyAsync(dstart, c->sstart, sizeof(c->sstart), hipMemcpyHostToDevice,
-                               st)));
+        pl.st = hw::InstState{};
+        pl.st.active = 1;
+        hw::batch_blocks(&g, 1, c->tiles, pl.start);
+        pl.dg = dg;
+        pl.dst = dst;
+        pl.dstart = dstart;
+        TRY(dev(hw::launch_place2(pl, st)));
         hw::BatchL bl;
         bl.dg = dg;
         bl.dstart = dstart;
-        bl.hstart = c->sstart;
+        bl.hstart = pl.start;
         bl.n = 1;
         bl.tiles = c->tiles;
         bl.var_mu = c->i0().phys.mu_exp != 0.0;
         bl.dr = c->i0().opt.gradients != 0;
-        TRY(dev(hw::launch_copy_in2(g, U, g.S[0], st)));
-        TRY(dev(hw::launch_reset2(bl, st)));
-        const bool own = bl.forms_ghosts();
-        if (!own) TRY(dev(hw::launch_ghost2(bl, 0, st, nullptr)));
-        TRY(dev(hw::launch_residual2(bl, 0, own ? -1 : hw::GHOSTS_FILLED, st, nullptr)));
+        if (bl.forms_ghosts()) {
+            TRY(dev(hw::launch_residual2(bl, 0, -1, st, nullptr, true, U)));
+        } else {
+            TRY(dev(hw::launch_copy_in2(g, U, g.S[0], st)));
+            TRY(dev(hw::launch_ghost2(bl, 0, st, nullptr)));
+            TRY(dev(hw::launch_residual2(bl, 0, hw::GHOSTS_FILLED, st, nullptr)));
+        }
         TRY(dev(hw::launch_update2(bl, 0, 0, 0, 0, R, V, st, nullptr)));
         red = (hw::Reduce*)g.red;
     } else {

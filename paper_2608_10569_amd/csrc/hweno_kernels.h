@@ -282,8 +282,21 @@ hipError_t launch_ghost2(const BatchL& b, int si, hipStream_t st, Timer* tm, int
 hipError_t launch_solid2(const Grid2* g, int n, int si, hipStream_t st);
 // alpha: the reconstruction also reduces the CFL wave speed (stage 1 and single
 // residuals; nothing reads it after the later stages)
+// U: the input in the caller's interior layout, read in place of S[si] where
+// the reconstruction forms the ghost cells, or null
 hipError_t launch_residual2(const BatchL& b, int si, int gst, hipStream_t st, Timer* tm,
-                            bool alpha = true);
+                            bool alpha = true, const double* U = nullptr);
+// Device descriptors of a single-grid call without a workspace, put in place
+// (with the reduction slots reset) by one launch.
+struct Place2 {
+    Grid2 g;
+    InstState st;
+    int start[2 * KB_COUNT];
+    Grid2* dg;
+    InstState* dst;
+    int* dstart;
+};
+hipError_t launch_place2(const Place2& a, hipStream_t st);
 // stage 0: write R (12) and Vhat (8) in interior layout (single grid);
 // stage 1..3: RK update S[iout] from S[i0] (U^n) and S[iin] (stage input);
 // src (single grid, may be null): source moments added to the residual

@@ -4,6 +4,7 @@ every rule on every side, corners of two rules, grids no wider than the halo,
 inflow states, profiles and stage profiles, and a limited cell at the edge.
 Both read the same cells, so every comparison is exact."""
 
+import ctypes
 import itertools
 
 import numpy as np
@@ -87,3 +88,17 @@ def test_line_between_the_variants(shape):
     U = torch.from_numpy(workloads.random_smooth_2d(nx, ny, seed=5, noise=1e-3)).cuda()
     s = hweno.Solver(nx, ny, mu_ref=1e-3, bc=('noslip', 'outflow', 'slip', 'noslip'))
     compare(s, U)
+
+
+def test_outputs_in_the_inputs_memory():
+    """The reconstruction reads the caller's state itself: R may still be
+    written over it, as the state is read before anything is written."""
+    nx, ny = 37, 29
+    U = torch.from_numpy(workloads.random_smooth_2d(nx, ny, seed=4, noise=1e-3)).cuda()
+    s = hweno.Solver(nx, ny, mu_ref=1e-3, bc=('noslip', 'outflow', 'slip', 'noslip'))
+    R, V, _ = s.residual(U)
+    for f in (hweno.lib().hweno_residual, hweno.lib().hweno_residual_noalloc):
+        W, V2 = U.clone(), torch.empty_like(V)
+        p = [ctypes.c_void_p(q.data_ptr()) for q in (W, W, V2)]
+        assert f(s._h, *p, None) == 0
+        assert torch.equal(W, R) and torch.equal(V2, V)
