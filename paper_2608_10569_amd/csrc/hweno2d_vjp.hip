@@ -13,14 +13,14 @@
 //   k_adj_flux<d>  face-flux adjoint (eq. (3.3)) -> trace / face-gradient adjoints
 //   k_adj_grad     volume-flux + gradient-reconstruction adjoint (eq. (3.9))
 //   k_adj_rgather  gather of the weak-moment adjoints from the 3x3 stencils
-//   k_adj_wmom     weak-moment adjoint (eqs. (3.6)-(3.8)) -> trace / volume adjoints
-//   k_adj_recon_a  forward recompute; limiter and back-transform adjoints
-//   k_adj_recon_b  scalar HWENO, eigen-system and projection adjoints
-//   k_adj_ugather  gather of the state adjoint from the 3x3 stencils
-//   k_adj_ghost_out adjoint of the ghost fill (Remark 4.1), written to the output
+//   k_adj_recon    weak-moment adjoint (eqs. (3.6)-(3.8)), limiter, back-transform,
+//                  scalar HWENO, eigen-system and projection adjoints; stencil sums
+//   k_adj_out      sums of the tiles' stencil shares and the adjoint of the ghost
+//                  fill (Remark 4.1), written to the output
 //   k_mu_sum       fixed-order sum of the mu-adjoint block partials
 
 #include "hweno_adj.h"
+#include "hweno_basis2.h"
 #include "hweno_vjp.h"
 
 namespace hw {
@@ -65,8 +65,7 @@ __device__ __forceinline__ double rbar(const AdjIn& A, const Grid2& g, int m, in
 // Logical index of this block: XCD-aware (each XCD takes a contiguous range
 // of the launch, so neighbouring rows of a stencil share an L2), last first
 // where bit k of W.rev is set (k: 0, 1 face fluxes x, y; 2 gradients; 3
-// weak-moment gather; 4 weak moments; 5, 7 the two reconstruction kernels;
-// 6 state gather).
+// weak-moment gather; 5 reconstruction).
 // The mu partials are stored by it, so their fixed summation order is
 // unchanged.
 __device__ __forceinline__ int lblock(const AdjWs& W, int k) {
@@ -335,605 +334,661 @@ __global__ __launch_bounds__(6 * AG) void k_adj_grad(Grid2 g, AdjIn A, AdjWs W) 
 // Gather of the weak-moment adjoints: cell X is slot k of the 3x3 stencil of
 // cell X - off(k).  Cells of halo ring 2.
 // ---------------------------------------------------------------------------
+// One gradient component s = 2 w + l per thread (the grid's second index); the 17
+// loads are unconditional (at the cell itself where the stencil's cell is not in
+// ring 1) and issued together: with a branch per slot and all components in one
+// thread the kernel took 25 us on 256 x 256.
 __global__ void k_adj_rgather(Grid2 g, AdjWs W) {
     const int wc = g.NX - 4;
-    const long long nreg = (long long)wc * (g.NY - 4);
-    const long long cid = (long long)lblock(W, 3) * blockDim.x + threadIdx.x;
+    const int nreg = wc * (g.NY - 4);
+    const int cid = lblock(W, 3) * (int)blockDim.x + (int)threadIdx.x;
     if (cid >= nreg) return;
-    const int j = 2 + (int)(cid / wc), i = 2 + (int)(cid % wc);
+    const int j = 2 + cid / wc, i = 2 + cid % wc;
     const long long N = g.ncell;
-    const long long cell = (long long)j * g.NX + i;
-    for (int s = 0; s < 6; ++s) {
-        const int w = s >> 1, l = s & 1;
-        double m0 = 0.0, m1 = 0.0, m2 = 0.0;
+    const int cell = j * g.NX + i;
+    const int s = (int)blockIdx.y, w = s >> 1, l = s & 1;
+    const double* P = W.rbc + (long long)s * 17 * N;
+    double m0 = 0.0, m1 = 0.0, m2 = 0.0;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const int ox = k % 3 - 1, oy = k / 3 - 1;
-            const int yj = j - oy, yi = i - ox;
-            if (yj < 3 || yj > g.NY - 4 || yi < 3 || yi > g.NX - 4) continue;   // not in ring 1
-            const long long Y = (long long)yj * g.NX + yi;
-            m0 += W.rbc[(s * 17 + k) * N + Y];
-            if (k & 1) {
-                const int e = k >> 1;     // k = 1, 3, 5, 7 -> edge slot 0..3
-                m1 += W.rbc[(s * 17 + 9 + e) * N + Y];
-                m2 += W.rbc[(s * 17 + 13 + e) * N + Y];
-            }
+    for (int k = 0; k < 9; ++k) {
+        const int ox = k % 3 - 1, oy = k / 3 - 1;
+        const int yj = j - oy, yi = i - ox;
+        const bool in = yj >= 3 && yj <= g.NY - 4 && yi >= 3 && yi <= g.NX - 4;   // ring 1
+        const int Y = in ? yj * g.NX + yi : cell;
+        const double x0 = P[k * N + Y];
+        m0 += in ? x0 : 0.0;
+        if (k & 1) {
+            const int e = k >> 1;     // k = 1, 3, 5, 7 -> edge slot 0..3
+            const double x1 = P[(9 + e) * N + Y], x2 = P[(13 + e) * N + Y];
+            m1 += in ? x1 : 0.0;
+            m2 += in ? x2 : 0.0;
         }
-        W.rbb[((l * 3 + w) * 3 + 0) * N + cell] = m0;
-        W.rbb[((l * 3 + w) * 3 + 1) * N + cell] = m1;
-        W.rbb[((l * 3 + w) * 3 + 2) * N + cell] = m2;
     }
+    W.rbb[((l * 3 + w) * 3 + 0) * N + cell] = m0;
+    W.rbb[((l * 3 + w) * 3 + 1) * N + cell] = m1;
+    W.rbb[((l * 3 + w) * 3 + 2) * N + cell] = m2;
 }
 
-// ---------------------------------------------------------------------------
-// Weak-moment adjoint (eqs. (3.6)-(3.8)) on cells X of ring 3 (every cell
-// with a reconstruction): its four faces' interface averages take adjoints
-// from the weak moments of both adjacent cells; half goes to each trace.
-// The wbar adjoint goes to the volume values.
-// ---------------------------------------------------------------------------
+// Ring 2: the cells with weak moments.
 __device__ __forceinline__ bool in_ring2(const Grid2& g, int j, int i) {
     return j >= 2 && j <= g.NY - 3 && i >= 2 && i <= g.NX - 3;
 }
 
-// Six independent tasks per cell, one per wavefront of the block: tasks 0..3
-// the four faces (left, right, bottom, top), tasks 4..5 the volume values of
-// the x and y bases.  Every task owns the cotangent slots it adds to.
-constexpr int WM_CELLS = 64;
-
-__global__ __launch_bounds__(6 * WM_CELLS) void k_adj_wmom(Grid2 g, AdjWs W) {
-    const int task = threadIdx.x / WM_CELLS;
-    const int wc = g.NX - 2;
-    const long long nreg = (long long)wc * (g.NY - 2);
-    const long long cid = (long long)lblock(W, 4) * WM_CELLS + threadIdx.x % WM_CELLS;
-    if (cid >= nreg) return;
-    const int j = 1 + (int)(cid / wc), i = 1 + (int)(cid % wc);
-    const long long N = g.ncell;
-    const long long cell = (long long)j * g.NX + i;
-    const double idx = g.K.idx, idy = g.K.idy;
-    auto RB = [&](int jj, int ii, int l, int w, int mom) -> double {
-        if (!in_ring2(g, jj, ii)) return 0.0;
-        return W.rbb[((l * 3 + w) * 3 + mom) * N + (long long)jj * g.NX + ii];
-    };
-    if (task < 4) {
-        // face `task`: 0 left (x, this cell is the plus side), 1 right (minus
-        // side), 2 bottom (y, plus side), 3 top (minus side)
-        const int face = task;
-        const int dir = face >> 1;
-        const bool hi = face & 1;
-        const int oj = dir == 1 ? (hi ? 1 : -1) : 0, oi = dir == 0 ? (hi ? 1 : -1) : 0;
-        const double* F = dir == 0 ? g.xf : g.yf;
-        double* FB = dir == 0 ? W.xfb : W.yfb;
-        const double ih = dir == 0 ? idx : idy;
-        double W0b[3], W1b[3];
-#pragma unroll
-        for (int w = 0; w < 3; ++w) {
-            // contributions of this cell (face on its hi side or lo side) and of the neighbour
-            const double own0 = RB(j, i, dir, w, 0);
-            const double ownm = RB(j, i, dir, w, dir == 0 ? 1 : 2);      // the (W0+ + W0-)/2 moment
-            const double own1 = RB(j, i, dir, w, dir == 0 ? 2 : 1);      // the transverse moment
-            const double nb0 = RB(j + oj, i + oi, dir, w, 0);
-            const double nbm = RB(j + oj, i + oi, dir, w, dir == 0 ? 1 : 2);
-            const double nb1 = RB(j + oj, i + oi, dir, w, dir == 0 ? 2 : 1);
-            if (hi) {   // this cell's upper face = neighbour's lower face
-                W0b[w] = (own0 + 0.5 * ownm) * ih + (-nb0 + 0.5 * nbm) * ih;
-                W1b[w] = own1 * ih - nb1 * ih;
-            } else {
-                W0b[w] = (-own0 + 0.5 * ownm) * ih + (nb0 + 0.5 * nbm) * ih;
-                W1b[w] = -own1 * ih + nb1 * ih;
-            }
-        }
-#pragma unroll
-        for (int G = 0; G < 3; ++G) {
-            const int p = (hi ? 3 : 0) + G;
-            double U[4], wb[3], Ub[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int c = 0; c < 4; ++c) U[c] = F[(p * 4 + c) * N + cell];
-#pragma unroll
-            for (int w = 0; w < 3; ++w) wb[w] = 0.5 * gw(G) * (W0b[w] + gx(G) * W1b[w]);
-            adj::prim2_vjp(U, wb, Ub);
-            const bool add = flux_face(g, j, i, dir * 2 + (hi ? 1 : 0));
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                double& x = FB[(p * 4 + c) * N + cell];
-                x = add ? x + Ub[c] : Ub[c];
-            }
-        }
-    } else if (!in_ring2(g, j, i)) {
-        // no weak moments here: the volume-value adjoints are zero
-        double* VB = task == 4 ? W.xvb : W.yvb;
-        for (int q = 0; q < 36; ++q) VB[q * N + cell] = 0.0;
-    } else {
-        // wbar adjoint of this cell's own weak moments, to its volume values
-        // (added to the volume-flux adjoints on interior cells)
-        const int dir = task - 4;
-        const bool add = interior(g, j, i);
-        const double* V = dir == 0 ? g.xv : g.yv;
-        double* VB = dir == 0 ? W.xvb : W.yvb;
-        double wbb[3];
-#pragma unroll
-        for (int w = 0; w < 3; ++w)
-            wbb[w] = -RB(j, i, dir, w, dir == 0 ? 1 : 2) * (dir == 0 ? idx : idy);
-        for (int q = 0; q < 9; ++q) {
-            const double wq = gw(q / 3) * gw(q % 3);
-            double U[4], wb[3], Ub[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int c = 0; c < 4; ++c) U[c] = V[(q * 4 + c) * N + cell];
-#pragma unroll
-            for (int w = 0; w < 3; ++w) wb[w] = wq * wbb[w];
-            adj::prim2_vjp(U, wb, Ub);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                double& x = VB[(q * 4 + c) * N + cell];
-                x = add ? x + Ub[c] : Ub[c];
-            }
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
-// Characteristic reconstruction adjoint, in two kernels over the same cells.
-// Block: 16 cells x 8 threads (b = basis, k = characteristic field /
-// conservative component).
-//   k_adj_recon_a: forward recompute (scalar HWENO, back-transform, limiter),
-//     adjoint of the limiter and of the back-transform: the cotangents of
-//     the 16 characteristic outputs of every (cell, b, k), the R-bar rows and
-//     the limiter's share of the cell-average adjoint go to the workspace;
-//   k_adj_recon_b: the scalar HWENO adjoint, the eigen-system adjoint and the
-//     projection adjoint.
-// Split, each kernel keeps fewer values live and less LDS per block than the
-// one kernel before it (256 VGPRs plus spill space, 75 KB of LDS, one wave
-// per SIMD).
+// Reconstruction adjoint: weak-moment shares of the point values (eqs.
+// (3.6)-(3.8)), limiter, back-transform, scalar HWENO, eigen-system and
+// projection adjoints of a tile of cells in one kernel.
+// Block: AT_X x AT_Y cells, four wavefronts, one thread per cell in each, split
+// as the forward kernel: wavefront (b, h) works in basis b on the fields
+// {0, 3} (h = 0) or {1, 2} and owns the face points (h = 0) or the volume points
+// of its basis, in the basis's (normal, tangential) coordinates.  It recomputes the
+// point values, forms the cotangents of all four fields at its own points,
+// hands the partner's two over in LDS and takes its own two back through
+// the scalar reconstruction.  The stencil shares of the tile's cells are summed
+// in LDS: in each of four phases a wavefront adds its share of one conserved
+// component, so every sum has a fixed order, and the tile with its ring of one
+// cell (25.5 doubles per cell) goes to the workspace for k_adj_out.
+// Bound: the latency of two wavefronts per SIMD (256 registers, about 6000
+// instructions each).  A thread per field in two kernels, which exchanged the
+// point values through LDS and 160 cotangents per cell through memory, a
+// weak-moment kernel that read and wrote all point cotangents (360 doubles per
+// cell) and a gather of 136 stencil shares per cell took 77 + 92 + 48 + 18 us on
+// 256 x 256; this kernel takes 102 - 110.
 // ---------------------------------------------------------------------------
-constexpr int AC = 16;
+constexpr int AT_X = 32, AT_Y = 2, AT_W = AT_X + 2, AT_H = AT_Y + 2, AT_P = AT_W * AT_H;
 
-__device__ __forceinline__ int pt_index(int b, int o) { return o < 6 ? b * 6 + o : 12 + b * 9 + (o - 6); }
+inline __host__ __device__ int at_tiles_x(const Grid2& g) { return (g.NX - 1 + AT_X - 1) / AT_X; }
+inline __host__ __device__ int at_tiles_y(const Grid2& g) { return (g.NY - 2 + AT_Y - 1) / AT_Y; }
 
-__global__ __launch_bounds__(8 * AC) void k_adj_recon_a(Grid2 g, AdjIn A, AdjWs W,
-                                                        const double* __restrict__ S) {
-    __shared__ double shc[8 * 16 * AC];   // characteristic point values (b, f, o)
-    // conservative point values (b, c, o); once the limiter adjoint has read
-    // them, the adjoints of the conservative values
-    __shared__ double shu[8 * 16 * AC];
-    __shared__ double shr[8 * AC];        // reductions (value)
-    __shared__ int shi[8 * AC];           // reductions (index)
-    __shared__ double shx[8 * AC];        // second reduction value
-    // limiter adjoints: slots 0..7 per-thread cell-average part (b*4+c), 8 P1 density,
-    // 9..12 P2 components, 13..16 cell-level part (rbar, pbar, eps)
-    __shared__ double shp[17 * AC];
-    __shared__ int shpi[2 * AC];
-    const Consts& K = g.K;
-    const int tid = threadIdx.x;
-    const int cl = tid % AC;
-    const int bk = tid / AC;
-    const int b = bk >> 2, k = bk & 3;
-    const int wc = g.NX - 2;
-    const long long nreg = (long long)wc * (g.NY - 2);
-    const long long cid = (long long)lblock(W, 5) * AC + cl;
-    const bool valid = cid < nreg;
-    int j = 1, i = 1;
-    if (valid) {
-        j = 1 + (int)(cid / wc);
-        i = 1 + (int)(cid % wc);
-    }
-    const long long N = g.ncell;
-    const long long cell = (long long)j * g.NX + i;
-    auto C_ = [&](int bb, int f, int o) -> double& { return shc[((bb * 4 + f) * 16 + o) * AC + cl]; };
-    auto U_ = [&](int bb, int c, int o) -> double& { return shu[((bb * 4 + c) * 16 + o) * AC + cl]; };
-    auto B_ = [&](int bb, int c, int o) -> double& { return shu[((bb * 4 + c) * 16 + o) * AC + cl]; };
+// Basis b's normal direction is x (b = 0) or y (b = 1): offset of stencil slot
+// s in the tile and plane of the normal and tangential moment fields.
+template <int b>
+struct TileBasis {
+    static constexpr int sn = b ? AT_W : 1, st = b ? 1 : AT_W;
+    static constexpr int mn = b ? 8 : 4, mt = b ? 4 : 8;
+    static constexpr int off(int s) { return (s % 3 - 1) * sn + (s / 3 - 1) * st; }
+};
 
-    // ---- forward recompute (as the forward reconstruction kernel) ----
-    double ub[4];
+// Adjoint of row L = (left eigenvector of field f) of project2: Lb[c] = sum_s ab[s] *
+// stencil datum (s, c).
+template <int b>
+__device__ __forceinline__ void project2_rowbar(const double* T0, const double* ab, double* Lb) {
+    constexpr int cm[4] = {0, b ? 2 : 1, b ? 1 : 2, 3};
+    using TB = TileBasis<b>;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) ub[c] = S[c * N + cell];
-    double Lr[4], Rr[4];
-    eig2_rows(K, ub, b, k, Lr, Rr);
-    // projected stencil data of field k (recomputed before the scalar adjoint
-    // instead of being kept live through the limiter)
-    auto project = [&](const double* Lrow, double* a) {
+    for (int c = 0; c < 4; ++c) Lb[c] = 0.0;
 #pragma unroll
-        for (int s = 0; s < 9; ++s) {
-            const long long nb = cell + (long long)(s / 3 - 1) * g.NX + (s % 3 - 1);
-            double acc = 0.0;
+    for (int s = 0; s < 9; ++s)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc += Lrow[c] * S[c * N + nb];
-            a[s] = acc;
-        }
+        for (int c = 0; c < 4; ++c) Lb[c] += ab[s] * T0[TB::off(s) + cm[c] * AT_P];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int s = 2 * e + 1;
-            const long long nb = cell + (long long)(s / 3 - 1) * g.NX + (s % 3 - 1);
-            double ax = 0.0, ay = 0.0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                ax += Lrow[c] * S[(4 + c) * N + nb];
-                ay += Lrow[c] * S[(8 + c) * N + nb];
-            }
-            a[9 + e] = ax;
-            a[13 + e] = ay;
-        }
-    };
-    {
-        double a[17];
-        project(Lr, a);
-        double C[15], out[16];
-        hweno2d(a, K, C);
-        if (b == 0) eval_xface(C, out);
-        else eval_yface(C, out);
-        eval_vol(C, out + 6);
-        out[15] = b == 0 ? moment_xi(C) : moment_eta(C);
-#pragma unroll
-        for (int o = 0; o < 16; ++o) C_(b, k, o) = out[o];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int o = 0; o < 16; ++o) {
-        double acc = 0.0;
-#pragma unroll
-        for (int f = 0; f < 4; ++f) acc += Rr[f] * C_(b, f, o);
-        U_(b, k, o) = acc;
-    }
-    __syncthreads();
-    // limiter forward: rho_min (argmin in the point order), theta1, then theta2
-    const double rbar = ub[0];
-    const double pbar = pressure2(K, ub[0], ub[1], ub[2], ub[3]);
-    const double e1 = K.eps_pp <= rbar ? K.eps_pp : rbar;
-    const int esrc1 = K.eps_pp <= rbar ? 0 : 1;
-    const double eps = e1 <= pbar ? e1 : pbar;
-    const int esrc = e1 <= pbar ? esrc1 : 2;
-    {
-        double v = INFINITY;
-        int ix = 1 << 30;
-        for (int o = k; o < 15; o += 4) {
-            const double r = U_(b, 0, o);
-            const int id = pt_index(b, o);
-            if (r < v || (r == v && id < ix)) { v = r; ix = id; }
-        }
-        shr[bk * AC + cl] = v;
-        shi[bk * AC + cl] = ix;
-    }
-    __syncthreads();
-    double rmin = INFINITY;
-    int irmin = 1 << 30;
-    for (int q = 0; q < 8; ++q) {
-        const double v = shr[q * AC + cl];
-        const int id = shi[q * AC + cl];
-        if (v < rmin || (v == rmin && id < irmin)) { rmin = v; irmin = id; }
-    }
-    const bool low1 = rmin < eps;
-    const double th1 = low1 ? (rbar - eps) / (rbar - rmin) : 1.0;
-    __syncthreads();
-    {
-        double v = INFINITY;
-        int ix = 1 << 30;
-        for (int o = k; o < 15; o += 4) {
-            const double rt = rbar + th1 * (U_(b, 0, o) - rbar);
-            const double pt = pressure2(K, rt, U_(b, 1, o), U_(b, 2, o), U_(b, 3, o));
-            const double t = pt < eps ? (pbar - eps) / (pbar - pt) : 1.0;
-            const int id = pt_index(b, o);
-            if (t < v || (t == v && id < ix)) { v = t; ix = id; }
-        }
-        shr[bk * AC + cl] = v;
-        shi[bk * AC + cl] = ix;
-    }
-    __syncthreads();
-    double tmin = INFINITY;
-    int itmin = 1 << 30;
-    for (int q = 0; q < 8; ++q) {
-        const double v = shr[q * AC + cl];
-        const int id = shi[q * AC + cl];
-        if (v < tmin || (v == tmin && id < itmin)) { tmin = v; itmin = id; }
-    }
-    const double th2 = tmin <= 1.0 ? tmin : 1.0;
-    const bool low2 = tmin < 1.0;
-
-    // ---- adjoint of the outputs of this thread's component k ----
-    const bool inter = valid && interior(g, j, i);
-    double Ub[16];
-    double th1b = 0.0, th2b = 0.0, ubb0 = 0.0;
-    {
-        const double* FB = b == 0 ? W.xfb : W.yfb;
-        const double* VB = b == 0 ? W.xvb : W.yvb;
-#pragma unroll
-        for (int o = 0; o < 6; ++o) {
-            const double lb = valid ? FB[(o * 4 + k) * N + cell] : 0.0;
-            const double x = U_(b, k, o);
-            if (k == 0) {
-                const double ut = rbar + th1 * (x - rbar);
-                Ub[o] = th2 * th1 * lb;
-                ubb0 += lb * (1.0 - th2 * th1);
-                th2b += lb * (ut - rbar);
-                th1b += th2 * lb * (x - rbar);
-            } else {
-                Ub[o] = th2 * lb;
-                ubb0 += lb * (1.0 - th2);
-                th2b += lb * (x - ub[k]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 9; ++q) Ub[6 + q] = valid ? VB[(q * 4 + k) * N + cell] : 0.0;
-        const long long nint = (long long)g.nx * g.ny;
-        Ub[15] = (inter && A.Vb)
-                     ? A.vs * A.Vb[(b * 4 + k) * nint + (long long)(j - HALO) * g.nx + (i - HALO)]
-                     : 0.0;
-    }
-    shr[bk * AC + cl] = th1b;
-    shx[bk * AC + cl] = th2b;
-    shp[bk * AC + cl] = ubb0;            // this thread's cell-average adjoint, component k
-    __syncthreads();
-    if (bk == 0) {
-        // cell-level limiter adjoint: thetas -> rbar, pbar, eps and the argmin points
-        double T1b = 0.0, T2b = 0.0;
-        for (int q = 0; q < 8; ++q) {
-            T1b += shr[q * AC + cl];
-            T2b += shx[q * AC + cl];
-        }
-        double rbb = 0.0, pbb = 0.0, epsb = 0.0;
-        double P2b[4] = {0.0, 0.0, 0.0, 0.0}, P1b = 0.0;
-        int b2 = 0, o2 = 0, b1 = 0, o1 = 0;
-        auto unidx = [&](int id, int& bb, int& oo) {
-            if (id < 12) { bb = id / 6; oo = id % 6; }
-            else { bb = (id - 12) / 9; oo = 6 + (id - 12) % 9; }
-        };
-        if (low2) {
-            unidx(itmin, b2, o2);
-            const double rho = U_(b2, 0, o2);
-            double Ut[4] = {rbar + th1 * (rho - rbar), U_(b2, 1, o2), U_(b2, 2, o2), U_(b2, 3, o2)};
-            const double pt = pressure2(K, Ut[0], Ut[1], Ut[2], Ut[3]);
-            const double den = pbar - pt;
-            pbb += T2b * (eps - pt) / (den * den);
-            epsb += -T2b / den;
-            const double ptb = T2b * (pbar - eps) / (den * den);
-            double Utb[4] = {0.0, 0.0, 0.0, 0.0};
-            adj::pres2_vjp(K, Ut, ptb, Utb);
-            rbb += Utb[0] * (1.0 - th1);
-            P2b[0] = Utb[0] * th1;
-            P2b[1] = Utb[1];
-            P2b[2] = Utb[2];
-            P2b[3] = Utb[3];
-            T1b += Utb[0] * (rho - rbar);
-        }
-        if (low1) {
-            unidx(irmin, b1, o1);
-            const double den = rbar - rmin;
-            rbb += T1b * (eps - rmin) / (den * den);
-            epsb += -T1b / den;
-            P1b = T1b * (rbar - eps) / (den * den);
-        }
-        if (esrc == 1) rbb += epsb;
-        double ubar_b[4] = {rbb, 0.0, 0.0, 0.0};
-        if (esrc == 2) pbb += epsb;
-        if (pbb != 0.0) adj::pres2_vjp(K, ub, pbb, ubar_b);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) shp[(13 + c) * AC + cl] = ubar_b[c];
-        // point adjoints: P2 (4 components) and P1 (density), marked by index
-        shp[8 * AC + cl] = P1b;
-        shpi[0 * AC + cl] = low1 ? (b1 * 16 + o1) : -1;
-        shpi[1 * AC + cl] = low2 ? (b2 * 16 + o2) : -1;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) shp[(9 + c) * AC + cl] = P2b[c];
-    }
-    __syncthreads();
-    {
-        const int p1 = shpi[0 * AC + cl], p2 = shpi[1 * AC + cl];
-        if (p1 >= 0 && k == 0 && p1 / 16 == b) Ub[p1 % 16] += shp[8 * AC + cl];
-        if (p2 >= 0 && p2 / 16 == b) Ub[p2 % 16] += shp[(9 + k) * AC + cl];
-    }
-#pragma unroll
-    for (int o = 0; o < 16; ++o) B_(b, k, o) = Ub[o];
-    __syncthreads();
-    // ---- back-transform adjoint: char-bar_f = sum_c R[c][f] Ub_c; R-bar row k ----
-    double Rb[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int o = 0; o < 16; ++o) {
-#pragma unroll
-        for (int f = 0; f < 4; ++f) Rb[f] += Ub[o] * C_(b, f, o);
-    }
-    // column k of R (eigenvector of field k), formed from the cell average
-    double Rk[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        double Lt[4], Rt[4];
-        eig2_rows(K, ub, b, c, Lt, Rt);
-        Rk[c] = Rt[k];
-    }
-    double cb[16];
-#pragma unroll
-    for (int o = 0; o < 16; ++o) {
-        double acc = 0.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc += Rk[c] * B_(b, c, o);
-        cb[o] = acc;
-    }
-    // ---- to the workspace: cotangents of the characteristic outputs, the
-    // R-bar row, and (thread b = 0, k = c) the limiter's cell-average part
-    // of component c ----
-    if (valid) {
-#pragma unroll
-        for (int o = 0; o < 16; ++o) W.rcb[(bk * 16 + o) * N + cell] = cb[o];
-#pragma unroll
-        for (int f = 0; f < 4; ++f) W.rrb[(bk * 4 + f) * N + cell] = Rb[f];
-        if (b == 0)
-            W.rlim[k * N + cell] = shp[(0 * 4 + k) * AC + cl] + shp[(1 * 4 + k) * AC + cl] +
-                                   shp[(13 + k) * AC + cl];
-    }
-}
-
-// Scalar HWENO, eigen-system and projection adjoints of (cell, b, k), from
-// the cotangents k_adj_recon_a left in the workspace.
-__global__ __launch_bounds__(8 * AC, 2) void k_adj_recon_b(Grid2 g, AdjWs W,
-                                                        const double* __restrict__ S) {
-    __shared__ double sha[8 * 17 * AC];   // adjoints of the projected inputs (b, k, s)
-    __shared__ double shL[8 * 4 * AC];    // rows of L (b, k, c)
-    __shared__ double shq[8 * 4 * AC];    // eigen-system part of the cell-average adjoint
-    const Consts& K = g.K;
-    const int tid = threadIdx.x;
-    const int cl = tid % AC;
-    const int bk = tid / AC;
-    const int b = bk >> 2, k = bk & 3;
-    const int wc = g.NX - 2;
-    const long long nreg = (long long)wc * (g.NY - 2);
-    const long long cid = (long long)lblock(W, 7) * AC + cl;
-    const bool valid = cid < nreg;
-    int j = 1, i = 1;
-    if (valid) {
-        j = 1 + (int)(cid / wc);
-        i = 1 + (int)(cid % wc);
-    }
-    const long long N = g.ncell;
-    const long long cell = (long long)j * g.NX + i;
-    double ub[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) ub[c] = S[c * N + cell];
-    double Lr[4], Rr[4];
-    eig2_rows(K, ub, b, k, Lr, Rr);
-#pragma unroll
-    for (int f = 0; f < 4; ++f) shL[(bk * 4 + f) * AC + cl] = Lr[f];
-    double cb[16], Rb[4];
-#pragma unroll
-    for (int o = 0; o < 16; ++o) cb[o] = valid ? W.rcb[(bk * 16 + o) * N + cell] : 0.0;
-#pragma unroll
-    for (int f = 0; f < 4; ++f) Rb[f] = valid ? W.rrb[(bk * 4 + f) * N + cell] : 0.0;
-    // ---- scalar reconstruction adjoint ----
-    double Cb[15];
-#pragma unroll
-    for (int q = 0; q < 15; ++q) Cb[q] = 0.0;
-    if (b == 0) adj::xface_T(cb, Cb);
-    else adj::yface_T(cb, Cb);
-    adj::vol_T(cb + 6, Cb);
-    if (b == 0) moment_xi_T(cb[15], Cb);
-    else moment_eta_T(cb[15], Cb);
-    double ab[17];
-    {
-        double a[17];
-#pragma unroll
-        for (int s = 0; s < 9; ++s) {
-            const long long nb = cell + (long long)(s / 3 - 1) * g.NX + (s % 3 - 1);
-            double acc = 0.0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc += Lr[c] * S[c * N + nb];
-            a[s] = acc;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int s = 2 * e + 1;
-            const long long nb = cell + (long long)(s / 3 - 1) * g.NX + (s % 3 - 1);
-            double ax = 0.0, ay = 0.0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                ax += Lr[c] * S[(4 + c) * N + nb];
-                ay += Lr[c] * S[(8 + c) * N + nb];
-            }
-            a[9 + e] = ax;
-            a[13 + e] = ay;
-        }
-        hweno2d_vjp(a, K, Cb, ab);
-    }
-#pragma unroll
-    for (int s = 0; s < 17; ++s) sha[(bk * 17 + s) * AC + cl] = ab[s];
-    // L-bar row k: sum_s ab[s] * stencil value (component c)
-    double Lb[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int s = 0; s < 9; ++s) {
-        const long long nb = cell + (long long)(s / 3 - 1) * g.NX + (s % 3 - 1);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) Lb[c] += ab[s] * S[c * N + nb];
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int s = 2 * e + 1;
-        const long long nb = cell + (long long)(s / 3 - 1) * g.NX + (s % 3 - 1);
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-            Lb[c] += ab[9 + e] * S[(4 + c) * N + nb] + ab[13 + e] * S[(8 + c) * N + nb];
-    }
-    double ubp[4] = {0.0, 0.0, 0.0, 0.0};
-    if (b == 0) adj::eig2_vjp_0(K, ub, k, Lb, Rb, ubp);
-    else adj::eig2_vjp_1(K, ub, k, Lb, Rb, ubp);
-    // cell-average adjoint of this thread: eigen part (4 comps) -> LDS for the owner threads
+            Lb[c] += ab[9 + e] * T0[TB::off(2 * e + 1) + (TB::mn + cm[c]) * AT_P] +
+                     ab[13 + e] * T0[TB::off(2 * e + 1) + (TB::mt + cm[c]) * AT_P];
+}
+
+// A wavefront's half: its points and the slots of the exchange it owns (the face
+// points and the moment, or the volume points).
+template <int h>
+struct Part {
+    static constexpr int value = h, points = h ? 9 : 6, slots = h ? 9 : 7;
+};
+
+// Add v to an LDS word: no other wavefront touches it in this phase and the lanes
+// of one call have words of their own, so the sums have the program's order.
+__device__ __forceinline__ void lds_add(double* p, double v) {
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Share of a field (entry l of its row of L, input adjoints ab) in component G
+// (global number) of the cell's stencil.
+template <int b>
+__device__ __forceinline__ void scatter2(double* A0, int G, double l, const double* ab) {
+    using TB = TileBasis<b>;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) shq[((b * 4 + k) * 4 + c) * AC + cl] = ubp[c];
-    __syncthreads();
-    // ---- projection adjoint, thread (b, c): sum_k L[k][c] ab_k[s] ----
-    if (valid) {
-        const int c = k;
-        double* UC = W.uc + (long long)b * 68 * N;
+    for (int s = 0; s < 9; ++s) lds_add(A0 + TB::off(s) + G * AT_P, l * ab[s]);
 #pragma unroll
-        for (int s = 0; s < 17; ++s) {
-            double acc = 0.0;
-#pragma unroll
-            for (int f = 0; f < 4; ++f) acc += shL[((b * 4 + f) * 4 + c) * AC + cl] * sha[((b * 4 + f) * 17 + s) * AC + cl];
-            if (s == 4) {
-                // own cell average: eigenvector dependence (both fields' rows of this basis)
-#pragma unroll
-                for (int f = 0; f < 4; ++f) acc += shq[((b * 4 + f) * 4 + c) * AC + cl];
-                // limiter: per-component pass-through of theta and the cell-level part
-                if (b == 0) acc += W.rlim[c * N + cell];
-            }
-            UC[(s * 4 + c) * N + cell] = acc;
-        }
+    for (int e = 0; e < 4; ++e) {
+        lds_add(A0 + TB::off(2 * e + 1) + (TB::mn + G) * AT_P, l * ab[9 + e]);
+        lds_add(A0 + TB::off(2 * e + 1) + (TB::mt + G) * AT_P, l * ab[13 + e]);
     }
 }
 
-// ---------------------------------------------------------------------------
-// State adjoint on the ghosted grid: cell X is slot k of the stencil of
-// cell X - off(k) (averages: all 9 slots; moments: the 4 edge slots).
-// ---------------------------------------------------------------------------
-__global__ void k_adj_ugather(Grid2 g, AdjWs W) {
-    const long long t = (long long)lblock(W, 6) * blockDim.x + threadIdx.x;
-    if (t >= g.ncell) return;
-    const int j = (int)(t / g.NX), i = (int)(t % g.NX);
+__global__ __launch_bounds__(256, 2) void k_adj_recon(Grid2 g, AdjIn A, AdjWs W,
+                                                      const double* __restrict__ S) {
+    constexpr int PL = AT_P;
+    constexpr int NP = (PL + 63) / 64;
+    constexpr int XB = 2 * (9 + 7) * 64;   // values at the partner's points: one field of each wavefront
+    __shared__ double sh[2 * XB];
+    __shared__ double tile[12 * PL];
+    __shared__ double sums[12 * PL];       // the stencil sums
+    __shared__ double shm[2][4][64];       // least [density, pressure] of a wavefront's points
+    __shared__ int shi[2][4][64];          // and where (index in the oracle's point order)
+    __shared__ double shl[4][64];          // rare: theta adjoints; conserved values at a point
+    const Consts& K = g.K;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = wv >> 1, hh = wv & 1;
     const long long N = g.ncell;
-    double acc[12];
+    const int lb = lblock(W, 5);
+    const int tiles_x = at_tiles_x(g);
+    const int i0 = (lb % tiles_x) * AT_X, j0 = 1 + (lb / tiles_x) * AT_Y;
+    const int lx = lane % AT_X, ly = lane / AT_X;
+    const int i = i0 + lx, j = j0 + ly;
+    const bool valid = i >= 1 && i <= g.NX - 2 && j <= g.NY - 2;
+    const long long cell = valid ? (long long)j * g.NX + i : (long long)g.NX + 1;
+    {
+        double v[3][NP];
 #pragma unroll
-    for (int q = 0; q < 12; ++q) acc[q] = 0.0;
-    for (int b = 0; b < 2; ++b) {
-        const double* UC = W.uc + (long long)b * 68 * N;
+        for (int q = 0; q < NP; ++q) {
+            const int t = lane + 64 * q, r = t / AT_W, c = t - r * AT_W;
+            const int gj = min(j0 - 1 + r, g.NY - 1), gi = min(max(i0 - 1 + c, 0), g.NX - 1);
 #pragma unroll
-        for (int s = 0; s < 9; ++s) {
-            const int ox = s % 3 - 1, oy = s / 3 - 1;
-            const int yj = j - oy, yi = i - ox;
-            if (yj < 1 || yj > g.NY - 2 || yi < 1 || yi > g.NX - 2) continue;
-            const long long Y = (long long)yj * g.NX + yi;
+            for (int f = 0; f < 3; ++f)
+                if (t < PL) v[f][q] = S[(3 * wv + f) * N + (long long)gj * g.NX + gi];
+        }
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[c] += UC[(s * 4 + c) * N + Y];
-            if (s & 1) {
-                const int e = s >> 1;
+        for (int q = 0; q < NP; ++q)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    acc[4 + c] += UC[((9 + e) * 4 + c) * N + Y];
-                    acc[8 + c] += UC[((13 + e) * 4 + c) * N + Y];
-                }
+            for (int f = 0; f < 3; ++f)
+                if (lane + 64 * q < PL) tile[(3 * wv + f) * PL + lane + 64 * q] = v[f][q];
+    }
+    for (int t = threadIdx.x; t < 12 * PL; t += 256) sums[t] = 0.0;
+    __syncthreads();
+    const int tc = (ly + 1) * AT_W + lx + 1;
+    const double* T0 = tile + tc;
+    const double rbar_ = T0[0];
+    const double pbar = pressure2(K, rbar_, T0[PL], T0[2 * PL], T0[3 * PL]);
+    const double mn = T0[(1 + b) * PL], mt = T0[(2 - b) * PL], Et = T0[3 * PL];
+    const Basis2 e = basis2(K, rbar_, mn, mt, Et);
+    // ---- forward: this wavefront's fields at its own points (last slot of
+    // h = 0: 6 face values, then the moment), the rest to the partner ----
+    double va[9], vb[9];
+#pragma unroll 1
+    for (int kk = 0; kk < 2; ++kk) {
+        const int k = hh == 0 ? 3 * kk : 1 + kk;
+        double C[15];
+        {
+            double L[4], R[4], a[17];
+            field_rows(e, k, L, R);
+            if (b == 0) project2<0, AT_W, PL>(T0, L, a);
+            else project2<1, AT_W, PL>(T0, L, a);
+            hweno2d(a, K, C);
+        }
+        double* X = sh + kk * XB + b * (XB / 2) + lane;
+        double f[7], w[9];
+        eval_xface(C, f);
+        f[6] = moment_xi(C);
+        eval_vol(C, w);
+        if (hh == 0) {
+#pragma unroll
+            for (int q = 0; q < 9; ++q) X[q * 64] = w[q];
+#pragma unroll
+            for (int q = 0; q < 7; ++q) {
+                va[q] = vb[q];
+                vb[q] = f[q];
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 7; ++q) X[(9 + q) * 64] = f[q];
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                va[q] = vb[q];
+                vb[q] = w[q];
             }
         }
     }
+    __syncthreads();
+    double* XP = sh + b * (XB / 2) + lane;   // partner's values at own points: + kk * XB
+    // the fields' values x and the conserved components u (basis order) at own
+    // point o (h = 0: face points, then the moment; h = 1: volume points)
+    auto point = [&](auto H, int o, double* x, double* u) {
+#pragma clang fp contract(off)   // the same bits wherever it is formed
+        if constexpr (H.value == 0) {
+            x[0] = va[o];
+            x[1] = XP[(9 + o) * 64];
+            x[2] = XP[XB + (9 + o) * 64];
+            x[3] = vb[o];
+        } else {
+            x[0] = XP[o * 64];
+            x[1] = va[o];
+            x[2] = vb[o];
+            x[3] = XP[XB + o * 64];
+        }
+        const double sm = x[0] + x[3], df = x[3] - x[0];
+        u[0] = sm + x[1];
+        u[1] = fma(e.un, u[0], e.c * df);
+        u[2] = fma(e.ut, u[0], x[2]);
+        u[3] = fma(e.H, sm, fma(e.un * e.c, df, fma(0.5 * e.q2, x[1], e.ut * x[2])));
+    };
+    const int gc[4] = {0, 1 + b, 2 - b, 3};   // global number of a basis component
+    auto gq = [&](int q) { return b ? 3 * (q % 3) + q / 3 : q; };
+    // own point o in the order of the oracle's minima (ties go to the first)
+    auto pidx = [&](auto H, int o) { return H.value == 0 ? b * 6 + o : 12 + b * 9 + gq(o); };
+    const Part<0> face{};
+    const Part<1> vol{};
+    // ---- limiter forward: least density and pressure ----
+    double th1 = 1.0, th2 = 1.0;
+    double rmin = INFINITY, pmin = INFINITY;
+    auto minima = [&](auto H) {
 #pragma unroll
-    for (int q = 0; q < 12; ++q) W.ubb[q * N + t] = acc[q];
+        for (int o = 0; o < H.points; ++o) {
+            double x[4], u[4];
+            point(H, o, x, u);
+            rmin = fmin(rmin, u[0]);
+            pmin = fmin(pmin, pressure2(K, u[0], u[1], u[2], u[3]));
+        }
+    };
+    if (hh == 0) minima(face);
+    else minima(vol);
+    auto least = [&](int q) {
+        return fmin(fmin(shm[q][0][lane], shm[q][1][lane]), fmin(shm[q][2][lane], shm[q][3][lane]));
+    };
+    shm[0][wv][lane] = rmin;
+    shm[1][wv][lane] = pmin;
+    __syncthreads();
+    rmin = least(0);
+    pmin = least(1);
+    const double e1 = K.eps_pp <= rbar_ ? K.eps_pp : rbar_;
+    const int esrc1 = K.eps_pp <= rbar_ ? 0 : 1;
+    const double eps = e1 <= pbar ? e1 : pbar;
+    const int esrc = e1 <= pbar ? esrc1 : 2;
+    const bool low1 = rmin < eps;
+    // ---- cotangents of the point values.  Loads are unconditional (a lane
+    // outside the region reads cell (1, 1)) and what does not count is dropped ----
+    const bool inter = valid && interior(g, j, i);
+    const bool ring2 = valid && in_ring2(g, j, i);
+    const double ih = b == 0 ? K.idx : K.idy;
+    // weak-moment adjoint of variable w, moment mom of the cell or a neighbour
+    auto RB = [&](int w, int mom, int off, bool in) {
+        const double x = W.rbb[((b * 3 + w) * 3 + mom) * N + cell + off];
+        return in ? x : 0.0;
+    };
+    // cotangents of (u_n, u_t, e): h = 0: of the lower (0) and upper face's
+    // average and first moment; h = 1: of the cell average wbar
+    double wa0[2][3], wa1[2][3];
+#pragma unroll
+    for (int z = 0; z < 3; ++z) {
+        const int w = z == 2 ? 2 : (z == 0 ? b : 1 - b);
+        const double ownm = RB(w, 1 + b, 0, ring2);   // the (W0+ + W0-) / 2 moment
+        if (hh == 0) {
+            const double own0 = RB(w, 0, 0, ring2);
+            const double own1 = RB(w, 2 - b, 0, ring2);   // the transverse moment
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) {
+                const int s = 2 * hi - 1;
+                const int off = b ? s * g.NX : s;
+                const bool in = valid && in_ring2(g, b ? j + s : j, b ? i : i + s);
+                const double nb0 = RB(w, 0, off, in), nbm = RB(w, 1 + b, off, in);
+                const double nb1 = RB(w, 2 - b, off, in);
+                wa0[hi][z] = 0.5 * ((s * (own0 - nb0) + 0.5 * (ownm + nbm)) * ih);
+                wa1[hi][z] = 0.5 * (s * (own1 - nb1) * ih);
+            }
+        } else {
+            wa0[0][z] = -ownm * ih;
+        }
+    }
+    const double* PB = hh == 0 ? (b == 0 ? W.xfb : W.yfb) : (b == 0 ? W.xvb : W.yvb);
+    const bool facelo = valid && flux_face(g, j, i, 2 * b), facehi = valid && flux_face(g, j, i, 2 * b + 1);
+    // cotangent of the (limited) value ul at own point o
+    auto cot = [&](auto H, int o, const double* ul, double* yb) {
+        double wb[3];
+        if constexpr (H.value == 0) {
+            const int hi = o / 3, G = o % 3;
+            const bool add = hi ? facehi : facelo;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double x = PB[(o * 4 + gc[c]) * N + cell];
+                yb[c] = add ? x : 0.0;
+            }
+#pragma unroll
+            for (int z = 0; z < 3; ++z) wb[z] = gw(G) * (wa0[hi][z] + gx(G) * wa1[hi][z]);
+            adj::prim2_vjp(ul, wb, yb);
+        } else {
+            double z4[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int z = 0; z < 3; ++z) wb[z] = gw(o / 3) * gw(o % 3) * wa0[0][z];
+            adj::prim2_vjp(ul, wb, z4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double x = PB[(gq(o) * 4 + gc[c]) * N + cell];
+                yb[c] = (ring2 ? z4[c] : 0.0) + (inter ? x : 0.0);
+            }
+        }
+    };
+    // limited face value ul (u1: at the limited density) from the unlimited u
+    const double ub[4] = {rbar_, mn, mt, Et};
+    bool acted = false;
+    auto limit = [&](const double* u, double* u1, double* ul) {
+        u1[0] = acted ? rbar_ + th1 * (u[0] - rbar_) : u[0];
+#pragma unroll
+        for (int c = 1; c < 4; ++c) u1[c] = u[c];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) ul[c] = acted ? ub[c] + th2 * (u1[c] - ub[c]) : u[c];
+    };
+    // where the limiter acts, the adjoints of its thetas go to the cell average
+    // and to the points that set them (id1: density, id2: pressure); every
+    // wavefront holds the same cells and minima, so the whole block takes the
+    // branch or none of it
+    double P1b = 0.0, P2b[4] = {0.0, 0.0, 0.0, 0.0};
+    int id1 = -1, id2 = -1;
+    double ctr[4] = {0.0, 0.0, 0.0, 0.0};     // cell-average adjoint (basis order)
+    const bool rare = __ballot(valid && (low1 || pmin < eps)) != 0;
+    if (rare) {
+        if (low1) th1 = (rbar_ - eps) / (rbar_ - rmin);
+        auto lower = [](double v, int id, double& m, int& im) {
+            if (v < m || (v == m && id < im)) {
+                m = v;
+                im = id;
+            }
+        };
+        double m1 = INFINITY, m2 = INFINITY;   // density; pressure at the limited densities
+        int n1 = 1 << 30, n2 = 1 << 30;
+        auto where = [&](auto H) {
+#pragma unroll
+            for (int o = 0; o < H.points; ++o) {
+                double x[4], u[4];
+                point(H, o, x, u);
+                lower(u[0], pidx(H, o), m1, n1);
+                lower(pressure2(K, low1 ? rbar_ + th1 * (u[0] - rbar_) : u[0], u[1], u[2], u[3]),
+                      pidx(H, o), m2, n2);
+            }
+        };
+        if (hh == 0) where(face);
+        else where(vol);
+        __syncthreads();                       // the minima have been read
+        shm[0][wv][lane] = m1;
+        shm[1][wv][lane] = m2;
+        shi[0][wv][lane] = n1;
+        shi[1][wv][lane] = n2;
+        __syncthreads();
+        int irmin = 1 << 30, ipmin = 1 << 30;
+        rmin = pmin = INFINITY;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            lower(shm[0][w][lane], shi[0][w][lane], rmin, irmin);
+            lower(shm[1][w][lane], shi[1][w][lane], pmin, ipmin);
+        }
+        const bool low2 = pmin < eps && (pbar - eps) / (pbar - pmin) < 1.0;
+        if (low2) th2 = (pbar - eps) / (pbar - pmin);
+        acted = low1 || low2;
+        double t1 = 0.0, t2 = 0.0;
+        auto thetas = [&](auto H) {
+#pragma unroll
+            for (int o = 0; o < H.points; ++o) {
+                double x[4], u[4];
+                point(H, o, x, u);
+                if constexpr (H.value == 0) {
+                    double u1[4], ul[4], yb[4];
+                    limit(u, u1, ul);
+                    cot(H, o, ul, yb);
+                    t1 += th2 * yb[0] * (u[0] - rbar_);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) t2 += yb[c] * (u1[c] - ub[c]);
+                }
+                if (low2 && pidx(H, o) == ipmin) {   // in global order
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) shl[gc[c]][lane] = u[c];
+                }
+            }
+        };
+        if (hh == 0) thetas(face);
+        else thetas(vol);
+        __syncthreads();
+        if (hh == 0) {
+            shm[0][b][lane] = t1;
+            shm[0][2 + b][lane] = t2;
+        }
+        __syncthreads();
+        double T1b = shm[0][0][lane] + shm[0][1][lane];
+        const double T2b = shm[0][2][lane] + shm[0][3][lane];
+        double rb_ = 0.0, pb_ = 0.0, epsb = 0.0;
+        if (low2) {
+            const double rho = shl[0][lane];
+            const double Ut[4] = {rbar_ + th1 * (rho - rbar_), shl[1][lane], shl[2][lane],
+                                  shl[3][lane]};
+            const double den = pbar - pmin;
+            pb_ += T2b * (eps - pmin) / (den * den);
+            epsb += -T2b / den;
+            double Utb[4] = {0.0, 0.0, 0.0, 0.0};
+            adj::pres2_vjp(K, Ut, T2b * (pbar - eps) / (den * den), Utb);
+            rb_ += Utb[0] * (1.0 - th1);
+            P2b[0] = Utb[0] * th1;
+            P2b[1] = b ? Utb[2] : Utb[1];
+            P2b[2] = b ? Utb[1] : Utb[2];
+            P2b[3] = Utb[3];
+            T1b += Utb[0] * (rho - rbar_);
+            id2 = ipmin;
+        }
+        if (low1) {
+            const double den = rbar_ - rmin;
+            rb_ += T1b * (eps - rmin) / (den * den);
+            epsb += -T1b / den;
+            P1b = T1b * (rbar_ - eps) / (den * den);
+            id1 = irmin;
+        }
+        if (esrc == 1) rb_ += epsb;
+        if (esrc == 2) pb_ += epsb;
+        if (wv == 0) {
+            ctr[0] = rb_;
+            if (pb_ != 0.0) adj::pres2_vjp(K, ub, pb_, ctr);
+        }
+    }
+    // ---- point cotangents to field cotangents: own two kept, the partner's two
+    // in place of its values; sums for the eigenvectors' adjoint ----
+    double a1 = 0.0, a2 = 0.0, a3 = 0.0, a4 = 0.0, a5 = 0.0, a6 = 0.0;
+    auto back = [&](auto H, auto Rare) {
+#pragma unroll
+        for (int o = 0; o < H.slots; ++o) {
+            double x[4], u[4], y[4];
+            point(H, o, x, u);
+            if (o == H.points) {     // the own-cell moment
+                const long long nint = (long long)g.nx * g.ny;
+                const long long t = inter ? (long long)(j - HALO) * g.nx + (i - HALO) : 0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const double s = A.Vb ? A.vs * A.Vb[(b * 4 + gc[c]) * nint + t] : 0.0;
+                    y[c] = inter ? s : 0.0;
+                }
+            } else if constexpr (Rare.value == 0) {
+                cot(H, o, u, y);
+            } else {
+                double u1[4], ul[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) ul[c] = u[c];
+                if constexpr (H.value == 0) limit(u, u1, ul);
+                cot(H, o, ul, y);
+                if constexpr (H.value == 0) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const double th = c == 0 ? th2 * th1 : th2;
+                        ctr[c] += acted ? y[c] * (1.0 - th) : 0.0;
+                        y[c] = acted ? y[c] * th : y[c];
+                    }
+                }
+                if (pidx(H, o) == id1) y[0] += P1b;
+                if (pidx(H, o) == id2)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) y[c] += P2b[c];
+            }
+            const double sm = x[0] + x[3], df = x[3] - x[0], al = sm + x[1];
+            a1 += y[1] * al;
+            a2 += y[2] * al + y[3] * x[2];
+            a3 += y[1] * df;
+            a4 += y[3] * df;
+            a5 += y[3] * sm;
+            a6 += y[3] * x[1];
+            const double s0 = y[0] + e.un * y[1] + e.ut * y[2];
+            const double sa = s0 + e.H * y[3], sd = e.c * (y[1] + e.un * y[3]);
+            const double z1 = s0 + 0.5 * e.q2 * y[3], z2 = y[2] + e.ut * y[3];
+            if constexpr (H.value == 0) {
+                va[o] = sa - sd;
+                vb[o] = sa + sd;
+                XP[(9 + o) * 64] = z1;
+                XP[XB + (9 + o) * 64] = z2;
+            } else {
+                va[o] = z1;
+                vb[o] = z2;
+                XP[o * 64] = sa - sd;
+                XP[XB + o * 64] = sa + sd;
+            }
+        }
+    };
+    if (rare) {
+        if (hh == 0) back(face, Part<1>{});
+        else back(vol, Part<1>{});
+    } else {
+        if (hh == 0) back(face, Part<0>{});
+        else back(vol, Part<0>{});
+    }
+    __syncthreads();
+    // ---- scalar reconstruction, projection row and eigenvector adjoints ----
+    double unb = a1 + e.c * a4, utb = a2, cb = a3 + e.un * a4, q2b = 0.5 * a6;
+    double b1b = 0.0, b2b = 0.0, icb = 0.0;
+    double* A0 = sums + tc;
+    auto component = [&](int G) { return b == 1 && (G == 1 || G == 2) ? 3 - G : G; };
+    auto sel = [](int c, const double* v) {
+        return c == 0 ? v[0] : (c == 1 ? v[1] : (c == 2 ? v[2] : v[3]));
+    };
+#pragma unroll 1
+    for (int kk = 0; kk < 2; ++kk) {
+        const int k = hh == 0 ? 3 * kk : 1 + kk;
+        double Cb[15];
+#pragma unroll
+        for (int q = 0; q < 15; ++q) Cb[q] = 0.0;
+        {
+            const double* X = XP + kk * XB;
+            double y[16];
+            if (hh == 0) {
+#pragma unroll
+                for (int q = 0; q < 7; ++q) y[q < 6 ? q : 15] = kk ? vb[q] : va[q];
+#pragma unroll
+                for (int q = 0; q < 9; ++q) y[6 + q] = X[q * 64];
+            } else {
+#pragma unroll
+                for (int q = 0; q < 7; ++q) y[q < 6 ? q : 15] = X[(9 + q) * 64];
+#pragma unroll
+                for (int q = 0; q < 9; ++q) y[6 + q] = kk ? vb[q] : va[q];
+            }
+            adj::xface_T(y, Cb);
+            adj::vol_T(y + 6, Cb);
+            moment_xi_T(y[15], Cb);
+        }
+        double L[4], R[4], a[17], ab[17], Lb[4];
+        field_rows(e, k, L, R);
+        if (b == 0) project2<0, AT_W, PL>(T0, L, a);
+        else project2<1, AT_W, PL>(T0, L, a);
+        hweno2d_vjp(a, K, Cb, ab);
+        if (b == 0) project2_rowbar<0>(T0, ab, Lb);
+        else project2_rowbar<1>(T0, ab, Lb);
+        if (k == 1) {
+            b2b -= Lb[0];
+            b1b += e.un * Lb[1] + e.ut * Lb[2] - Lb[3];
+            unb += e.b1 * Lb[1];
+            utb += e.b1 * Lb[2];
+        } else if (k == 2) {
+            utb -= Lb[0];
+        } else {
+            const double sg = k == 0 ? -1.0 : 1.0, si = sg * e.ic;
+            b2b += 0.5 * Lb[0];
+            unb -= 0.5 * (si * Lb[0] + e.b1 * Lb[1]);
+            icb += 0.5 * sg * (Lb[1] - e.un * Lb[0]);
+            b1b += 0.5 * (Lb[3] - e.un * Lb[1] - e.ut * Lb[2]);
+            utb -= 0.5 * e.b1 * Lb[2];
+        }
+#pragma unroll 1
+        for (int ph = 0; ph < 4; ++ph) {
+            const int G = (wv + ph) & 3;
+            const double l = sel(component(G), L);
+            if (valid) {
+                if (b == 0) scatter2<0>(A0, G, l, ab);
+                else scatter2<1>(A0, G, l, ab);
+            }
+            __syncthreads();
+        }
+    }
+    {
+        // back through basis2
+        const double ir = rcp(rbar_), p = K.gm1 * (Et - 0.5 * rbar_ * e.q2);
+        b1b += 0.5 * e.q2 * b2b;
+        q2b += 0.5 * e.b1 * b2b;
+        icb += 2.0 * K.gm1 * e.ic * b1b;
+        cb -= e.ic * e.ic * icb;
+        const double c2b = 0.5 * e.ic * cb;
+        const double pb = ir * a5 + K.gamma * ir * c2b;
+        double irb = (Et + p) * a5 + K.gamma * p * c2b;
+        q2b -= 0.5 * K.gm1 * rbar_ * pb;
+        unb += 2.0 * e.un * q2b;
+        utb += 2.0 * e.ut * q2b;
+        irb += mn * unb + mt * utb;
+        ctr[0] -= 0.5 * K.gm1 * e.q2 * pb + ir * ir * irb;
+        ctr[1] += ir * unb;
+        ctr[2] += ir * utb;
+        ctr[3] += ir * a5 + K.gm1 * pb;
+    }
+#pragma unroll 1
+    for (int ph = 0; ph < 4; ++ph) {
+        const int G = (wv + ph) & 3;
+        if (valid) lds_add(A0 + G * PL, sel(component(G), ctr));
+        __syncthreads();
+    }
+    double* out = W.uc + (long long)lb * (12 * PL);
+    for (int t = threadIdx.x; t < 12 * PL; t += 256) out[t] = sums[t];
 }
+
+// State adjoint of ghosted cell (j, i), component q: the sums of the tiles that
+// hold the cell (each tile its ring of one cell too), in a fixed order.
+__device__ __forceinline__ double state_bar(const Grid2& g, const AdjWs& W, int q, int j, int i) {
+    const int ntx = at_tiles_x(g), nty = at_tiles_y(g);
+    const int t1 = j / AT_Y, x1 = i / AT_X, xr = i % AT_X;
+    double v = 0.0;
+#pragma unroll
+    for (int d = 1; d >= 0; --d) {
+        const int ty = t1 - d;
+        if (ty < 0 || ty >= nty) continue;
+        const double* R = W.uc + ((long long)ty * ntx * 12 + q) * AT_P + (j % AT_Y + AT_Y * d) * AT_W;
+        auto T = [&](int tx) { return R[(long long)tx * (12 * AT_P) + i - tx * AT_X + 1]; };
+        if (xr == 0 && x1 > 0) v += T(x1 - 1);
+        if (x1 < ntx) v += T(x1);
+        if (xr == AT_X - 1 && x1 + 1 < ntx) v += T(x1 + 1);
+    }
+    return v;
+}
+static_assert(AT_Y == 2, "state_bar: a row lies in two tiles");
 
 // ---------------------------------------------------------------------------
 // Adjoint of the ghost fill: the y sweep is undone first (its sources include
 // the x-ghost columns), then the x sweep.  Each source cell gathers the
 // ghost cells copied from it, in a fixed order.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int ghost_src(int kind, int side, int d, int n) {
-    if (kind == 2) return -1;                 // inflow: constant
-    if (side == 0) return kind == 0 ? HALO + n - d : (kind == 1 ? HALO : HALO + d - 1);
-    return kind == 0 ? HALO + d - 1 : (kind == 1 ? HALO + n - 1 : HALO + n - d);
+// The ghost rows (columns) of one side that copy interior row r of n: first one
+// and count (outflow copies the boundary row to all of them, the other kinds map
+// one to one as n >= HALO).
+__device__ __forceinline__ int ghosts_of(int kind, int side, int r, int n, int* count) {
+    const int first = side ? HALO + n : 0;          // the side's ghost rows: HALO from here
+    if (kind == 1) {
+        *count = r == (side ? HALO + n - 1 : HALO) ? HALO : 0;
+        return first;
+    }
+    const int gj = kind == 0 ? (side ? r + n : r - n)
+                             : (side ? 2 * (HALO + n) - 1 - r : 2 * HALO - 1 - r);
+    *count = kind != 2 && gj >= first && gj < first + HALO ? 1 : 0;   // inflow: constant
+    return gj;
 }
 
 // Component q of the adjoint at cell (r, i) of an interior row once the y
 // sweep is undone: its own value plus the ghost rows copied from it.
 __device__ __forceinline__ double ghost_y_gather(const Grid2& g, const AdjWs& W, int q, int r,
                                                  int i) {
-    const long long N = g.ncell;
-    double v = W.ubb[q * N + (long long)r * g.NX + i];
+    double v = state_bar(g, W, q, r, i);
+    if (r >= 2 * HALO && r < g.ny) return v;
     for (int side = 0; side < 2; ++side) {
         const Side& sd = g.side[2 + side];
-        for (int d = 1; d <= HALO; ++d) {
-            if (ghost_src(sd.kind, side, d, g.ny) != r) continue;
-            const int gj = side == 0 ? HALO - d : HALO + g.ny - 1 + d;
-            v += sd.sign[q] * W.ubb[q * N + (long long)gj * g.NX + i];
-        }
+        int n;
+        const int gj = ghosts_of(sd.kind, side, r, g.ny, &n);
+        for (int d = 0; d < n; ++d) v += sd.sign[q] * state_bar(g, W, q, gj + d, i);
     }
     return v;
 }
@@ -942,36 +997,27 @@ __device__ __forceinline__ double ghost_y_gather(const Grid2& g, const AdjWs& W,
 // caller's interior array: the y sweep's gather at the cell, then the x
 // ghost columns copied from it, each with its own y sweep's gather (the
 // corner ghost cells reach the interior through the x-ghost columns).
-__global__ void k_adj_ghost_out(Grid2 g, AdjWs W, double* __restrict__ Ubar,
-                                const double* __restrict__ add, double add_a,
-                                const double* __restrict__ pass) {
-    const long long nint = (long long)g.nx * g.ny;
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nint * 12) return;
-    const int q = (int)(t / nint);
-    const long long r = t % nint;
-    const int j = HALO + (int)(r / g.nx), c0 = HALO + (int)(r % g.nx);
+// Component q is the grid's second index.
+__global__ void k_adj_out(Grid2 g, AdjWs W, double* __restrict__ Ubar,
+                          const double* __restrict__ add, double add_a,
+                          const double* __restrict__ pass) {
+    const unsigned nint = (unsigned)g.nx * (unsigned)g.ny;
+    const unsigned r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= nint) return;
+    const int q = (int)blockIdx.y;
+    const long long t = (long long)q * nint + r;
+    const int j = HALO + (int)(r / (unsigned)g.nx), c0 = HALO + (int)(r % (unsigned)g.nx);
     // a stage's direct term: fluid cells (averages) or, on a masked grid,
     // solid cells (every component: a stage leaves them at its filled input)
     const bool sol = solid_cell(g, r);
-    // every ghost cell copies one of the HALO cells next to a side
-    if (c0 >= 2 * HALO && c0 < g.nx && j >= 2 * HALO && j < g.ny) {
-        double v = W.ubb[q * g.ncell + (long long)j * g.NX + c0];
-        if (sol) {
-            if (pass) v += pass[t];
-        } else if (add && q < 4) {
-            v += add_a * add[t];
-        }
-        Ubar[t] = v;
-        return;
-    }
     double v = ghost_y_gather(g, W, q, j, c0);
-    for (int side = 0; side < 2; ++side) {
-        const Side& sd = g.side[side];
-        for (int d = 1; d <= HALO; ++d) {
-            if (ghost_src(sd.kind, side, d, g.nx) != c0) continue;
-            const int gi = side == 0 ? HALO - d : HALO + g.nx - 1 + d;
-            v += sd.sign[q] * ghost_y_gather(g, W, q, j, gi);
+    // every ghost cell copies one of the HALO cells next to a side
+    if (c0 < 2 * HALO || c0 >= g.nx) {
+        for (int side = 0; side < 2; ++side) {
+            const Side& sd = g.side[side];
+            int n;
+            const int gi = ghosts_of(sd.kind, side, c0, g.nx, &n);
+            for (int d = 0; d < n; ++d) v += sd.sign[q] * ghost_y_gather(g, W, q, j, gi + d);
         }
     }
     if (sol) {
@@ -1073,6 +1119,10 @@ inline unsigned nb2(long long n, int bs) { return (unsigned)((n + bs - 1) / bs);
 
 }  // namespace
 
+size_t adj_tile_doubles2(const Grid2& g) {
+    return (size_t)at_tiles_x(g) * at_tiles_y(g) * (12 * AT_P);
+}
+
 long long adj_mu_partials2(const Grid2& g) {
     return (long long)nb2((long long)(g.nx + 1) * g.ny, AF) + nb2((long long)g.nx * (g.ny + 1), AF) +
            nb2((long long)(g.NX - 6) * (g.NY - 6), AG);
@@ -1087,8 +1137,8 @@ hipError_t launch_vjp2(const Grid2& g, const AdjIn& A0, AdjWs W, const double* S
     W.mu_off1 = bx;
     W.mu_off2 = bx + by;
     // the reconstruction adjoint walks its blocks last first, opposite to the
-    // weak-moment adjoint before it (1.5 % of a step adjoint on 256^2; the
-    // other kernels showed no gain)
+    // kernels before it (1.5 % of a step adjoint on 256^2; the other kernels
+    // showed no gain)
     W.rev = 1u << 5;
     AdjIn A = A0;
     if (g.solid) {   // masked grid: the solid cells' seeds zeroed once, for every kernel
@@ -1105,14 +1155,11 @@ hipError_t launch_vjp2(const Grid2& g, const AdjIn& A0, AdjWs W, const double* S
         k_adj_flux<1, false><<<by, 3 * AF, 0, st>>>(g, A, W);
         k_adj_grad<false><<<bg, 6 * AG, 0, st>>>(g, A, W);
     }
-    k_adj_rgather<<<nb2((long long)(g.NX - 4) * (g.NY - 4), 256), 256, 0, st>>>(g, W);
-    k_adj_wmom<<<nb2((long long)(g.NX - 2) * (g.NY - 2), WM_CELLS), 6 * WM_CELLS, 0, st>>>(g, W);
-    const unsigned brec = nb2((long long)(g.NX - 2) * (g.NY - 2), AC);
-    k_adj_recon_a<<<brec, 8 * AC, 0, st>>>(g, A, W, S);
-    k_adj_recon_b<<<brec, 8 * AC, 0, st>>>(g, W, S);
-    k_adj_ugather<<<nb2(g.ncell, 256), 256, 0, st>>>(g, W);
-    k_adj_ghost_out<<<nb2((long long)g.nx * g.ny * 12, 256), 256, 0, st>>>(g, W, Ubar, add, add_a,
-                                                                            pass);
+    const dim3 br(nb2((long long)(g.NX - 4) * (g.NY - 4), 256), 6);
+    k_adj_rgather<<<br, 256, 0, st>>>(g, W);
+    k_adj_recon<<<(unsigned)(at_tiles_x(g) * at_tiles_y(g)), 256, 0, st>>>(g, A, W, S);
+    const dim3 bo(nb2((long long)g.nx * g.ny, 256), 12);
+    k_adj_out<<<bo, 256, 0, st>>>(g, W, Ubar, add, add_a, pass);
     if (g.nsolid > 0) {   // masked grid: the mirror fill, undone
         if (W.nsrc > 0)
             k_adj_solid_gather<<<nb2((long long)W.nsrc * 12, 256), 256, 0, st>>>(g, W, Ubar);

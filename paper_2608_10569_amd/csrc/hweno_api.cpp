@@ -297,11 +297,7 @@ size_t layout(hweno_ctx* c, char* base) {
         A.gfb = take(72 * m);
         A.rbc = take(102 * m);
         A.rbb = take(18 * m);
-        A.uc = take(136 * m);
-        A.rcb = take(128 * m);
-        A.rrb = take(32 * m);
-        A.rlim = take(4 * m);
-        A.ubb = take(12 * m);
+        A.uc = take(hw::adj_tile_doubles2(c->hg[0]));
         A.mupart = take((size_t)hw::adj_mu_partials2(c->hg[0]));
         c->mu_dev = take(1);
         const size_t nint = (size_t)c->hg[0].nx * c->hg[0].ny;

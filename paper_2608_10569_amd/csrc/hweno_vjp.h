@@ -22,11 +22,8 @@ struct AdjWs {
     double* gfb;        // 72 / 8: face-gradient adjoints
     double* rbc;        // 102 / 10: weak-moment contributions to the 3x3 stencil
     double* rbb;        // 18 / 4: gathered weak-moment adjoints
-    double* uc;         // 136 / 15: state contributions to the stencil
-    double* rcb;        // 128: cotangents of the 16 characteristic outputs per (b, k)
-    double* rrb;        // 32: R-bar rows per (b, k)
-    double* rlim;       // 4: the limiter's share of the cell-average adjoint
-    double* ubb;        // 12 / 6: gathered state adjoint (ghosted)
+    double* uc;         // sums of the state adjoint per tile of cells and its ring
+                        // (adj_tile_doubles2)
     double* mupart;     // block partials of the mu adjoint
     double* rbm;        // 12 / cell (interior): a masked grid's residual seed, solid cells zeroed
     double* vbm;        // 8 / cell (interior): its modified-moment seed likewise
@@ -162,6 +159,7 @@ hipError_t launch_vjp1(const Grid1& g, const AdjIn& A, AdjWs1 W, const double* S
                        double* mu_out, int mu_acc, hipStream_t st);
 
 long long adj_mu_partials2(const Grid2& g);
+size_t adj_tile_doubles2(const Grid2& g);
 // mu_acc = 0: *mu_out = mu-bar; 1: *mu_out += mu-bar (device scalar).
 // add != nullptr: add_a * add[t] joins the cell-average adjoints (the first
 // 4 nx ny entries of Ubar) of the fluid cells, as an axpy after the call would.
