@@ -10,7 +10,7 @@
 // Branches (limiter thetas, LF-speed maximum, |.| in the weights) follow the
 // forward point; ties go to the lowest index in the order of the oracle.
 //
-//   k_adj_flux<d>  face-flux adjoint (eq. (3.3)) -> trace / face-gradient adjoints
+//   k_adj_flux     face-flux adjoint (eq. (3.3)) -> trace / face-gradient adjoints
 //   k_adj_grad     volume-flux + gradient-reconstruction adjoint (eq. (3.9))
 //   k_adj_rgather  gather of the weak-moment adjoints from the 3x3 stencils
 //   k_adj_recon    weak-moment adjoint (eqs. (3.6)-(3.8)), limiter, back-transform,
@@ -64,7 +64,7 @@ __device__ __forceinline__ double rbar(const AdjIn& A, const Grid2& g, int m, in
 
 // Logical index of this block: XCD-aware (each XCD takes a contiguous range
 // of the launch, so neighbouring rows of a stencil share an L2), last first
-// where bit k of W.rev is set (k: 0, 1 face fluxes x, y; 2 gradients; 3
+// where bit k of W.rev is set (k: 0 face fluxes; 2 gradients; 3
 // weak-moment gather; 5 reconstruction).
 // The mu partials are stored by it, so their fixed summation order is
 // unchanged.
@@ -93,20 +93,23 @@ __device__ __forceinline__ void mu_partial(double v, double* part, int lb) {
 // ---------------------------------------------------------------------------
 // Face fluxes: fhat = 1/2 (f(u-,s-) + f(u+,s+) - beta (u+ - u-)), beta the
 // max over the face's 3 Gauss points x 2 sides of max(|u_n| + c, beta_PP).
-// Block: 3 Gauss points x 64 faces.
+// Block: 64 faces, a wavefront per side and Gauss point; the x-faces' blocks
+// (W.mu_off1 of them), then the y-faces', in one launch.  With both sides in a
+// thread (204 registers, two wavefronts per SIMD) and a launch per direction the
+// two took 54 us on 256 x 256; now 48.
 // ---------------------------------------------------------------------------
 constexpr int AF = 64;
 
 template <int d, bool VarMu>
-__global__ __launch_bounds__(3 * AF) void k_adj_flux(Grid2 g, AdjIn A, AdjWs W) {
-    __shared__ double shs[2][3 * AF];     // speeds of the two sides
-    __shared__ double shb[3 * AF];        // beta-bar partial sums
+__device__ __forceinline__ void adj_flux_body(const Grid2& g, const AdjIn& A, const AdjWs& W, int lb,
+                                              double (*shs)[AF], double (*shu)[4][AF],
+                                              double (*shb)[AF]) {
     const Consts& K = g.K;
     const int nfi = d == 0 ? g.nx + 1 : g.nx;
     const int nfj = d == 0 ? g.ny : g.ny + 1;
-    const int G = threadIdx.x / AF;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / AF);
+    const int side = wv / 3, G = wv % 3;         // side 0: minus, 1: plus
     const int fl = threadIdx.x % AF;
-    const int lb = lblock(W, d);
     const long long t = (long long)lb * AF + fl;
     const bool valid = t < (long long)nfi * nfj;
     const long long N = g.ncell;
@@ -117,24 +120,16 @@ __global__ __launch_bounds__(3 * AF) void k_adj_flux(Grid2 g, AdjIn A, AdjWs W) 
         i = d == 0 ? HALO - 1 + fi : HALO + fi;
     }
     const long long cm = (long long)j * g.NX + i;
-    const long long cp = d == 0 ? cm + 1 : cm + g.NX;
     const int jp = d == 0 ? j : j + 1, ip = d == 0 ? i + 1 : i;
+    const long long co = side ? (d == 0 ? cm + 1 : cm + g.NX) : cm;   // this side's cell
+    const int po = side ? G : 3 + G;                                  // its face point
     const double* F = d == 0 ? g.xf : g.yf;
     const int pg = d == 0 ? 0 : 6;
-    double Um[4], Up[4], sm[6], sp[6];
+    double U[4], s[6];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        Um[c] = F[((3 + G) * 4 + c) * N + cm];
-        Up[c] = F[(G * 4 + c) * N + cp];
-    }
+    for (int c = 0; c < 4; ++c) U[c] = F[(po * 4 + c) * N + co];
 #pragma unroll
-    for (int z = 0; z < 6; ++z) {
-        sm[z] = g.gf[((pg + 3 + G) * 6 + z) * N + cm];
-        sp[z] = g.gf[((pg + G) * 6 + z) * N + cp];
-    }
-    const double spm = speed2<d>(K, Um, sm), spp = speed2<d>(K, Up, sp);
-    shs[0][threadIdx.x] = valid ? spm : -INFINITY;
-    shs[1][threadIdx.x] = valid ? spp : -INFINITY;
+    for (int z = 0; z < 6; ++z) s[z] = g.gf[((pg + po) * 6 + z) * N + co];
     // adjoint of fhat at this Gauss point from the two adjacent residuals
     double fb[4] = {0.0, 0.0, 0.0, 0.0};
     if (valid) {
@@ -157,67 +152,64 @@ __global__ __launch_bounds__(3 * AF) void k_adj_flux(Grid2 g, AdjIn A, AdjWs W) 
             fb[c] = v;
         }
     }
+    const double sp = speed2<d>(K, U, s);
+    shs[wv][fl] = valid ? sp : -INFINITY;
+    if (side) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) shu[G][c][fl] = U[c];
+    }
     __syncthreads();
     // beta and its argmax in the order (minus side G = 0,1,2, plus side G = 0,1,2)
     double beta = -INFINITY;
     int arg = 0;
 #pragma unroll
-    for (int side = 0; side < 2; ++side) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const double v = shs[side][q * AF + fl];
-            if (v > beta) {
-                beta = v;
-                arg = side * 3 + q;
-            }
+    for (int q = 0; q < 6; ++q) {
+        const double v = shs[q][fl];
+        if (v > beta) {
+            beta = v;
+            arg = q;
         }
     }
-    double Umb[4] = {0.0, 0.0, 0.0, 0.0}, Upb[4] = {0.0, 0.0, 0.0, 0.0};
-    double smb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, spb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    double mub = 0.0, betab = 0.0;
-    // the viscosity at the point on each side: mu_ref, or mu(T) of that
-    // side's state, whose adjoint (mbm, mbp) is chained through T below
-    const double mum = VarMu ? point_mu(K, Um) : K.mu_ref;
-    const double mup = VarMu ? point_mu(K, Up) : K.mu_ref;
-    double mubm = 0.0, mubp = 0.0;
-    double& mbm = VarMu ? mubm : mub;
-    double& mbp = VarMu ? mubp : mub;
-    if (valid) {
-        double hf[4];
+    if (side == 0) {
+        double betab = 0.0;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            hf[c] = 0.5 * fb[c];
-            Umb[c] += 0.5 * beta * fb[c];
-            Upb[c] -= 0.5 * beta * fb[c];
-            betab -= 0.5 * fb[c] * (Up[c] - Um[c]);
-        }
-        flux2_vjp<d>(K, Um, sm, mum, hf, Umb, smb, mbm);
-        flux2_vjp<d>(K, Up, sp, mup, hf, Upb, spb, mbp);
+        for (int c = 0; c < 4; ++c) betab -= 0.5 * fb[c] * (shu[G][c][fl] - U[c]);
+        shb[G][fl] = betab;
     }
-    shb[threadIdx.x] = betab;
     __syncthreads();
-    if (valid && arg % 3 == G) {
-        const double bsum = shb[fl] + shb[AF + fl] + shb[2 * AF + fl];
-        if (arg < 3) speed2_vjp<d>(K, Um, sm, mum, bsum, Umb, smb, mbm);
-        else speed2_vjp<d>(K, Up, sp, mup, bsum, Upb, spb, mbp);
-    }
-    if constexpr (VarMu) {
-        if (valid) mub = mubm * mu_T_vjp(K, Um, mubm, Umb) + mubp * mu_T_vjp(K, Up, mubp, Upb);
+    double Ub[4], sb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, hf[4];
+    // the viscosity at the point: mu_ref, or mu(T) of the state, whose adjoint
+    // is chained through T below
+    const double mu = VarMu ? point_mu(K, U) : K.mu_ref;
+    double mub = 0.0;
+    const double hb = side ? -0.5 * beta : 0.5 * beta;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        hf[c] = 0.5 * fb[c];
+        Ub[c] = hb * fb[c];
     }
     if (valid) {
+        flux2_vjp<d>(K, U, s, mu, hf, Ub, sb, mub);
+        if (arg == wv)
+            speed2_vjp<d>(K, U, s, mu, shb[0][fl] + shb[1][fl] + shb[2][fl], Ub, sb, mub);
+        if constexpr (VarMu) mub *= mu_T_vjp(K, U, mub, Ub);
         double* XB = d == 0 ? W.xfb : W.yfb;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            XB[((3 + G) * 4 + c) * N + cm] = Umb[c];
-            XB[(G * 4 + c) * N + cp] = Upb[c];
-        }
+        for (int c = 0; c < 4; ++c) XB[(po * 4 + c) * N + co] = Ub[c];
 #pragma unroll
-        for (int z = 0; z < 6; ++z) {
-            W.gfb[((pg + 3 + G) * 6 + z) * N + cm] = smb[z];
-            W.gfb[((pg + G) * 6 + z) * N + cp] = spb[z];
-        }
+        for (int z = 0; z < 6; ++z) W.gfb[((pg + po) * 6 + z) * N + co] = sb[z];
     }
-    mu_partial<3 * AF>(valid ? mub : 0.0, W.mupart + (d == 0 ? 0 : W.mu_off1), lb);
+    mu_partial<6 * AF>(valid ? mub : 0.0, W.mupart + (d == 0 ? 0 : W.mu_off1), lb);
+}
+
+template <bool VarMu>
+__global__ __launch_bounds__(6 * AF) void k_adj_flux(Grid2 g, AdjIn A, AdjWs W) {
+    __shared__ double shs[6][AF];         // speeds
+    __shared__ double shu[3][4][AF];      // states of the plus side
+    __shared__ double shb[3][AF];         // beta-bar partial sums
+    const int lb = lblock(W, 0);
+    if (lb < W.mu_off1) adj_flux_body<0, VarMu>(g, A, W, lb, shs, shu, shb);
+    else adj_flux_body<1, VarMu>(g, A, W, lb - W.mu_off1, shs, shu, shb);
 }
 
 // ---------------------------------------------------------------------------
@@ -1147,12 +1139,10 @@ hipError_t launch_vjp2(const Grid2& g, const AdjIn& A0, AdjWs W, const double* S
         A.Vb = A0.Vb ? W.vbm : nullptr;
     }
     if (g.K.mu_exp != 0.0) {   // mu(T): the viscosity's dependence on the state too
-        k_adj_flux<0, true><<<bx, 3 * AF, 0, st>>>(g, A, W);
-        k_adj_flux<1, true><<<by, 3 * AF, 0, st>>>(g, A, W);
+        k_adj_flux<true><<<bx + by, 6 * AF, 0, st>>>(g, A, W);
         k_adj_grad<true><<<bg, 6 * AG, 0, st>>>(g, A, W);
     } else {
-        k_adj_flux<0, false><<<bx, 3 * AF, 0, st>>>(g, A, W);
-        k_adj_flux<1, false><<<by, 3 * AF, 0, st>>>(g, A, W);
+        k_adj_flux<false><<<bx + by, 6 * AF, 0, st>>>(g, A, W);
         k_adj_grad<false><<<bg, 6 * AG, 0, st>>>(g, A, W);
     }
     const dim3 br(nb2((long long)(g.NX - 4) * (g.NY - 4), 256), 6);
