@@ -1580,6 +1580,30 @@ __device__ __forceinline__ void update_comp(const Grid2& g, const Grid2& gsrc, l
     }
 }
 
+__device__ __forceinline__ void reset_reduce(Reduce* r) {
+    r->alpha_key = dkey(-INFINITY);
+    r->beta_key = dkey(-INFINITY);
+    r->pp_cells = 0;
+    r->min_rho_key = dkey(INFINITY);
+    r->min_p_key = dkey(INFINITY);
+    r->bad[0] = r->bad[1] = r->bad[2] = r->bad[3] = 0;
+}
+
+// Step size of an update (StepRule).  In stage 1 every thread forms it from the
+// wave speed, which no kernel after that stage's reconstruction changes;
+// publish_step leaves it in the slots.
+__device__ __forceinline__ double step_dt(const Grid2& g, const StepRule& r) {
+    if (r.mode == 0) return g.red->dt;
+    if (r.mode == 2) return r.dt;
+    return fmin(fmin(r.cfl_h / dkey_inv(g.red->alpha_key), r.visc_dt), r.t_left);
+}
+__device__ __forceinline__ void publish_step(const Grid2& g, const StepRule& r, int block) {
+    if (r.mode == 0 || block != 0 || threadIdx.x != 0) return;
+    g.red->dt = step_dt(g, r);
+    g.red->alpha1_key = g.red->alpha_key;
+    if (r.clear) reset_reduce(r.clear);
+}
+
 __device__ __forceinline__ void store_comp(const Grid2& g, const Grid2& gsrc, long long t,
                                            long long cell, int c, int stage, int iout,
                                            double* __restrict__ Rout, double* __restrict__ Vout,
@@ -1629,8 +1653,9 @@ __device__ __forceinline__ void update_cell(const Grid2& g, const Grid2& gsrc, l
                                             int ii, int stage, int i0, int iin, int iout,
                                             double* __restrict__ Rout,
                                             double* __restrict__ Vout,
-                                            const double* __restrict__ src, const FF& ff,
-                                            double& rmin, double& pmin, unsigned int& bad) {
+                                            const double* __restrict__ src, double dt,
+                                            const FF& ff, double& rmin, double& pmin,
+                                            unsigned int& bad) {
     const long long cell = (long long)(jj + HALO) * g.NX + ii + HALO;
     if (gsrc.solid && gsrc.solid[t]) {
 #pragma unroll
@@ -1638,7 +1663,6 @@ __device__ __forceinline__ void update_cell(const Grid2& g, const Grid2& gsrc, l
             update_solid(g, gsrc, t, cell, c, stage, iin, iout, Rout, Vout);
         return;
     }
-    const double dt = stage > 0 ? g.red->dt : 0.0;
     double nw[4][3], vh[4][2];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -1663,11 +1687,13 @@ __device__ __forceinline__ void update_cell(const Grid2& g, const Grid2& gsrc, l
 __global__ __launch_bounds__(256) void k_update2(Batch bt, int stage, int i0, int iin, int iout,
                                                  double* __restrict__ Rout,
                                                  double* __restrict__ Vout,
-                                                 const double* __restrict__ src) {
+                                                 const double* __restrict__ src,
+                                                 StepRule rule) {
     const Loc lc = locate(bt);
     const Grid2& gsrc = bt.g[lc.p];   // arrays indexed at run time are read from here
     if (!gsrc.st->active) return;
     const Grid2 g = gsrc;
+    publish_step(g, rule, lc.b);
     const long long nint = (long long)g.nx * g.ny;
     const long long t = (long long)lc.b * blockDim.x + threadIdx.x;
     double rmin = INFINITY, pmin = INFINITY;
@@ -1685,8 +1711,8 @@ __global__ __launch_bounds__(256) void k_update2(Batch bt, int stage, int i0, in
                 Bo[m] = g.fy[(4 * m + c) * N + cell - g.NX];
             }
         };
-        update_cell(g, gsrc, t, jj, ii, stage, i0, iin, iout, Rout, Vout, src, ff, rmin, pmin,
-                    bad);
+        update_cell(g, gsrc, t, jj, ii, stage, i0, iin, iout, Rout, Vout, src,
+                    stage > 0 ? step_dt(g, rule) : 0.0, ff, rmin, pmin, bad);
     }
     if (stage > 0) reduce_update<256>(gsrc.red, stage, -INFINITY, rmin, pmin, bad != 0);
 }
@@ -1749,7 +1775,8 @@ template <bool FULL>
 __global__ __launch_bounds__(FU_TX * FU_TY) void k_fluxup2(Batch bt, int stage, int i0, int iin,
                                                            int iout, double* __restrict__ Rout,
                                                            double* __restrict__ Vout,
-                                                           const double* __restrict__ src) {
+                                                           const double* __restrict__ src,
+                                                           StepRule rule) {
     constexpr int RX = FU_TX + 1;                              // x-face columns per row
     constexpr int SX = FU_TY * RX, SY = (FU_TY + 1) * FU_TX;   // plane sizes
     __shared__ double lx[8 * SX];    // [moment*4 + c][row][face column 0..FU_TX]
@@ -1758,6 +1785,7 @@ __global__ __launch_bounds__(FU_TX * FU_TY) void k_fluxup2(Batch bt, int stage, 
     const Grid2& gsrc = bt.g[lc.p];   // arrays indexed at run time are read from here
     if (!gsrc.st->active) return;
     const Grid2 g = gsrc;
+    publish_step(g, rule, lc.b);
     // tiles start at multiples of FU_TX columns of the ghosted grid, so that
     // their row segments are whole cache lines; the first tile's leading
     // columns are ghost cells and stay idle
@@ -1801,7 +1829,7 @@ __global__ __launch_bounds__(FU_TX * FU_TY) void k_fluxup2(Batch bt, int stage, 
             }
         };
         update_cell(g, gsrc, (long long)jj * g.nx + ii, jj, ii, stage, i0, iin, iout, Rout, Vout,
-                    src, ff, rmin, pmin, bad);
+                    src, stage > 0 ? step_dt(g, rule) : 0.0, ff, rmin, pmin, bad);
     }
     reduce_update<FU_TX * FU_TY>(gsrc.red, stage, bmax, rmin, pmin, bad != 0);
 }
@@ -1852,7 +1880,8 @@ template <bool VarMu, bool FULL>
 __global__ __launch_bounds__(FS_NT) void k_fluxup2s(Batch bt, int stage, int i0, int iin, int iout,
                                                     double* __restrict__ Rout,
                                                     double* __restrict__ Vout,
-                                                    const double* __restrict__ src) {
+                                                    const double* __restrict__ src,
+                                                    StepRule rule) {
     constexpr int RX = FU_TX + 1;                              // x-face columns per row
     constexpr int NXF = FS_TY * RX, NYF = (FS_TY + 1) * FU_TX, NF = NXF + NYF;
     constexpr int NT = 3 * NF, NIT = (NT + FS_NT - 1) / FS_NT;
@@ -1864,6 +1893,7 @@ __global__ __launch_bounds__(FS_NT) void k_fluxup2s(Batch bt, int stage, int i0,
     const Grid2& gsrc = bt.g[lc.p];   // arrays indexed at run time are read from here
     if (!gsrc.st->active) return;
     const Grid2 g = gsrc;
+    publish_step(g, rule, lc.b);
     const int tiles_x = (g.nx + HALO + FU_TX - 1) / FU_TX;
     const int ii0 = (lc.b % tiles_x) * FU_TX - HALO, jj0 = (lc.b / tiles_x) * FS_TY;
     double fs[NIT][4] = {}, du[NIT][4] = {}, bmax = -INFINITY;
@@ -1920,8 +1950,8 @@ __global__ __launch_bounds__(FS_NT) void k_fluxup2s(Batch bt, int stage, int i0,
             mom(ty * RX + tx + 1, R);
             mom(NXF + ty * FU_TX + tx, Bo);
             mom(NXF + (ty + 1) * FU_TX + tx, T);
-            update_comp(g, gsrc, t, cell, c, stage, i0, iin, stage > 0 ? g.red->dt : 0.0, src, L,
-                        R, Bo, T, nw, vh);
+            update_comp(g, gsrc, t, cell, c, stage, i0, iin, stage > 0 ? step_dt(g, rule) : 0.0,
+                        src, L, R, Bo, T, nw, vh);
             store_comp(g, gsrc, t, cell, c, stage, iout, Rout, Vout, nw, vh);
             shu[c][ct] = nw[0];
             shk[c][ct] = isfinite(nw[0]) && isfinite(nw[1]) && isfinite(nw[2]);
@@ -1984,28 +2014,8 @@ __global__ __launch_bounds__(256) void k_check2(Batch bt, int si) {
     red_add32<256>(&g.red->bad[0], bad);
 }
 
-__device__ __forceinline__ void reset_reduce(Reduce* r) {
-    r->alpha_key = dkey(-INFINITY);
-    r->beta_key = dkey(-INFINITY);
-    r->pp_cells = 0;
-    r->min_rho_key = dkey(INFINITY);
-    r->min_p_key = dkey(INFINITY);
-    r->bad[0] = r->bad[1] = r->bad[2] = r->bad[3] = 0;
-}
-
 __global__ void k_reset(Reduce* r) {
     if (threadIdx.x == 0) reset_reduce(r);
-}
-
-__global__ void k_dt(Reduce* r, double cfl_h, double visc_dt, double t_left) {
-    if (threadIdx.x == 0) {
-        r->alpha1_key = r->alpha_key;
-        const double a = dkey_inv(r->alpha_key);
-        double dt = cfl_h / a;
-        dt = fmin(dt, visc_dt);
-        dt = fmin(dt, t_left);
-        r->dt = dt;
-    }
 }
 
 __global__ void k_set_dt(Reduce* r, double dt) {
@@ -2113,11 +2123,6 @@ inline unsigned nblk(long long n, int bs) { return (unsigned)((n + bs - 1) / bs)
 
 hipError_t launch_reset(Reduce* red, hipStream_t st) {
     k_reset<<<1, 64, 0, st>>>(red);
-    return hipGetLastError();
-}
-
-hipError_t launch_dt(Reduce* red, double cfl_h, double visc_dt, double t_left, hipStream_t st) {
-    k_dt<<<1, 64, 0, st>>>(red, cfl_h, visc_dt, t_left);
     return hipGetLastError();
 }
 
@@ -2317,28 +2322,25 @@ hipError_t launch_residual2(const BatchL& b, int si, int gst, hipStream_t st, Ti
 
 template <bool VarMu, bool FULL>
 void launch_fluxup2(const BatchL& b, int stage, int i0, int iin, int iout, double* R, double* Vhat,
-                    hipStream_t st, Timer* tm, const double* src) {
+                    hipStream_t st, Timer* tm, const double* src, const StepRule& rule) {
     if (VarMu || b.blocks(KB_FLUXUP) <= FS_MAX_BLOCKS)
         tlaunch(tm, KC_FLUXUP, k_fluxup2s<VarMu, FULL>, b.blocks(KB_FLUXUPS), FS_NT, st,
-                b.arg(KB_FLUXUPS), stage, i0, iin, iout, R, Vhat, src);
+                b.arg(KB_FLUXUPS), stage, i0, iin, iout, R, Vhat, src, rule);
     else
         tlaunch(tm, KC_FLUXUP, k_fluxup2<FULL>, b.blocks(KB_FLUXUP), FU_TX * FU_TY, st,
-                b.arg(KB_FLUXUP), stage, i0, iin, iout, R, Vhat, src);
+                b.arg(KB_FLUXUP), stage, i0, iin, iout, R, Vhat, src, rule);
 }
 
 hipError_t launch_update2(const BatchL& b, int stage, int i0, int iin, int iout, double* R,
-                          double* Vhat, hipStream_t st, Timer* tm, const double* src) {
+                          double* Vhat, hipStream_t st, Timer* tm, const double* src,
+                          const StepRule& rule) {
     if (b.tiles.flux == 0) {
-        if (b.full_grad) {
-            if (b.var_mu) launch_fluxup2<true, true>(b, stage, i0, iin, iout, R, Vhat, st, tm, src);
-            else launch_fluxup2<false, true>(b, stage, i0, iin, iout, R, Vhat, st, tm, src);
-        } else {
-            if (b.var_mu) launch_fluxup2<true, false>(b, stage, i0, iin, iout, R, Vhat, st, tm, src);
-            else launch_fluxup2<false, false>(b, stage, i0, iin, iout, R, Vhat, st, tm, src);
-        }
+        auto launch = [&](auto f) { f(b, stage, i0, iin, iout, R, Vhat, st, tm, src, rule); };
+        if (b.full_grad) launch(b.var_mu ? launch_fluxup2<true, true> : launch_fluxup2<false, true>);
+        else launch(b.var_mu ? launch_fluxup2<true, false> : launch_fluxup2<false, false>);
     } else {
         tlaunch(tm, KC_UPDATE, k_update2, b.blocks(KB_CELLS), 256, st, b.arg(KB_CELLS), stage, i0,
-                iin, iout, R, Vhat, src);
+                iin, iout, R, Vhat, src, rule);
     }
     return hipGetLastError();
 }

@@ -66,8 +66,9 @@ struct hweno_ctx {
     // landing place of result copies (PINNED bytes of pinned host memory, from
     // the first hweno_set_workspace; null: copies go to the caller's memory)
     void* pinned = nullptr;
-    // reduction slots red[1 + k] of the 1D steps, used in turn: a step's last
-    // kernel resets the slots of the next (red_clean[k]: they are reset)
+    // reduction slots red[1 + k] of a single grid's steps (2D: through the
+    // descriptors dg[1 + k]), used in turn: a step resets the slots of the
+    // next (red_clean[k]: they are reset)
     int red_turn = 0;
     bool red_clean[2] = {false, false};
     // reverse mode (single 2D grid; 1D grid)
@@ -336,9 +337,11 @@ size_t layout(hweno_ctx* c, char* base) {
             c->dstage = reinterpret_cast<hw::Grid2*>(take_bytes(2 * sizeof(hw::Grid2)));
         }
     }
-    c->red = reinterpret_cast<hw::Reduce*>(take_bytes(n * sizeof(hw::Reduce)));
+    // a single grid's steps take the slots and descriptors 1 and 2 in turn
+    const int turns = c->batch ? 0 : 2;
+    c->red = reinterpret_cast<hw::Reduce*>(take_bytes((n + turns) * sizeof(hw::Reduce)));
     c->dst = reinterpret_cast<hw::InstState*>(take_bytes(n * sizeof(hw::InstState)));
-    c->dg = reinterpret_cast<hw::Grid2*>(take_bytes(n * sizeof(hw::Grid2)));
+    c->dg = reinterpret_cast<hw::Grid2*>(take_bytes((n + turns) * sizeof(hw::Grid2)));
     c->dstart = reinterpret_cast<int*>(take_bytes(hw::KB_COUNT * (n + 1) * sizeof(int)));
     if (c->batch)
         for (int k = 0; k < 2; ++k)
@@ -450,8 +453,14 @@ hweno_status upload_grids(hweno_ctx* c) {
     for (int p = 0; p < n; ++p) slots[p] = c->hg[c->order[p]];
     c->hstart.assign(hw::KB_COUNT * (n + 1), 0);
     hw::batch_blocks(slots.data(), n, c->tiles, c->hstart.data());
-    TRY(dev(hipMemcpyAsync(c->dg, slots.data(), n * sizeof(hw::Grid2), hipMemcpyHostToDevice,
-                           c->stream)));
+    if (!c->batch) {
+        for (int k = 1; k <= 2; ++k) {
+            slots.push_back(slots[0]);
+            slots[k].red = (HW_GLOBAL hw::Reduce*)(c->red + k);
+        }
+    }
+    TRY(dev(hipMemcpyAsync(c->dg, slots.data(), slots.size() * sizeof(hw::Grid2),
+                           hipMemcpyHostToDevice, c->stream)));
     TRY(dev(hipMemcpyAsync(c->dstart, c->hstart.data(), c->hstart.size() * sizeof(int),
                            hipMemcpyHostToDevice, c->stream)));
     TRY(dev(hipStreamSynchronize(c->stream)));
@@ -652,7 +661,8 @@ bool fills_ghosts(hweno_ctx* c) {
 
 // 2D residual at a state whose ghost cells are not filled (nor the walls inside
 // the grid).  alpha: the CFL wave speed is wanted.
-hweno_status eval2(hweno_ctx* c, int si, int stage = -1, bool alpha = true) {
+hweno_status eval2(hweno_ctx* c, int si, int stage = -1, bool alpha = true,
+                   const hw::BatchL* b = nullptr) {
     hw::Timer* tm = c->tm();
     if (fills_ghosts(c)) {
         TRY(ghost(c, si, stage));
@@ -660,14 +670,15 @@ hweno_status eval2(hweno_ctx* c, int si, int stage = -1, bool alpha = true) {
     } else if (!c->batch && !c->sdst_host.empty()) {
         TRY(dev(hw::launch_solid2(c->dg, (int)c->sdst_host.size(), si, c->stream)));
     }
-    return dev(hw::launch_residual2(c->bl, si, stage, c->stream, tm, alpha));
+    return dev(hw::launch_residual2(b ? *b : c->bl, si, stage, c->stream, tm, alpha));
 }
 
 // 2D
 hweno_status update(hweno_ctx* c, int stage, int i0, int iin, int iout, double* R, double* V,
-                    const double* src = nullptr, const hw::BatchL* b = nullptr) {
+                    const double* src = nullptr, const hw::BatchL* b = nullptr,
+                    const hw::StepRule& rule = hw::StepRule()) {
     return dev(hw::launch_update2(b ? *b : c->bl, stage, i0, iin, iout, R, V, c->stream, c->tm(),
-                                  src));
+                                  src, rule));
 }
 
 // Whether the n doubles at a and the m doubles at b share memory.
@@ -1420,19 +1431,28 @@ hweno_status step(hweno_ctx* c, double dt, const double* const* src, hweno_diag*
             TRY(attempt1(c, auto_dt && restarts == 0, cur_dt, cfl_h, visc, t_left, check, src,
                          &r));
         } else {
-            TRY(reset(c));
-            if (check) TRY(dev(hw::launch_check2(c->bl, a, c->stream)));
-            TRY(eval2(c, a, staged ? 0 : -1));
-            if (auto_dt && restarts == 0)
-                TRY(dev(hw::launch_dt(c->red, cfl_h, visc, t_left, c->stream)));
-            else
-                TRY(dev(hw::launch_set_dt(c->red, cur_dt, c->stream)));
-            TRY(update(c, 1, a, a, b, nullptr, nullptr, src1));
-            TRY(eval2(c, b, staged ? 1 : -1, false));
-            TRY(update(c, 2, a, b, s2, nullptr, nullptr, src2));
-            TRY(eval2(c, s2, staged ? 2 : -1, false));
-            TRY(update(c, 3, a, s2, b, nullptr, nullptr, src3));
-            TRY(read_reduce(c, c->red, &r));
+            const int k = c->red_turn;
+            c->red_turn = 1 - k;
+            hw::BatchL bl = c->bl;
+            bl.dg = c->dg + 1 + k;
+            if (!c->red_clean[k]) TRY(dev(hw::launch_reset2(bl, c->stream)));
+            c->red_clean[0] = c->red_clean[1] = false;
+            hw::StepRule rl;
+            rl.mode = auto_dt && restarts == 0 ? 1 : 2;
+            rl.dt = cur_dt;
+            rl.cfl_h = cfl_h;
+            rl.visc_dt = visc;
+            rl.t_left = t_left;
+            rl.clear = c->red + 1 + (1 - k);
+            if (check) TRY(dev(hw::launch_check2(bl, a, c->stream)));
+            TRY(eval2(c, a, staged ? 0 : -1, true, &bl));
+            TRY(update(c, 1, a, a, b, nullptr, nullptr, src1, &bl, rl));
+            TRY(eval2(c, b, staged ? 1 : -1, false, &bl));
+            TRY(update(c, 2, a, b, s2, nullptr, nullptr, src2, &bl));
+            TRY(eval2(c, s2, staged ? 2 : -1, false, &bl));
+            TRY(update(c, 3, a, s2, b, nullptr, nullptr, src3, &bl));
+            TRY(read_reduce(c, c->red + 1 + k, &r));
+            c->red_clean[1 - k] = true;
         }
         if (restarts == 0 && r.bad[0] != 0) return HWENO_E_NONFINITE;
         if (!(r.dt > 0.0) || !std::isfinite(r.dt)) return HWENO_E_NONFINITE;

@@ -297,19 +297,29 @@ struct Place2 {
     int* dstart;
 };
 hipError_t launch_place2(const Place2& a, hipStream_t st);
+// Step size of an update: what the reduction slots hold (mode 0), or in stage 1 of
+// a single grid's step formed by its first update kernel itself, from the stage's
+// wave speed (1: min(cfl_h / alpha, visc_dt, t_left)) or as given (2), and left in
+// the slots for the later stages; `clear`: slots that kernel resets, those of
+// the next step.  As launches of their own the step size and the reset cost
+// a 64x64 step 9 of 103 us.
+struct StepRule {
+    int mode = 0;
+    double dt = 0.0, cfl_h = 0.0, visc_dt = 0.0, t_left = 0.0;
+    Reduce* clear = nullptr;
+};
 // stage 0: write R (12) and Vhat (8) in interior layout (single grid);
 // stage 1..3: RK update S[iout] from S[i0] (U^n) and S[iin] (stage input);
 // src (single grid, may be null): source moments added to the residual
 hipError_t launch_update2(const BatchL& b, int stage, int i0, int iin, int iout, double* R,
                           double* Vhat, hipStream_t st, Timer* tm,
-                          const double* src = nullptr);
+                          const double* src = nullptr, const StepRule& rule = StepRule());
 hipError_t launch_check2(const BatchL& b, int si, hipStream_t st);
 hipError_t launch_reset2(const BatchL& b, hipStream_t st);
 // per-instance step size from its InstState rule, halved per pending restart
 hipError_t launch_dt2(const BatchL& b, hipStream_t st);
 // accept (S[1] -> S[0], time, counters) or reject (halve) every active instance
 hipError_t launch_commit2(const BatchL& b, hipStream_t st);
-hipError_t launch_dt(Reduce* red, double cfl_h, double visc_dt, double t_left, hipStream_t st);
 hipError_t launch_set_dt(Reduce* red, double dt, hipStream_t st);
 
 hipError_t launch_copy_in1(const Grid1& g, const double* U, double* S, hipStream_t st);
