@@ -333,6 +333,93 @@ __global__ void k_ghost2(Batch bt, int sidx, int stage) {
     for (int q = 0; q < 12; ++q) S[q * g.ncell + dst] = v[q];
 }
 
+// Element i (cell offset in bytes) of a plane; base uniform per wavefront.
+__device__ __forceinline__ gdouble& at(gdouble* base, unsigned off) {
+    return *(gdouble*)((HW_GLOBAL char*)base + off);
+}
+
+// The 12 fields of a tile of TX x (64 / TX) cells at (i0, j0) and the ring around
+// it into LDS (planes of the tile with ring, clamped to the grid): wavefront wv
+// of four loads fields 3 wv .. 3 wv + 2, every load issued before the first LDS
+// write.  GH: no fill has written the ghost cells (inflow profiles of stage gst),
+// and the input may be the caller's interior array U.
+template <int TX, bool GH>
+__device__ __forceinline__ void load_tile(const Grid2& g, const Grid2& gsrc, int si, int gst,
+                                          const double* U, int i0, int j0, int lane, int wv,
+                                          double* tile) {
+    constexpr int TY = 64 / TX, TW = TX + 2, TH = TY + 2, PL = TW * TH;
+    constexpr int NP = (PL + 63) / 64;
+    // plane and row sizes pl and nr; U has interior cell (0, 0) first
+    const double* __restrict__ S = GH && U ? U : gsrc.S[si];
+    const long long N = g.ncell;
+    const long long pl = GH && U ? (long long)g.nx * g.ny : N;
+    const int nr = GH && U ? g.nx : g.NX, n0 = GH && U ? HALO * (g.nx + 1) : 0;
+    double v[3][NP];
+    if constexpr (!GH) {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
+            const int gj = min(j0 - 1 + r, g.NY - 1), gi = min(max(i0 - 1 + c, 0), g.NX - 1);
+            const unsigned src = 8u * (unsigned)(gj * g.NX + gi);
+#pragma unroll
+            for (int f = 0; f < 3; ++f)
+                if (t < PL) v[f][q] = at((gdouble*)S + (3 * wv + f) * N, src);
+        }
+    } else {
+        // no fill has written the ghost cells: they are read from their
+        // source cells, sources and signs without branches (index gi of a
+        // ghost cell has source ga * gi + gb); prescribed states (inflow)
+        // replace theirs afterwards
+        int ga[4], gb[4];
+#pragma unroll
+        for (int sd = 0; sd < 4; ++sd) {
+            const int kind = g.rule[sd] & 15, n = sd < 2 ? g.nx : g.ny;
+            ga[sd] = kind == 0 ? 1 : (kind == 1 ? 0 : -1);
+            if (sd & 1) gb[sd] = kind == 0 ? -n : (kind == 1 ? HALO + n - 1 : 2 * (HALO + n) - 1);
+            else gb[sd] = kind == 0 ? n : (kind == 1 ? HALO : 2 * HALO - 1);
+        }
+        unsigned in = 0;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
+            const int gj = min(j0 - 1 + r, g.NY - 1), gi = min(max(i0 - 1 + c, 0), g.NX - 1);
+            const bool yl = gj < HALO, yh = gj >= HALO + g.ny;
+            const bool xl = gi < HALO, xh = gi >= HALO + g.nx;
+            const int sj = (yl ? ga[2] : (yh ? ga[3] : 1)) * gj + (yl ? gb[2] : (yh ? gb[3] : 0));
+            const int sx = (xl ? ga[0] : (xh ? ga[1] : 1)) * gi + (xl ? gb[0] : (xh ? gb[1] : 0));
+            const unsigned ry = yl ? g.rule[2] : (yh ? g.rule[3] : 0u);
+            const unsigned rx = xl ? g.rule[0] : (xh ? g.rule[1] : 0u);
+            in |= ((ry | rx) >> 31) << q;
+            const unsigned src = 8u * (unsigned)(sj * nr + sx - n0);
+            const unsigned neg = (ry ^ rx) >> (4 + 3 * wv);
+#pragma unroll
+            for (int f = 0; f < 3; ++f)
+                if (t < PL)
+                    v[f][q] = flip_sign(at((gdouble*)S + (3 * wv + f) * pl, src), neg >> f & 1u);
+        }
+        if (__ballot(in != 0)) {
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
+                const int gj = min(j0 - 1 + r, g.NY - 1);
+                const int gi = min(max(i0 - 1 + c, 0), g.NX - 1);
+                double st[4];
+                if (t < PL && (in >> q & 1)) {
+                    inflow_at(gsrc, gj, gi, gst, st);
+#pragma unroll
+                    for (int f = 0; f < 3; ++f)   // wavefront 0: fields 0-2, 1: 3-5, ...
+                        v[f][q] = wv == 0 ? st[f] : (wv == 1 && f == 0 ? st[3] : 0.0);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+        for (int f = 0; f < 3; ++f)
+            if (lane + 64 * q < PL) tile[(3 * wv + f) * PL + lane + 64 * q] = v[f][q];
+}
+
 // ---------------------------------------------------------------------------
 // Characteristic reconstruction + positivity limiter (HWENO-GR).
 // Block: a TX x (64 / TX) tile of cells, four wavefronts, one thread per cell
@@ -354,11 +441,6 @@ __global__ void k_ghost2(Batch bt, int sidx, int stage) {
 // us, but 12.1 us on 64^2.  Four wavefronts per SIMD instead of three spill
 // (193 us).
 // ---------------------------------------------------------------------------
-// Element i (cell offset in bytes) of a plane; base uniform per wavefront.
-__device__ __forceinline__ gdouble& at(gdouble* base, unsigned off) {
-    return *(gdouble*)((HW_GLOBAL char*)base + off);
-}
-
 template <int TX, bool VarMu, bool FULL, bool GH>
 __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_alpha, int gst,
                                                  const double* U) {
@@ -376,11 +458,7 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
     const Grid2& gsrc = bt.g[lc.p];   // arrays indexed at run time are read from here
     if (!gsrc.st->active) return;
     const Grid2 g = gsrc;
-    // GH: the input may be the caller's interior array U (plane and row sizes
-    // pl and nr, interior cell (0, 0) first)
-    const double* __restrict__ S = GH && U ? U : gsrc.S[si];
-    const long long pl = GH && U ? (long long)g.nx * g.ny : g.ncell;
-    const int nr = GH && U ? g.nx : g.NX, n0 = GH && U ? HALO * (g.nx + 1) : 0;
+    const double* __restrict__ S = gsrc.S[si];
     const Consts& K = g.K;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -393,74 +471,7 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
     const int lx = lane % TX, ly = lane / TX;
     const int i = i0 + lx, j = j0 + ly;
     const bool valid = i >= 1 && i <= g.NX - 2 && j <= g.NY - 2;
-    // stencil tile: wavefront wv loads fields 3 wv .. 3 wv + 2, every load
-    // issued before the first LDS write
-    {
-        double v[3][NP];
-        if constexpr (!GH) {
-#pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
-                const int gj = min(j0 - 1 + r, g.NY - 1), gi = min(max(i0 - 1 + c, 0), g.NX - 1);
-                const unsigned src = 8u * (unsigned)(gj * g.NX + gi);
-#pragma unroll
-                for (int f = 0; f < 3; ++f)
-                    if (t < PL) v[f][q] = at((gdouble*)S + (3 * wv + f) * N, src);
-            }
-        } else {
-            // no fill has written the ghost cells: they are read from their
-            // source cells, sources and signs without branches (index gi of a
-            // ghost cell has source ga * gi + gb); prescribed states (inflow)
-            // replace theirs afterwards
-            int ga[4], gb[4];
-#pragma unroll
-            for (int sd = 0; sd < 4; ++sd) {
-                const int kind = g.rule[sd] & 15, n = sd < 2 ? g.nx : g.ny;
-                ga[sd] = kind == 0 ? 1 : (kind == 1 ? 0 : -1);
-                if (sd & 1) gb[sd] = kind == 0 ? -n : (kind == 1 ? HALO + n - 1 : 2 * (HALO + n) - 1);
-                else gb[sd] = kind == 0 ? n : (kind == 1 ? HALO : 2 * HALO - 1);
-            }
-            unsigned in = 0;
-#pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
-                const int gj = min(j0 - 1 + r, g.NY - 1), gi = min(max(i0 - 1 + c, 0), g.NX - 1);
-                const bool yl = gj < HALO, yh = gj >= HALO + g.ny;
-                const bool xl = gi < HALO, xh = gi >= HALO + g.nx;
-                const int sj = (yl ? ga[2] : (yh ? ga[3] : 1)) * gj + (yl ? gb[2] : (yh ? gb[3] : 0));
-                const int si = (xl ? ga[0] : (xh ? ga[1] : 1)) * gi + (xl ? gb[0] : (xh ? gb[1] : 0));
-                const unsigned ry = yl ? g.rule[2] : (yh ? g.rule[3] : 0u);
-                const unsigned rx = xl ? g.rule[0] : (xh ? g.rule[1] : 0u);
-                in |= ((ry | rx) >> 31) << q;
-                const unsigned src = 8u * (unsigned)(sj * nr + si - n0);
-                const unsigned neg = (ry ^ rx) >> (4 + 3 * wv);
-#pragma unroll
-                for (int f = 0; f < 3; ++f)
-                    if (t < PL)
-                        v[f][q] = flip_sign(at((gdouble*)S + (3 * wv + f) * pl, src), neg >> f & 1u);
-            }
-            if (__ballot(in != 0)) {
-#pragma unroll
-                for (int q = 0; q < NP; ++q) {
-                    const int t = lane + 64 * q, r = t / TW, c = t - r * TW;
-                    const int gj = min(j0 - 1 + r, g.NY - 1);
-                    const int gi = min(max(i0 - 1 + c, 0), g.NX - 1);
-                    double st[4];
-                    if (t < PL && (in >> q & 1)) {
-                        inflow_at(gsrc, gj, gi, gst, st);
-#pragma unroll
-                        for (int f = 0; f < 3; ++f)   // wavefront 0: fields 0-2, 1: 3-5, ...
-                            v[f][q] = wv == 0 ? st[f] : (wv == 1 && f == 0 ? st[3] : 0.0);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < NP; ++q)
-#pragma unroll
-            for (int f = 0; f < 3; ++f)
-                if (lane + 64 * q < PL) tile[(3 * wv + f) * PL + lane + 64 * q] = v[f][q];
-    }
+    load_tile<TX, GH>(g, gsrc, si, gst, U, i0, j0, lane, wv, tile);
     __syncthreads();
     const double* T0 = tile + (ly + 1) * TW + lx + 1;
     if constexpr (GH) shu[wv][lane] = T0[wv * PL];
@@ -667,319 +678,301 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
 
 // ---------------------------------------------------------------------------
 // Characteristic reconstruction + positivity limiter, HWENO-DR (eq. (3.5)).
-// Block: 32 cells x 8 threads; thread (b, k) projects onto characteristic
-// field k of basis b (0: x-Jacobian, 1: y-Jacobian), reconstructs it, and
-// after an LDS exchange owns conservative component k of basis b.  The thread
-// also differentiates its field's combination in xi and eta at the basis's face
-// and volume points (weights kept), the derivatives go back to conservative
-// variables through the same exchange, and the viscous gradients
-// s = (u_x, u_y, v_x, v_y, e_x, e_y) are formed with the point values that
-// enter the flux there (limited face traces; each basis's unlimited volume
-// values for its own volume flux).  The kernel then writes the face
-// gradients and the volume-flux quadratures itself, in place of the
-// weak-moment and gradient kernels.
+// The block, the split over its wavefronts and the handing over are those of
+// k_recon2.  A wavefront keeps the coefficients of its two fields and, after
+// the limiter, differentiates them (weights kept) along the normal, then along the
+// tangent of its basis; the derivatives take the same way as the values: the
+// partner's points through LDS, four conserved components at its own points in
+// registers.  There they give the gradients of (u_n, u_t, e) with the point values
+// that enter the flux (limited face traces; unlimited volume values), so the
+// kernel writes the face gradients and the volume-flux quadratures itself, in
+// place of the weak-moment and gradient kernels.
+// Bound: arithmetic at two wavefronts per SIMD (two fields' coefficients are live
+// throughout).  A thread per field, which exchanged every value and derivative
+// twice through LDS behind 19 barriers, took 97 us per stage on 500x250 and 111
+// with mu(T); this one takes 77 and 97 (13.5 and 15.4 on 64x64, where the ghost
+// cells formed in its loads save a launch of 5).
 // ---------------------------------------------------------------------------
-template <int RC_CELLS, bool VarMu>
-__global__ __launch_bounds__(8 * RC_CELLS) void k_recon2_dr(Batch bt, int si) {
-    // one block = RC_CELLS consecutive cells of one row; the 3-row stencil
-    // tile of all 12 fields is staged in LDS first, then the same memory holds
-    // the exchange of the 16 outputs of every (basis, field) thread
-    constexpr int TW = RC_CELLS + 2;                 // tile width (columns)
-    constexpr int TILE = 12 * 3 * TW;
-    constexpr int SH = 8 * 16 * RC_CELLS;
-    __shared__ double sh[SH > TILE ? SH : TILE];
-    // the per-thread reductions use the exchange's moment slots (o = 15),
-    // which are never read back
-    double* const red = sh + 15 * RC_CELLS;
+template <int TX, bool VarMu, bool GH>
+__global__ __launch_bounds__(256, 2) void k_recon2_dr(Batch bt, int si, int want_alpha, int gst,
+                                                      const double* U) {
+    constexpr int TY = 64 / TX, TW = TX + 2, TH = TY + 2, PL = TW * TH;
+    // handed over per basis, one field of each wavefront: 9 volume values (h = 0),
+    // 6 face values and the moment (h = 1); the derivatives likewise
+    constexpr int XV = 2 * (9 + 7) * 64, XD = 2 * (9 + 6) * 64;
+    __shared__ double shv[2 * XV];
+    __shared__ double shd[2 * XD];         // the stencil tile first
+    __shared__ double shm[2][4][64];       // [density, pressure][wavefront][cell]
+    __shared__ double shk[VarMu ? 2 * 9 * 64 : 1];   // mu(T) at the volume points
+    static_assert(2 * XD >= 12 * PL, "the derivatives reuse the tile");
     const Loc lc = locate(bt);
     const Grid2& gsrc = bt.g[lc.p];   // arrays indexed at run time are read from here
     if (!gsrc.st->active) return;
     const Grid2 g = gsrc;
-    const double* __restrict__ S = gsrc.S[si];
     const Consts& K = g.K;
-    const int tid = threadIdx.x;
-    const int cl = tid & (RC_CELLS - 1);
-    // 32 cells: wavefront w holds field k = w of both bases (lanes 0..31 the
-    // x-basis, 32..63 the y-basis), so k is uniform per wavefront
-    const int k = RC_CELLS == 32 ? __builtin_amdgcn_readfirstlane(tid >> 6) : (tid / RC_CELLS) & 3;
-    const int b = RC_CELLS == 32 ? (tid >> 5) & 1 : (tid / RC_CELLS) >> 2;
-    const int bk = b * 4 + k;
-    // region: rows 1..NY-2, columns 1..NX-2, in row segments of RC_CELLS
-    const int segs = (g.NX - 2 + RC_CELLS - 1) / RC_CELLS;
-    const int j = 1 + lc.b / segs;
-    const int i0 = 1 + (lc.b % segs) * RC_CELLS;
-    const int i = i0 + cl;
-    const bool valid = i <= g.NX - 2;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = wv >> 1, hh = wv & 1;
     const long long N = g.ncell;
-    const long long cell = (long long)j * g.NX + i;
-    // stencil tile: rows j-1..j+1, columns i0-1..i0+RC_CELLS (clamped to the
-    // grid); tile row R = 3 c + r holds field c of grid row j-1+r.  All of a
-    // thread's loads are issued before the first LDS write.
-    if constexpr (RC_CELLS == 32) {
-        // wavefront wv loads tile rows 9 wv .. 9 wv + 8, lane = column: the row
-        // base is wave-uniform and the lane offset is fixed
-        const int lane = tid & 63;
-        const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int gi = min(i0 - 1 + lane, g.NX - 1);
-        const bool col_ok = lane < TW;
-        double v[9];
-#pragma unroll
-        for (int q = 0; q < 9; ++q) {
-            const int R = 9 * wv + q, c = R / 3, r = R - 3 * c;
-            if (col_ok) v[q] = S[c * N + (long long)(j - 1 + r) * g.NX + gi];
-        }
-#pragma unroll
-        for (int q = 0; q < 9; ++q)
-            if (col_ok) sh[(9 * wv + q) * TW + lane] = v[q];
-    } else {
-        constexpr int NT = 8 * RC_CELLS;
-        constexpr int NIT = (TILE + NT - 1) / NT;
-        double v[NIT];
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            const int t = tid + it * NT;
-            if (t < TILE) {
-                const int R = t / TW, col = t - R * TW;
-                const int c = R / 3, r = R - 3 * c;
-                const int gi = min(i0 - 1 + col, g.NX - 1);
-                v[it] = S[c * N + (long long)(j - 1 + r) * g.NX + gi];
-            }
-        }
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            const int t = tid + it * NT;
-            if (t < TILE) sh[t] = v[it];
-        }
-    }
+    // region: rows 1..NY-2, columns 1..NX-2; tiles start at multiples of TX
+    // columns of the ghosted grid
+    const int tiles_x = (g.NX - 1 + TX - 1) / TX;
+    const int i0 = (lc.b % tiles_x) * TX, j0 = 1 + (lc.b / tiles_x) * TY;
+    const int lx = lane % TX, ly = lane / TX;
+    const int i = i0 + lx, j = j0 + ly;
+    const bool valid = i >= 1 && i <= g.NX - 2 && j <= g.NY - 2;
+    const unsigned off = 8u * (unsigned)(j * g.NX + i);
+    load_tile<TX, GH>(g, gsrc, si, gst, U, i0, j0, lane, wv, shd);
     __syncthreads();
-    auto T = [&](int c, int oy, int ox) -> double {
-        return sh[(c * 3 + 1 + oy) * TW + cl + 1 + ox];
-    };
-
-    double ub[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) ub[c] = T(c, 0, 0);
-    double Lr[4], Rr[4];
-    eig2_rows(K, ub, b, k, Lr, Rr);
-
-    double a[17];
-#pragma unroll
-    for (int s = 0; s < 9; ++s) {
-        double acc = 0.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc += Lr[c] * T(c, s / 3 - 1, s % 3 - 1);
-        a[s] = acc;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int s = 2 * e + 1;   // cells 2, 4, 6, 8
-        double ax = 0.0, ay = 0.0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            ax += Lr[c] * T(4 + c, s / 3 - 1, s % 3 - 1);
-            ay += Lr[c] * T(8 + c, s / 3 - 1, s % 3 - 1);
-        }
-        a[9 + e] = ax;
-        a[13 + e] = ay;
-    }
-    __syncthreads();   // the tile is dead; sh holds the output exchange from here
-    double C[15];
-    hweno2d(a, K, C);
-    double out[16];
-    if (b == 0) eval_xface(C, out);
-    else eval_yface(C, out);
-    eval_vol(C, out + 6);
-    out[15] = b == 0 ? moment_xi(C) : moment_eta(C);
-#pragma unroll
-    for (int o = 0; o < 16; ++o) sh[(bk * 16 + o) * RC_CELLS + cl] = out[o];
-    __syncthreads();
-    // back to conservative component k of basis b
-    double U[16];
-#pragma unroll
-    for (int o = 0; o < 16; ++o) {
-        double acc = 0.0;
-#pragma unroll
-        for (int f = 0; f < 4; ++f) acc += Rr[f] * sh[((b * 4 + f) * 16 + o) * RC_CELLS + cl];
-        U[o] = acc;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int o = 0; o < 16; ++o) sh[(bk * 16 + o) * RC_CELLS + cl] = U[o];
-    __syncthreads();
-
-    // positivity limiter: theta over 6 face + 9 volume points of both bases
-    auto comp = [&](int bb, int c, int o) { return sh[((bb * 4 + c) * 16 + o) * RC_CELLS + cl]; };
-    double rmin = INFINITY;
-    for (int o = k; o < 15; o += 4) rmin = fmin(rmin, comp(b, 0, o));
-    red[bk * 16 * RC_CELLS + cl] = rmin;
-    __syncthreads();
-    rmin = red[cl];
-#pragma unroll
-    for (int q = 1; q < 8; ++q) rmin = fmin(rmin, red[q * 16 * RC_CELLS + cl]);
+    const double* T0 = shd + (ly + 1) * TW + lx + 1;
+    // cell average in basis order (pbar: the same bits in every wavefront)
+    const double ub[4] = {T0[0], T0[(1 + b) * PL], T0[(2 - b) * PL], T0[3 * PL]};
     const double rbar = ub[0];
-    const double pbar = pressure2(K, ub[0], ub[1], ub[2], ub[3]);
-    const double eps = fmin(fmin(K.eps_pp, rbar), pbar);
-    const double th1 = rmin < eps ? (rbar - eps) / (rbar - rmin) : 1.0;
-    double tmin = 1.0;
-    for (int o = k; o < 15; o += 4) {
-        const double rt = rbar + th1 * (comp(b, 0, o) - rbar);
-        const double pt = pressure2(K, rt, comp(b, 1, o), comp(b, 2, o), comp(b, 3, o));
-        if (pt < eps) tmin = fmin(tmin, (pbar - eps) / (pbar - pt));
-    }
-    __syncthreads();   // every thread has read the rho minima
-    red[bk * 16 * RC_CELLS + cl] = tmin;
-    __syncthreads();
-    double th2 = red[cl];
+    const double pbar = pressure2(K, rbar, T0[PL], T0[2 * PL], T0[3 * PL]);
+    const Basis2 e = basis2(K, rbar, ub[1], ub[2], ub[3]);
+    const Part<0> face{};
+    const Part<1> vol{};
+    // this wavefront's fields: coefficients, and values at its own points (the
+    // last slot of h = 0: 6 face values, then the moment)
+    double Ca[15], Cb[15], va[9], vb[9];
+#pragma unroll 1
+    for (int kk = 0; kk < 2; ++kk) {
+        const int k = hh == 0 ? 3 * kk : 1 + kk;
 #pragma unroll
-    for (int q = 1; q < 8; ++q) th2 = fmin(th2, red[q * 16 * RC_CELLS + cl]);
-
-    const bool inter = valid && j >= HALO && j < HALO + g.ny && i >= HALO && i < HALO + g.nx;
-    if (valid) {
-        double* F = (b == 0 ? g.xf : g.yf) + k * N + cell;
-#pragma unroll
-        for (int o = 0; o < 6; ++o) {
-            const double ut = k == 0 ? rbar + th1 * (U[o] - rbar) : U[o];
-            F[o * 4 * N] = ub[k] + th2 * (ut - ub[k]);
-        }
-    }
-    if (inter) g.vk[(b * 4 + k) * N + cell] = U[15];
-    // CFL wave speed over the limited face traces of interior cells; thread k
-    // takes the face points o = k, k+4
-    double amax = -INFINITY;
-    if (inter) {
-        for (int o = k; o < 6; o += 4) {
-            double Ul[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const double x = comp(b, c, o);
-                const double ut = c == 0 ? rbar + th1 * (x - rbar) : x;
-                Ul[c] = ub[c] + th2 * (ut - ub[c]);
-            }
-            const double ir = rcp(Ul[0]);
-            const double u = Ul[1] * ir, v = Ul[2] * ir;
-            const double p = K.gm1 * (Ul[3] - 0.5 * (Ul[1] * u + Ul[2] * v));
-            const double sp = fmax(fabs(u), fabs(v)) + sqrt(K.gamma * p * ir);
-            amax = fmax(amax, sp);
-        }
-    }
-    // thread k converts the points o = k, k+4, k+8, k+12 of basis b:
-    // gather the four components of the point values (limited on the
-    // faces) and of their two derivatives from the exchange
-    double P[4][4], Dx[4][4], Dy[4][4];
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-        const int o = k + 4 * s4;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (o < 15) {
-                const double x = comp(b, c, o);
-                const double ut = c == 0 ? rbar + th1 * (x - rbar) : x;
-                P[s4][c] = o < 6 ? ub[c] + th2 * (ut - ub[c]) : x;
-            } else {
-                P[s4][c] = 1.0;
-            }
-        }
-    }
-    // the derivatives of this field's combination in xi, then eta, at the
-    // 15 points; back to conservative component k through the exchange
-    // (as the values), then a second exchange hands each thread the four
-    // components at its points
-#pragma unroll
-    for (int dir = 0; dir < 2; ++dir) {
-        double dv[15];
+        for (int q = 0; q < 15; ++q) Ca[q] = Cb[q];
         {
-            double D[15];
-            if (dir == 0) dxi_coeffs(C, D);
-            else deta_coeffs(C, D);
-            if (b == 0) eval_xface(D, dv);
-            else eval_yface(D, dv);
-            eval_vol(D, dv + 6);
+            double L[4], R[4], a[17];
+            field_rows(e, k, L, R);
+            if (b == 0) project2<0, TW, PL>(T0, L, a);
+            else project2<1, TW, PL>(T0, L, a);
+            hweno2d(a, K, Cb);
         }
-        __syncthreads();
+        double* X = shv + kk * XV + b * (XV / 2) + lane;
+        double f[7], w[9];
+        eval_xface(Cb, f);
+        f[6] = moment_xi(Cb);
+        eval_vol(Cb, w);
+        if (hh == 0) {
 #pragma unroll
-        for (int o = 0; o < 15; ++o) sh[(bk * 16 + o) * RC_CELLS + cl] = dv[o];
-        __syncthreads();
-        const double h = dir == 0 ? K.idx : K.idy;
+            for (int q = 0; q < 9; ++q) X[q * 64] = w[q];
 #pragma unroll
-        for (int o = 0; o < 15; ++o) {
-            double acc = 0.0;
+            for (int q = 0; q < 7; ++q) {
+                va[q] = vb[q];
+                vb[q] = f[q];
+            }
+        } else {
 #pragma unroll
-            for (int f = 0; f < 4; ++f)
-                acc += Rr[f] * sh[((b * 4 + f) * 16 + o) * RC_CELLS + cl];
-            dv[o] = acc * h;
-        }
-        __syncthreads();
+            for (int q = 0; q < 7; ++q) X[(9 + q) * 64] = f[q];
 #pragma unroll
-        for (int o = 0; o < 15; ++o) sh[(bk * 16 + o) * RC_CELLS + cl] = dv[o];
-        __syncthreads();
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-            const int o = min(k + 4 * s4, 14);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const double x = sh[((b * 4 + c) * 16 + o) * RC_CELLS + cl];
-                if (dir == 0) Dx[s4][c] = x;
-                else Dy[s4][c] = x;
+            for (int q = 0; q < 9; ++q) {
+                va[q] = vb[q];
+                vb[q] = w[q];
             }
         }
     }
-    // faces of interior cells read the gradients of the cells on both
-    // sides; volume fluxes are needed in interior cells only
+    __syncthreads();   // the values are handed over and the tile is dead
+    auto cons = [&](double x0, double x1, double x2, double x3, double* u) {
+#pragma clang fp contract(off)
+        const double sm = x0 + x3, df = x3 - x0;
+        u[0] = sm + x1;
+        u[1] = fma(e.un, u[0], e.c * df);
+        u[2] = fma(e.ut, u[0], x2);
+        u[3] = fma(e.H, sm, fma(e.un * e.c, df, fma(0.5 * e.q2, x1, e.ut * x2)));
+    };
+    // conserved components at own point o from the wavefront's fields xa, xb and
+    // the partner's at X and X + step
+    auto point = [&](auto H, int o, const double* xa, const double* xb, const double* X, int step,
+                     double* u) {
+        if constexpr (H.value == 0) cons(xa[o], X[(9 + o) * 64], X[step + (9 + o) * 64], xb[o], u);
+        else cons(X[o * 64], xa[o], xb[o], X[step + o * 64], u);
+    };
+    const double* XP = shv + b * (XV / 2) + lane;
+    const int gc[4] = {0, 1 + b, 2 - b, 3};   // global number of a basis component
+    const bool inter = valid && j >= HALO && j < HALO + g.ny && i >= HALO && i < HALO + g.nx;
+    // positivity limiter, as in k_recon2
+    double rmin = INFINITY, pmin = INFINITY, th1 = 1.0, th2 = 1.0;
+    bool acted = false;
+    auto minima = [&](auto H, bool limited) {
+#pragma unroll
+        for (int o = 0; o < H.points; ++o) {
+            double u[4];
+            point(H, o, va, vb, XP, XV, u);
+            if (!limited) rmin = fmin(rmin, u[0]);
+            const double r = limited ? rbar + th1 * (u[0] - rbar) : u[0];
+            pmin = fmin(pmin, pressure2(K, r, u[1], u[2], u[3]));
+        }
+    };
+    if (hh == 0) minima(face, false);
+    else minima(vol, false);
+    shm[0][wv][lane] = rmin;
+    shm[1][wv][lane] = pmin;
+    __syncthreads();
+    auto least = [&](int q) {
+        return fmin(fmin(shm[q][0][lane], shm[q][1][lane]), fmin(shm[q][2][lane], shm[q][3][lane]));
+    };
+    rmin = least(0);
+    pmin = least(1);
+    const double eps = fmin(fmin(K.eps_pp, rbar), pbar);
+    // every wavefront holds the same cells and minima: the branch is taken by
+    // the whole block or not at all
+    if (__ballot(valid && rmin < eps)) {
+        th1 = rmin < eps ? (rbar - eps) / (rbar - rmin) : 1.0;
+        pmin = INFINITY;
+        if (hh == 0) minima(face, true);
+        else minima(vol, true);
+        __syncthreads();   // the unlimited minima have been read
+        shm[1][wv][lane] = pmin;
+        __syncthreads();
+        pmin = least(1);
+    }
+    acted = th1 < 1.0 || pmin < eps;
+    if (pmin < eps) th2 = fmin((pbar - eps) / (pbar - pmin), 1.0);
+    // value that enters the flux at own point o
+    auto value = [&](auto H, int o, double* u) {
+        point(H, o, va, vb, XP, XV, u);
+        if constexpr (H.value == 0) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double x = c == 0 ? rbar + th1 * (u[0] - rbar) : u[c];
+                u[c] = acted ? ub[c] + th2 * (x - ub[c]) : u[c];
+            }
+        }
+    };
+    if (hh == 0) {
+        double amax = -INFINITY;
+        gdouble* F = b ? g.yf : g.xf;
+#pragma unroll
+        for (int o = 0; o < 7; ++o) {
+            double u[4];
+            if (o == 6) {
+                point(face, o, va, vb, XP, XV, u);
+                if (inter) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) at(g.vk + (b * 4 + gc[c]) * N, off) = u[c];
+                }
+                continue;
+            }
+            value(face, o, u);
+            if (valid) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) at(F + (o * 4 + gc[c]) * N, off) = u[c];
+            }
+            // CFL wave speed over the limited face traces of interior cells
+            const double ir = rcp(u[0]);
+            const double un = u[1] * ir, ut = u[2] * ir;
+            const double p = K.gm1 * fma(-0.5, fma(u[1], un, u[2] * ut), u[3]);
+            amax = fmax(amax, fmax(fabs(un), fabs(ut)) + sqrt(K.gamma * p * ir));
+        }
+        if (want_alpha) {
+            amax = wave_max(inter ? amax : -INFINITY);
+            if (lane == 0) {
+                const unsigned long long k = dkey(amax);
+                HW_GLOBAL unsigned long long* slot = &gsrc.red->alpha_key;
+                if (amax > -INFINITY && k > *(volatile HW_GLOBAL unsigned long long*)slot)
+                    atomicMax((unsigned long long*)slot, k);
+            }
+        }
+        const unsigned long long n = __ballot(inter && acted);
+        if (b == 0 && lane == 0 && n)
+            atomicAdd((unsigned long long*)&gsrc.red->pp_cells, (unsigned long long)__popcll(n));
+    }
+    // mu(T) at the volume points ahead of the gradients, whose registers it would
+    // spill (the wavefront reads its own back)
+    double* M = shk + (VarMu ? b * (9 * 64) + lane : 0);
+    if constexpr (VarMu) {
+        if (hh == 1) {
+#pragma unroll
+            for (int o = 0; o < 9; ++o) {
+                double u[4];
+                value(vol, o, u);
+                M[o * 64] = viscosity<true>(K, u[0], pressure2(K, u[0], u[1], u[2], u[3]));
+            }
+        }
+    }
+    // derivatives along the normal (dir 0) and the tangent (dir 1), and from them
+    // the gradients; faces of interior cells read those of the cells on both
+    // sides, volume fluxes are needed in interior cells only
     const bool ring = valid && j >= HALO - 1 && j <= HALO + g.ny && i >= HALO - 1 &&
                       i <= HALO + g.nx;
+    double sn[9][3];                      // normal derivatives of (u_n, u_t, e)
     double vfs[4] = {0.0, 0.0, 0.0, 0.0};
+    auto gradients = [&](auto H, int dir, const double* da, const double* db) {
+        const double* X = shd + b * (XD / 2) + lane;
+        const double h = (b == 0) == (dir == 0) ? K.idx : K.idy;
 #pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-        const int o = k + 4 * s4;
-        if (o >= 15 || !ring) continue;
-        const double ir = rcp(P[s4][0]);
-        const double u = P[s4][1] * ir, v = P[s4][2] * ir, eo = P[s4][3] * ir;
-        double sg[6];
+        for (int o = 0; o < H.points; ++o) {
+            double P[4], D[4];
+            value(H, o, P);
+            point(H, o, da, db, X, XD, D);
 #pragma unroll
-        for (int dir = 0; dir < 2; ++dir) {
-            const double* D = dir == 0 ? Dx[s4] : Dy[s4];
-            const double ul = (D[1] - u * D[0]) * ir;
-            const double vl = (D[2] - v * D[0]) * ir;
-            const double el = (D[3] - eo * D[0]) * ir - u * ul - v * vl;
-            sg[0 + dir] = ul;
-            sg[2 + dir] = vl;
-            sg[4 + dir] = el;
+            for (int c = 0; c < 4; ++c) D[c] *= h;
+            const double ir = rcp(P[0]);
+            const double un = P[1] * ir, ut = P[2] * ir;
+            const double dn = (D[1] - un * D[0]) * ir, dt = (D[2] - ut * D[0]) * ir;
+            const double de = (D[3] - P[3] * ir * D[0]) * ir - un * dn - ut * dt;
+            if (dir == 0) {
+                sn[o][0] = dn;
+                sn[o][1] = dt;
+                sn[o][2] = de;
+                continue;
+            }
+            // (u_n)_n, (u_n)_t, (u_t)_n, (u_t)_t, e_n, e_t: direction 0 of the
+            // basis's own coordinates
+            const double sg[6] = {sn[o][0], dn, sn[o][1], dt, sn[o][2], de};
+            if constexpr (H.value == 0) {
+                double dc[3];
+                stress_combos<0>(sg, dc);
+                if (ring) {
+#pragma unroll
+                    for (int z = 0; z < 3; ++z) at(g.gf + ((b * 6 + o) * 3 + z) * N, off) = dc[z];
+                }
+            } else {
+                const double w = (o / 3 == 1 ? GW1 : GW0) * (o % 3 == 1 ? GW1 : GW0);
+                const double mu = VarMu ? M[o * 64] : K.mu_ref;
+                const double p = K.gm1 * fma(-0.5, fma(P[1], un, P[2] * ut), P[3]);
+                const Stress tau = stresses(mu, sg);
+                double f[4];
+                f[0] = P[1];
+                f[1] = fma(P[1], un, p) - tau.xx;
+                f[2] = fma(P[2], un, -tau.xy);
+                f[3] = fma(P[3] + p, un, -fma(tau.xx, un, fma(tau.xy, ut, K.gPr * mu * sg[4])));
+#pragma unroll
+                for (int c = 0; c < 4; ++c) vfs[c] = fma(w, f[c], vfs[c]);
+            }
         }
-        if (o < 6) {
-            const int p = b * 6 + o;
-            double dc[3];
-            if (b == 0) stress_combos<0>(sg, dc);
-            else stress_combos<1>(sg, dc);
+    };
 #pragma unroll
-            for (int z = 0; z < 3; ++z) g.gf[(p * 3 + z) * N + cell] = dc[z];
-        } else {
-            const int q = o - 6;
-            const double w = (q / 3 == 1 ? GW1 : GW0) * (q % 3 == 1 ? GW1 : GW0);
-            double f[4];
-            flux2_dir<VarMu>(K, P[s4], sg, b == 1, f);
+    for (int dir = 0; dir < 2; ++dir) {
+        double da[9], db[9];
+        if (dir == 1) __syncthreads();   // the normal derivatives have been read
 #pragma unroll
-            for (int c = 0; c < 4; ++c) vfs[c] += w * f[c];
+        for (int kk = 0; kk < 2; ++kk) {
+            const double* C = kk == 0 ? Ca : Cb;
+            double* X = shd + kk * XD + b * (XD / 2) + lane;
+            double* d = kk == 0 ? da : db;
+            double D[15], w[9];
+            if (dir == 0) dxi_coeffs(C, D);
+            else deta_coeffs(C, D);
+            if (hh == 0) {
+                eval_xface(D, d);
+                eval_vol(D, w);
+#pragma unroll
+                for (int q = 0; q < 9; ++q) X[q * 64] = w[q];
+            } else {
+                eval_xface(D, w);
+                eval_vol(D, d);
+#pragma unroll
+                for (int q = 0; q < 6; ++q) X[(9 + q) * 64] = w[q];
+            }
         }
+        __syncthreads();
+        if (hh == 0) gradients(face, dir, da, db);
+        else gradients(vol, dir, da, db);
     }
-    __syncthreads();
+    if (hh == 1 && inter) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) sh[(bk * 16 + c) * RC_CELLS + cl] = vfs[c];
-    __syncthreads();
-    if (inter && k == 0) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            double acc = 0.0;
-#pragma unroll
-            for (int f = 0; f < 4; ++f) acc += sh[((b * 4 + f) * 16 + c) * RC_CELLS + cl];
-            g.vf[(b * 4 + c) * N + cell] = acc;
-        }
+        for (int c = 0; c < 4; ++c) at(g.vf + (b * 4 + gc[c]) * N, off) = vfs[c];
     }
-    // the block reductions use moment slots of the exchange: past the
-    // barriers above, no thread reads or writes them any more
-    red_max<8 * RC_CELLS>(&g.red->alpha_key, amax, red);
-    red_add<8 * RC_CELLS>(&g.red->pp_cells,
-                          (inter && bk == 0 && (th1 < 1.0 || th2 < 1.0)) ? 1ull : 0ull,
-                          reinterpret_cast<unsigned long long*>(red + 8));
 }
 
 // ---------------------------------------------------------------------------
@@ -2142,10 +2135,9 @@ void batch_blocks(const Grid2* hg, int n, const Tiles& t, int* out) {
             switch (k) {
                 case KB_GHOST: work = (long long)(g.ny + g.NX) * 2 * HALO; break;
                 case KB_RECON:   // tiles of t.recon x (64 / t.recon) cells, aligned to
-                                 // ghosted columns; HWENO-DR: row segments of t.recon cells
-                    work = g.K.dr ? (long long)(g.NY - 2) * ((g.NX - 2 + t.recon - 1) / t.recon)
-                                  : (long long)((g.NX - 1 + t.recon - 1) / t.recon) *
-                                        ((g.NY - 2 + 64 / t.recon - 1) / (64 / t.recon));
+                                 // ghosted columns
+                    work = (long long)((g.NX - 1 + t.recon - 1) / t.recon) *
+                           ((g.NY - 2 + 64 / t.recon - 1) / (64 / t.recon));
                     per = 1;
                     break;
                 case KB_RBAR:    // tiles of RB_TX x RB_TY cells, aligned to ghosted columns
@@ -2281,18 +2273,25 @@ void launch_rgrad2(const BatchL& b, hipStream_t st, Timer* tm) {
                 b.arg(KB_RGRAD));
 }
 
+template <int TX>
+void launch_recon2_dr(const BatchL& b, int si, bool alpha, int gst, const double* U,
+                      hipStream_t st, Timer* tm) {
+    auto launch = [&](auto f) {
+        tlaunch(tm, KC_RECON, f, b.blocks(KB_RECON), 256, st, b.arg(KB_RECON), si, (int)alpha, gst,
+                U);
+    };
+    if (gst == GHOSTS_FILLED)
+        launch(b.var_mu ? k_recon2_dr<TX, true, false> : k_recon2_dr<TX, false, false>);
+    else
+        launch(b.var_mu ? k_recon2_dr<TX, true, true> : k_recon2_dr<TX, false, true>);
+}
+
 hipError_t launch_residual2(const BatchL& b, int si, int gst, hipStream_t st, Timer* tm, bool alpha,
                             const double* U) {
-    const unsigned nr = b.blocks(KB_RECON), ng = b.blocks(KB_GRAD);
-    const Batch ar = b.arg(KB_RECON);
+    const unsigned ng = b.blocks(KB_GRAD);
     if (b.dr) {   // HWENO-DR: gradients and volume fluxes come with the reconstruction
-        if (b.tiles.recon == 16) {
-            if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2_dr<16, true>, nr, 128, st, ar, si);
-            else tlaunch(tm, KC_RECON, k_recon2_dr<16, false>, nr, 128, st, ar, si);
-        } else {
-            if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2_dr<32, true>, nr, 256, st, ar, si);
-            else tlaunch(tm, KC_RECON, k_recon2_dr<32, false>, nr, 256, st, ar, si);
-        }
+        if (b.tiles.recon == 16) launch_recon2_dr<16>(b, si, alpha, gst, U, st, tm);
+        else launch_recon2_dr<32>(b, si, alpha, gst, U, st, tm);
     } else if (b.tiles.recon == 16) {
         launch_recon2<16>(b, si, alpha, gst, U, st, tm);
     } else {

@@ -421,13 +421,6 @@ __device__ __forceinline__ void project2_rowbar(const double* T0, const double* 
                      ab[13 + e] * T0[TB::off(2 * e + 1) + (TB::mt + cm[c]) * AT_P];
 }
 
-// A wavefront's half: its points and the slots of the exchange it owns (the face
-// points and the moment, or the volume points).
-template <int h>
-struct Part {
-    static constexpr int value = h, points = h ? 9 : 6, slots = h ? 9 : 7;
-};
-
 // Add v to an LDS word: no other wavefront touches it in this phase and the lanes
 // of one call have words of their own, so the sums have the program's order.
 __device__ __forceinline__ void lds_add(double* p, double v) {

@@ -46,6 +46,13 @@ __device__ __forceinline__ void field_rows(const Basis2& e, int k, double* L, do
     }
 }
 
+// A wavefront's half: its points and the slots of the exchange it owns (the face
+// points and the moment, or the volume points).
+template <int h>
+struct Part {
+    static constexpr int value = h, points = h ? 9 : 6, slots = h ? 9 : 7;
+};
+
 // The 17 stencil data of the field with left eigenvector L: sh holds 12
 // fields of PL doubles, rows of TW; basis b's normal direction is x (b = 0)
 // or y (b = 1).

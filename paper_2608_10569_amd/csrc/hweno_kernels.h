@@ -220,8 +220,7 @@ struct Batch {
 
 // Work per block of the tunable kernels (cells, cells, faces).
 struct Tiles {
-    int recon = 32;   // 16 or 32 (columns of the reconstruction's 64-cell tiles; HWENO-DR:
-                      // cells per block)
+    int recon = 32;   // 16 or 32 (columns of the reconstruction's 64-cell tiles)
     int grad = 32;    // the reverse mode's gradient kernel: 64, else 32 cells per block
     int flux = 0;     // 64 or 128; 0: face fluxes formed inside the update kernel
     int xcd = 1;      // 1: each XCD takes a contiguous range of a launch's blocks
@@ -237,6 +236,7 @@ constexpr int GHOSTS_FILLED = -2;
 // 256x256 (1161 blocks) 241 and 233, 400x400 (2639) 404 and 407, 512x512 690
 // and 699, 1000x500 1317 and 1340: the index arithmetic of every tile costs
 // the reconstruction 3 us at 64x64 and 15 of 136 at 1000x500.
+// HWENO-DR alike: four steps of 500x250 (2032 blocks) 1318 and 1290 us.
 constexpr unsigned GHOST_MAX_BLOCKS = 2048;
 
 struct BatchL {
@@ -261,9 +261,9 @@ struct BatchL {
         return Batch{dg, dstart + k * (n + 1), n, tiles.xcd, (int)((rev >> k) & 1u)};
     }
     unsigned blocks(int k) const { return (unsigned)hstart[k * (n + 1) + n]; }
-    // HWENO-DR and the reverse mode (which reads them) need filled ghost cells
+    // the reverse mode (which reads them) needs filled ghost cells
     bool forms_ghosts() const {
-        return !dr && !full_grad && blocks(KB_RECON) <= GHOST_MAX_BLOCKS;
+        return !full_grad && blocks(KB_RECON) <= GHOST_MAX_BLOCKS;
     }
 };
 
