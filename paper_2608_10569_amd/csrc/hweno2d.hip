@@ -441,7 +441,9 @@ __device__ __forceinline__ void load_tile(const Grid2& g, const Grid2& gsrc, int
 // us, but 12.1 us on 64^2.  Four wavefronts per SIMD instead of three spill
 // (193 us).
 // ---------------------------------------------------------------------------
-template <int TX, bool VarMu, bool FULL, bool GH>
+// FULL: 0, or the reverse mode's 1 (the full volume values as well) and 2 (these
+// alone, where no residual is formed from them).
+template <int TX, bool VarMu, int FULL, bool GH>
 __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_alpha, int gst,
                                                  const double* U) {
     constexpr int TY = 64 / TX, TW = TX + 2, TH = TY + 2, PL = TW * TH;
@@ -574,13 +576,15 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
             const double p = K.gm1 * fma(-0.5, fma(u[1], un, u[2] * ut), u[3]);
             rmin = fmin(rmin, u[0]);
             pmin = fmin(pmin, p);
-            fs[0] = fma(w, u[1], fs[0]);
-            fs[1] = fma(w, fma(u[1], un, p), fs[1]);
-            fs[2] = fma(w, u[2] * un, fs[2]);
-            fs[3] = fma(w, (u[3] + p) * un, fs[3]);
-            at(VC + ((b ? 13 : 4) + gq(q)) * N, off) = un;
-            at(VC + ((b ? 4 : 13) + gq(q)) * N, off) = ut;
-            if constexpr (VarMu) at(VC + (22 + gq(q)) * N, off) = (p / u[0]) / K.T_ref;
+            if constexpr (FULL != 2) {
+                fs[0] = fma(w, u[1], fs[0]);
+                fs[1] = fma(w, fma(u[1], un, p), fs[1]);
+                fs[2] = fma(w, u[2] * un, fs[2]);
+                fs[3] = fma(w, (u[3] + p) * un, fs[3]);
+                at(VC + ((b ? 13 : 4) + gq(q)) * N, off) = un;
+                at(VC + ((b ? 4 : 13) + gq(q)) * N, off) = ut;
+                if constexpr (VarMu) at(VC + (22 + gq(q)) * N, off) = (p / u[0]) / K.T_ref;
+            }
             if constexpr (FULL) {   // the reverse mode reads the full volume values
                 gdouble* V = b ? g.yv : g.xv;
 #pragma unroll
@@ -591,8 +595,10 @@ __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_al
         at(WB + b * N, off) = sn;
         at(WB + (1 - b) * N, off) = st;
         at(WB + 2 * N, off) = se;
+        if constexpr (FULL != 2) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) at(VC + gc[c] * N, off) = fs[c];
+            for (int c = 0; c < 4; ++c) at(VC + gc[c] * N, off) = fs[c];
+        }
     }
     // positivity limiter: theta1 from the least density, theta2 from the least
     // pressure over the points of both bases ((pbar - eps) / (pbar - p) falls
@@ -1146,7 +1152,7 @@ __device__ __forceinline__ void swap_halves(double& x, double& y) {
 // the volume flux.  k: the wavefront's pair (uniform); g3: which three
 // wavefronts of the block; shm: NC / 32 * (3 * 64 (+ GW_MU)) doubles of LDS.
 // Every thread of the block calls it (it holds barriers).
-template <bool VarMu, bool FULL>
+template <bool VarMu, bool FULL, bool SUMS = true>
 __device__ __forceinline__ void grad_body(const Grid2& g, double* shm, const double* a, int k,
                                           bool valid, int j, int i) {
 #pragma clang fp contract(off)
@@ -1160,7 +1166,8 @@ __device__ __forceinline__ void grad_body(const Grid2& g, double* shm, const dou
     // the normal stress, tangential for the shear, gamma / Pr for e
     gdouble* VC = g.vc + (hi ? VC_B : 0) * N;
     double pv[9];
-    if (k < 2) {
+    if constexpr (!SUMS) {
+    } else if (k < 2) {
         gdouble* VV = VC + ((k ^ hi) == 0 ? 4 : 13) * N;
 #pragma unroll
         for (int q = 0; q < 9; ++q) pv[q] = at(VV + q * N, off);
@@ -1184,6 +1191,7 @@ __device__ __forceinline__ void grad_body(const Grid2& g, double* shm, const dou
             }
         }
     }
+    if constexpr (!SUMS) return;
     // the pair's combination from the values of the lane's own direction and
     // the other one (stress_combos)
     const double co = k == 0 ? 4.0 / 3.0 : 1.0, ct = k == 0 ? -(2.0 / 3.0) : 1.0;
@@ -1239,7 +1247,8 @@ __device__ __forceinline__ void grad_body(const Grid2& g, double* shm, const dou
 
 // The gradient kernel of the reverse mode, which reads the weak moments itself
 // (k_rbar2 leaves them in memory) and all six gradients: GR_CELLS cells per block.
-template <int GR_CELLS, bool VarMu>
+// SUMS: the volume-flux quadratures too, from which a residual is formed.
+template <int GR_CELLS, bool VarMu, bool SUMS>
 __global__ __launch_bounds__(6 * GR_CELLS) void k_grad2(Batch bt) {
     constexpr int SH = 3 * 64 + (VarMu ? GW_MU : 0);
     __shared__ double shm[GR_CELLS / 32 * SH];
@@ -1271,7 +1280,7 @@ __global__ __launch_bounds__(6 * GR_CELLS) void k_grad2(Batch bt) {
         a[9 + e] = at(R + N, nb);
         a[13 + e] = at(R + 2 * N, nb);
     }
-    grad_body<VarMu, true>(g, shm + wv / 3 * SH, a, k, valid, j, i);
+    grad_body<VarMu, true, SUMS>(g, shm + wv / 3 * SH, a, k, valid, j, i);
 }
 
 // ---------------------------------------------------------------------------
@@ -2251,16 +2260,11 @@ void launch_recon2(const BatchL& b, int si, int alpha, int gst, const double* U,
                    Timer* tm) {
     const unsigned n = b.blocks(KB_RECON);
     const Batch a = b.arg(KB_RECON);
-    if (b.full_grad) {
-        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, true, false>, n, 256, st, a, si, alpha, gst, U);
-        else tlaunch(tm, KC_RECON, k_recon2<TX, false, true, false>, n, 256, st, a, si, alpha, gst, U);
-    } else if (gst == GHOSTS_FILLED) {
-        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, false, false>, n, 256, st, a, si, alpha, gst, U);
-        else tlaunch(tm, KC_RECON, k_recon2<TX, false, false, false>, n, 256, st, a, si, alpha, gst, U);
-    } else {
-        if (b.var_mu) tlaunch(tm, KC_RECON, k_recon2<TX, true, false, true>, n, 256, st, a, si, alpha, gst, U);
-        else tlaunch(tm, KC_RECON, k_recon2<TX, false, false, true>, n, 256, st, a, si, alpha, gst, U);
-    }
+    auto launch = [&](auto f) { tlaunch(tm, KC_RECON, f, n, 256, st, a, si, alpha, gst, U); };
+    if (b.full_grad && !b.sums) launch(k_recon2<TX, false, 2, false>);
+    else if (b.full_grad) launch(b.var_mu ? k_recon2<TX, true, 1, false> : k_recon2<TX, false, 1, false>);
+    else if (gst == GHOSTS_FILLED) launch(b.var_mu ? k_recon2<TX, true, 0, false> : k_recon2<TX, false, 0, false>);
+    else launch(b.var_mu ? k_recon2<TX, true, 0, true> : k_recon2<TX, false, 0, true>);
 }
 
 template <bool VarMu>
@@ -2302,14 +2306,17 @@ hipError_t launch_residual2(const BatchL& b, int si, int gst, hipStream_t st, Ti
         else launch_rgrad2<false>(b, st, tm);
     } else if (!b.dr) {   // the reverse mode reads the weak moments and all six gradients
         tlaunch(tm, KC_RBAR, k_rbar2, b.blocks(KB_RBAR), RB_TX * RB_TY, st, b.arg(KB_RBAR));
-        const Batch ag = b.arg(KB_GRAD);
+        auto launch = [&](auto f, unsigned threads) {
+            tlaunch(tm, KC_GRAD, f, ng, threads, st, b.arg(KB_GRAD));
+        };
         if (b.tiles.grad == 64) {
-            if (b.var_mu) tlaunch(tm, KC_GRAD, k_grad2<64, true>, ng, 384, st, ag);
-            else tlaunch(tm, KC_GRAD, k_grad2<64, false>, ng, 384, st, ag);
+            if (!b.sums) launch(k_grad2<64, false, false>, 384);
+            else launch(b.var_mu ? k_grad2<64, true, true> : k_grad2<64, false, true>, 384);
         } else {
-            if (b.var_mu) tlaunch(tm, KC_GRAD, k_grad2<32, true>, ng, 192, st, ag);
-            else tlaunch(tm, KC_GRAD, k_grad2<32, false>, ng, 192, st, ag);
+            if (!b.sums) launch(k_grad2<32, false, false>, 192);
+            else launch(b.var_mu ? k_grad2<32, true, true> : k_grad2<32, false, true>, 192);
         }
+        if (!b.sums) return hipGetLastError();
     }
     if (b.tiles.flux == 0) return hipGetLastError();   // fluxes formed by the update kernel
     tbeg(tm, KC_FLUX, st);

@@ -1559,6 +1559,7 @@ HWENO_API hweno_status hweno_residual_vjp(hweno_ctx* c, const double* U, const d
     const hw::Grid2& g = g2(c);
     hw::BatchL full = c->bl;   // the adjoint kernels read all six face gradients
     full.full_grad = true;
+    full.sums = false;         // and no residual is formed
     TRY(dev(hw::launch_copy_in2(g, U, g.S[2], c->stream)));
     TRY(reset(c));
     TRY(ghost(c, 2));
@@ -1643,9 +1644,11 @@ HWENO_API hweno_status hweno_rk_step_vjp(hweno_ctx* c, const double* U0, double 
                       const double* Rb, const double* Vb, double rs, double vs, double* out,
                       int acc, const double* add, double add_a, const double* pass) {
         if (form) {
+            hw::BatchL bl = *bi;
+            bl.sums = false;   // no residual is formed from these
             TRY(reset(c));
             TRY(ghost(c, si));
-            TRY(residual(c, si, bi));
+            TRY(residual(c, si, &bl));
         }
         hw::AdjIn A{Rb, Vb, rs, vs};
         return dev(hw::launch_vjp2(gi, A, c->adj, g.S[si], out, c->mu_dev, acc, c->stream, add,

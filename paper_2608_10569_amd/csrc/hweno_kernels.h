@@ -250,6 +250,10 @@ struct BatchL {
     bool full_grad = false;        // face gradients stored as all six (the reverse mode
                                    // reads them); else as the three combinations the
                                    // face fluxes use
+    // full_grad: the volume-flux sums and face fluxes are wanted; false where an
+    // adjoint alone reads the intermediates (96 planes less through memory: the
+    // gradient kernel of a 256x256 residual adjoint 20 -> 15 us, the call 349 -> 340)
+    bool sums = true;
     // bit k: kernel class k runs its blocks last first.  The weak-moment and
     // face-flux kernels run in the opposite order of the kernel that wrote
     // most of their input just before them (reconstruction, gradients), so
