@@ -56,25 +56,23 @@ PEAK_HBM_GBS = 8000.0
 #          135, moment 5) = 4648; characteristic bases 75; back-transform 1024;
 #          limiter on 30 points 420; wbar 240; wave speed 300; convective
 #          volume fluxes and their Gauss sums at 18 points 342.
-#   grad:  6 scalar reconstructions at 21 points (495 each) = 2970; viscous
-#          volume fluxes at 18 points and the sums 458.
-#   rbar:  interface averages, face moments, 18 weak moments.
+#   grad:  interface averages, face moments and 18 weak moments 414; 6 scalar
+#          reconstructions at 21 points (495 each) = 2970; viscous volume fluxes
+#          at 18 points and the sums 458.
 #   flux:  per face 6 point fluxes and PP speed bounds, 12 LF combinations.
 #   update: assembly of 12 residual entries and the stage combination.
 #   fluxup: the face fluxes formed inside the update kernel, per cell: the
 #          fluxes of two faces and the update (faces on tile edges, formed
 #          twice, counted once).
-FLOPS = {'recon': 7049, 'grad': 3428, 'rbar': 414, 'flux': 560, 'update': 400,
+FLOPS = {'recon': 7049, 'grad': 3842, 'flux': 560, 'update': 400,
          'fluxup': 2 * 560 + 400}
 # HBM bytes per launch from rocprofv3 FETCH_SIZE and WRITE_SIZE (KiB per
 # dispatch) scaled by the factors a 1 GiB device copy gives in the same process
 # (FETCH x 2.0, WRITE x 1.0), per kernel class and tile variant, on this grid
 # and for the kernels as they are now: e.g. recon with 32-cell tiles reads
-# 50.9 MB and writes 432.1 MB per launch.
-TRAFFIC_BYTES = {('recon', 16): 485727236, ('recon', 32): 483043051,
-                 ('grad', 32): 432885712, ('grad', 64): 431268299, ('grad', 0): 715273789,
-                 ('rbar', None): 315149506, ('update', None): 227677481,
-                 ('fluxup', None): 618245338}
+# 55.8 MB and writes 439.9 MB per launch.
+TRAFFIC_BYTES = {('recon', 32): 495675392, ('grad', None): 667913216,
+                 ('fluxup', None): 617230336}
 # Algorithmic HBM bytes per cell-stage of the whole path if every input were
 # read once and every output written once (stage average: 256 B residual
 # in/out + the RK bases of stages 2 and 3).
@@ -87,9 +85,7 @@ def pipeline_hbm(tiles, value):
     the rate they imply at the measured throughput."""
     if tiles.get('flux') != 0:   # split face-flux kernels have no entry in the table
         return None
-    parts = [('recon', tiles.get('recon')), ('grad', tiles.get('grad')), ('fluxup', None)]
-    if tiles.get('grad') != 0:   # the fused gradient kernel forms the weak moments itself
-        parts.append(('rbar', None))
+    parts = [('recon', tiles.get('recon')), ('grad', None), ('fluxup', None)]
     if any(p not in TRAFFIC_BYTES for p in parts):
         return None
     per_cell = sum(TRAFFIC_BYTES[p] for p in parts) / (NX * NY)
@@ -107,8 +103,6 @@ def log(msg):
 def units_per_launch(kind):
     if kind == 'recon':
         return (NX + 6) * (NY + 6)
-    if kind == 'rbar':
-        return (NX + 4) * (NY + 4)
     if kind == 'grad':
         return (NX + 2) * (NY + 2)
     if kind == 'flux':
@@ -514,8 +508,9 @@ def main():
     kern = {k: {'ms_total': round(v[0], 3), 'launches': v[1],
                 'us_avg': round(1e3 * v[0] / v[1], 2) if v[1] else None}
             for k, v in tm.items()}
-    path_flops = (FLOPS['recon'] + FLOPS['grad'] + FLOPS['rbar'] + FLOPS['update']
-                  + 2 * FLOPS['flux'])
+    # the roof the kernel is nearer to: its FP64 work or the bytes it moves
+    mem = bool(traffic) and traffic / avg_s / (PEAK_HBM_GBS * 1e9) > achieved / PEAK_FP64_TFLOPS
+    path_flops = FLOPS['recon'] + FLOPS['grad'] + FLOPS['update'] + 2 * FLOPS['flux']
     out = {
         'metric': METRIC, 'value': value, 'unit': UNIT, 'n_gpus': 1,
         'steps': args.steps, 'warmup': args.warmup, 'ms_per_step': 1e3 * el / args.steps,
@@ -525,9 +520,13 @@ def main():
                                'symmetry top, SSP-RK3 CFL 0.3 from t=0, paper dt rule',
                    'cells': NX * NY, 'stages_per_step': 3, 't_end': t_end,
                    'restarts': restarts, 'pp_cell_stages': pp, 'tiles': tiles},
-        'roofline': {'bound': 'alu', 'kernel': dom, 'achieved': achieved,
-                     'peak': PEAK_FP64_TFLOPS, 'unit': 'TFLOP/s',
-                     'frac': achieved / PEAK_FP64_TFLOPS,
+        'roofline': {'bound': 'hbm' if mem else 'alu', 'kernel': dom,
+                     'achieved': traffic / avg_s / 1e9 if mem else achieved,
+                     'peak': PEAK_HBM_GBS if mem else PEAK_FP64_TFLOPS,
+                     'unit': 'GB/s' if mem else 'TFLOP/s',
+                     'frac': traffic / avg_s / (PEAK_HBM_GBS * 1e9) if mem
+                     else achieved / PEAK_FP64_TFLOPS,
+                     'fp64_tflops': achieved,
                      'traffic': traffic,
                      'traffic_unit': 'HBM bytes per launch (rocprofv3 counters, calibrated)',
                      'traffic_gbs': traffic / avg_s / 1e9 if traffic else None,

@@ -442,7 +442,7 @@ HWENO_API hweno_status hweno_batch_get_diag(hweno_ctx* ctx, int i, hweno_diag* o
 /* Work per block of the tunable kernels and the instance order of a launch. */
 typedef struct hweno_tiles {
     int recon;      /* columns of the characteristic reconstruction's 64-cell tiles: 16
-                       (tiles of 16 x 4 cells) or 32 (32 x 2); HWENO-DR: cells per block */
+                       (tiles of 16 x 4 cells) or 32 (32 x 2) */
     int grad;       /* cells per block of the gradient reconstruction in the reverse
                        mode's forward launches, which leave the weak moments (eqs.
                        3.6-3.8) in memory for the adjoint: 64, or 32 (also for 0).

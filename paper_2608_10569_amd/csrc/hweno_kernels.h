@@ -31,7 +31,7 @@ struct Reduce {
     unsigned long long min_p_key;     // min cell-average pressure
     unsigned int bad[4];              // inadmissible cells per stage (index 1..3)
     double dt;                        // step size used by the update kernels
-    unsigned long long alpha1_key;    // alpha of the stage-1 reconstruction (copied by k_dt)
+    unsigned long long alpha1_key;    // alpha of the stage-1 reconstruction, kept for the diagnostics
     double pad[2];
 };
 
