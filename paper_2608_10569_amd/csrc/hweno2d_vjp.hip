@@ -6,7 +6,7 @@
 // The forward pipeline is recomputed first (its intermediates stay in the
 // workspace); the adjoint kernels then run in reverse order.  Every adjoint
 // slot has exactly one writer and cross-cell sums are gathers in a fixed
-// order, so the result is deterministic (no floating-point atomics).
+// order, so the result is deterministic.
 // Branches (limiter thetas, LF-speed maximum, |.| in the weights) follow the
 // forward point; ties go to the lowest index in the order of the oracle.
 //
@@ -379,15 +379,17 @@ __device__ __forceinline__ bool in_ring2(const Grid2& g, int j, int i) {
 // the scalar reconstruction.  The stencil shares of the tile's cells are summed
 // in LDS: in each of four phases a wavefront adds its share of one conserved
 // component, so every sum has a fixed order, and the tile with its ring of one
-// cell (25.5 doubles per cell) goes to the workspace for k_adj_out.
+// cell (20 doubles per cell) goes to the workspace for k_adj_out.
 // Bound: the latency of two wavefronts per SIMD (256 registers, about 6000
 // instructions each).  A thread per field in two kernels, which exchanged the
 // point values through LDS and 160 cotangents per cell through memory, a
 // weak-moment kernel that read and wrote all point cotangents (360 doubles per
 // cell) and a gather of 136 stencil shares per cell took 77 + 92 + 48 + 18 us on
-// 256 x 256; this kernel takes 102 - 110.
+// 256 x 256; this kernel takes 100.  Tiles of 32 x 2 cells (a twelfth of their cells
+// outside the grid there, 5 % more blocks) take 108, 8 x 8 112; 240 x 200: 71, 75
+// and 81 us, 64 x 64: 27.8, 29.1 and 30.9.
 // ---------------------------------------------------------------------------
-constexpr int AT_X = 32, AT_Y = 2, AT_W = AT_X + 2, AT_H = AT_Y + 2, AT_P = AT_W * AT_H;
+constexpr int AT_X = 16, AT_Y = 4, AT_W = AT_X + 2, AT_H = AT_Y + 2, AT_P = AT_W * AT_H;
 
 inline __host__ __device__ int at_tiles_x(const Grid2& g) { return (g.NX - 1 + AT_X - 1) / AT_X; }
 inline __host__ __device__ int at_tiles_y(const Grid2& g) { return (g.NY - 2 + AT_Y - 1) / AT_Y; }
@@ -932,7 +934,7 @@ __device__ __forceinline__ double state_bar(const Grid2& g, const AdjWs& W, int 
 #pragma unroll
     for (int d = 1; d >= 0; --d) {
         const int ty = t1 - d;
-        if (ty < 0 || ty >= nty) continue;
+        if (ty < 0 || ty >= nty || (d && j % AT_Y >= 2)) continue;
         const double* R = W.uc + ((long long)ty * ntx * 12 + q) * AT_P + (j % AT_Y + AT_Y * d) * AT_W;
         auto T = [&](int tx) { return R[(long long)tx * (12 * AT_P) + i - tx * AT_X + 1]; };
         if (xr == 0 && x1 > 0) v += T(x1 - 1);
@@ -941,7 +943,7 @@ __device__ __forceinline__ double state_bar(const Grid2& g, const AdjWs& W, int 
     }
     return v;
 }
-static_assert(AT_Y == 2, "state_bar: a row lies in two tiles");
+static_assert(AT_Y >= 2, "state_bar: a row lies in at most two tiles");
 
 // ---------------------------------------------------------------------------
 // Adjoint of the ghost fill: the y sweep is undone first (its sources include

@@ -1,5 +1,6 @@
-"""Residual adjoint at the edges of its tiles of 32 x 2 cells on the ghosted grid:
-the ghosted width one short of, at and past a multiple of 32, odd heights and
+"""Residual adjoint at the edges of its tiles of 16 x 4 cells on the ghosted grid:
+the ghosted width one short of, at and past a multiple of 16, heights of every
+remainder and
 the smallest grid.  Oracle and bound are those of
 the dot-product test (double rounding of a sum over the grid)."""
 
