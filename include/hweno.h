@@ -387,7 +387,9 @@ typedef struct hweno_timing {
  * 0 stops recording; events are created on first use).  Each recorded launch
  * adds two event records to the stream, so time a long run with the classes
  * of interest only.  At most 1024 launches are recorded between two reads of
- * the totals (rk_step reads them at the end of every step). */
+ * the totals; every single-grid call that waits for a result of its own (a step,
+ * a residual with a diag, an adjoint with a mu_bar) reads them, as do
+ * hweno_batch_run and hweno_get_timing. */
 HWENO_API hweno_status hweno_set_timing(hweno_ctx* ctx, int enable);
 
 /* Synchronises the stream, returns the totals; reset != 0 zeroes them. */

@@ -744,6 +744,7 @@ hweno_status fetch(hweno_ctx* c, void* out, const void* src, size_t bytes) {
     TRY(dev(hipMemcpyAsync(to, src, bytes, hipMemcpyDeviceToHost, c->stream)));
     TRY(dev(hipStreamSynchronize(c->stream)));
     if (to != out) std::memcpy(out, to, bytes);
+    if (c->timer.on) c->timer.collect();   // its pool is bounded
     return HWENO_OK;
 }
 
