@@ -28,9 +28,11 @@
  *    caller owns every pointer it passes; the library keeps none after a
  *    call returns, except the workspace given to hweno_set_workspace.
  *  - The library allocates no device memory.  All scratch lives in a
- *    caller-provided workspace of hweno_workspace_bytes() bytes.  A single
- *    grid's context keeps one page of pinned host memory from its first
- *    hweno_set_workspace to hweno_destroy.
+ *    caller-provided workspace of hweno_workspace_bytes() bytes.  The first
+ *    hweno_set_workspace of a single grid allocates 256 KiB of pinned host
+ *    memory for the library, kept from then on; up to 1024 single-grid
+ *    contexts at a time receive their results through it, from that call to
+ *    hweno_destroy (others in pageable memory, a few us slower).
  *  - Calls are ordered on the HIP stream set with hweno_set_stream (default:
  *    the null stream).  hweno_rk_step and hweno_residual with a non-NULL
  *    diag synchronise that stream once; other calls are asynchronous.

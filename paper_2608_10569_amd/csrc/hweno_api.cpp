@@ -10,6 +10,7 @@
 #include <cstdint>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <utility>
 #include <vector>
@@ -63,9 +64,11 @@ struct hweno_ctx {
     // the reverse mode's recomputed stages
     double* S1[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     hw::Grid1 g1{};
-    // landing place of result copies (PINNED bytes of pinned host memory, from
-    // the first hweno_set_workspace; null: copies go to the caller's memory)
+    // landing place of result copies (a slot of pinned host memory, from the
+    // first hweno_set_workspace; null: copies go to the caller's memory), and
+    // whether a copy into it may still be on its way (its wait failed)
     void* pinned = nullptr;
+    bool pinned_late = false;
     // reduction slots red[1 + k] of a single grid's steps (2D: through the
     // descriptors dg[1 + k]), used in turn: a step resets the slots of the
     // next (red_clean[k]: they are reset)
@@ -135,7 +138,6 @@ struct hweno_ctx {
 namespace {
 
 constexpr int HALO = 4;
-constexpr size_t PINNED = sizeof(hw::Reduce) > 256 ? sizeof(hw::Reduce) : 256;
 constexpr size_t ALIGN = 256;
 
 size_t up(size_t n) { return (n + ALIGN - 1) / ALIGN * ALIGN; }
@@ -722,27 +724,63 @@ hweno_status reset(hweno_ctx* c) {
     return dev(hw::launch_reset(c->red, c->stream));
 }
 
-// Allocate or free a context's pinned buffer.  Neither call touches a stream, so
-// a capture that is open on one meanwhile goes on (relaxed capture mode).
-void pinned_swap(void** p, bool alloc) {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-    void* q = *p;
-    *p = nullptr;   // copies go to the caller's memory without one
-    if ((alloc ? hipHostMalloc(p, PINNED, hipHostMallocPortable) : hipHostFree(q)) != hipSuccess) {
-        *p = nullptr;
-        (void)hipGetLastError();
+// Pinned host memory that results are copied through: one allocation of 256 KiB,
+// made for the first context that asks and kept from then on, in slots that
+// contexts take and give back.  A page per context, freed with it, made
+// hweno_destroy wait for all work on the device (215 ms behind 400 ms of another
+// stream's kernels, 2 us without).  A context that finds every slot taken copies to
+// the caller's memory.
+class PinnedSlots {
+public:
+    static constexpr size_t SLOT = 256;
+    static constexpr int SLOTS = 1024;
+    void* take() {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (!base_ && !allocate()) return nullptr;
+        for (int k = 0; k < SLOTS; ++k) {
+            if (taken_[k]) continue;
+            taken_[k] = true;
+            return base_ + k * SLOT;
+        }
+        return nullptr;
     }
-    if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
-}
+    void give(void* p) {
+        std::lock_guard<std::mutex> lock(mu_);
+        taken_[(static_cast<char*>(p) - base_) / SLOT] = false;
+    }
 
-// Copy a result of `bytes` (at most PINNED) to the host and wait for it, by
-// way of the context's pinned buffer: three small kernels and the copy take
+private:
+    // The allocation touches no stream, so a capture that is open on one
+    // meanwhile goes on (relaxed capture mode).
+    bool allocate() {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void* p = nullptr;
+        if (hipHostMalloc(&p, SLOT * SLOTS, hipHostMallocPortable) != hipSuccess) {
+            p = nullptr;
+            (void)hipGetLastError();
+        }
+        if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        base_ = static_cast<char*>(p);
+        return p != nullptr;
+    }
+    std::mutex mu_;
+    char* base_ = nullptr;
+    bool taken_[SLOTS] = {};
+};
+static_assert(sizeof(hw::Reduce) <= PinnedSlots::SLOT, "a result fits a slot");
+
+PinnedSlots pinned_slots;
+
+// Copy a result of `bytes` (at most a slot) to the host and wait for it, by
+// way of the context's pinned slot: three small kernels and the copy take
 // 18.5 us with it and 26.7 us to pageable memory.
 hweno_status fetch(hweno_ctx* c, void* out, const void* src, size_t bytes) {
     void* to = c->pinned ? c->pinned : out;
     TRY(dev(hipMemcpyAsync(to, src, bytes, hipMemcpyDeviceToHost, c->stream)));
-    TRY(dev(hipStreamSynchronize(c->stream)));
+    const hweno_status s = dev(hipStreamSynchronize(c->stream));
+    c->pinned_late = s != HWENO_OK;
+    TRY(s);
     if (to != out) std::memcpy(out, to, bytes);
     if (c->timer.on) c->timer.collect();   // its pool is bounded
     return HWENO_OK;
@@ -969,7 +1007,7 @@ HWENO_API hweno_status hweno_destroy(hweno_ctx* c) {
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->cap_stream2) (void)hipStreamDestroy(c->cap_stream2);
     c->timer.destroy();
-    if (c->pinned) pinned_swap(&c->pinned, false);
+    if (c->pinned && !c->pinned_late) pinned_slots.give(c->pinned);
     delete c;
     return HWENO_OK;
     GUARD_END
@@ -988,7 +1026,7 @@ HWENO_API hweno_status hweno_set_workspace(hweno_ctx* c, void* p, size_t bytes) 
     if (!c || !p) return HWENO_E_INVAL;
     if (bytes < c->ws_bytes || (reinterpret_cast<uintptr_t>(p) % ALIGN) != 0)
         return HWENO_E_WORKSPACE;
-    if (!c->pinned && !c->batch) pinned_swap(&c->pinned, true);
+    if (!c->pinned && !c->batch) c->pinned = pinned_slots.take();
     c->ws = static_cast<char*>(p);
     layout(c, c->ws);
     c->has_state = false;
