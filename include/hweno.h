@@ -470,7 +470,8 @@ HWENO_API hweno_status hweno_set_tiles(hweno_ctx* ctx, const hweno_tiles* tiles)
  * the fastest per kernel (for the face fluxes: split or fused into the
  * update, by the time of fluxes plus update; grad stays as set), then the
  * faster block order and (batches) the faster instance order, and sets them;
- * `chosen` may be NULL.  Needs the state(s) set; leaves them unchanged.  Synchronises. */
+ * `chosen` may be NULL.  The launches are those of a step or, group by group, of
+ * a batched run.  Needs the state(s) set; leaves them unchanged.  Synchronises. */
 HWENO_API hweno_status hweno_autotune(hweno_ctx* ctx, int reps, hweno_tiles* chosen);
 
 #ifdef __cplusplus

@@ -636,11 +636,12 @@ hweno_status download_state(hweno_ctx* c) {
 
 hw::Grid2& g2(hweno_ctx* c) { return c->hg[0]; }
 
-hweno_status ghost(hweno_ctx* c, int si, int stage = -1) {
+// b: the 2D launch list to use; default the grid's (or the whole batch's)
+hweno_status ghost(hweno_ctx* c, int si, int stage = -1, const hw::BatchL* b = nullptr) {
     if (c->dim() == 2) {
         if (!c->batch && !c->sdst_host.empty())     // walls inside the grid first
             TRY(dev(hw::launch_solid2(c->dg, (int)c->sdst_host.size(), si, c->stream)));
-        return dev(hw::launch_ghost2(c->bl, si, c->stream, c->tm(), stage));
+        return dev(hw::launch_ghost2(b ? *b : c->bl, si, c->stream, c->tm(), stage));
     }
     return dev(hw::launch_ghost1(c->g1, c->S1[si], c->stream, c->tm()));
 }
@@ -654,25 +655,24 @@ hweno_status residual(hweno_ctx* c, int si, const hw::BatchL* b = nullptr) {
     return dev(hw::launch_residual1(c->g1, c->S1[si], c->stream, c->tm()));
 }
 
-// Whether a 2D residual's ghost cells are filled by a launch of their own (also
-// while that is timed) or formed in the reconstruction.
-bool fills_ghosts(hweno_ctx* c) {
+// Whether the ghost cells of a 2D residual through b are filled by a launch of
+// their own or formed in the reconstruction.  A caller who records the fill's
+// time gets the fill.
+bool fills_ghosts(hweno_ctx* c, const hw::BatchL& b) {
     const hw::Timer* tm = c->tm();
-    return !c->bl.forms_ghosts() || (tm && (tm->mask >> hw::KC_GHOST & 1u));
+    return !b.forms_ghosts() || (tm && (tm->mask >> hw::KC_GHOST & 1u));
 }
 
 // 2D residual at a state whose ghost cells are not filled (nor the walls inside
-// the grid).  alpha: the CFL wave speed is wanted.
-hweno_status eval2(hweno_ctx* c, int si, int stage = -1, bool alpha = true,
-                   const hw::BatchL* b = nullptr) {
-    hw::Timer* tm = c->tm();
-    if (fills_ghosts(c)) {
-        TRY(ghost(c, si, stage));
+// the grid).  alpha: the CFL wave speed is wanted; fill: fills_ghosts.
+hweno_status eval2(hweno_ctx* c, int si, int stage, bool alpha, const hw::BatchL& b, bool fill) {
+    if (fill) {
+        TRY(ghost(c, si, stage, &b));
         stage = hw::GHOSTS_FILLED;
     } else if (!c->batch && !c->sdst_host.empty()) {
         TRY(dev(hw::launch_solid2(c->dg, (int)c->sdst_host.size(), si, c->stream)));
     }
-    return dev(hw::launch_residual2(b ? *b : c->bl, si, stage, c->stream, tm, alpha));
+    return dev(hw::launch_residual2(b, si, stage, c->stream, c->tm(), alpha));
 }
 
 // 2D
@@ -1239,9 +1239,10 @@ HWENO_API hweno_status hweno_residual(hweno_ctx* c, const double* U, double* R, 
     if (!c->ws) return HWENO_E_WORKSPACE;
     if (c->dim() == 2) {
         TRY(reset(c));
-        if (fills_ghosts(c) || !c->sdst_host.empty()) {
+        const bool fill = fills_ghosts(c, c->bl);
+        if (fill || !c->sdst_host.empty()) {
             TRY(dev(hw::launch_copy_in2(g2(c), U, g2(c).S[2], c->stream)));
-            TRY(eval2(c, 2));
+            TRY(eval2(c, 2, -1, true, c->bl, fill));
         } else {
             TRY(dev(hw::launch_residual2(c->bl, 2, -1, c->stream, c->tm(), true, U)));
         }
@@ -1484,11 +1485,12 @@ hweno_status step(hweno_ctx* c, double dt, const double* const* src, hweno_diag*
             rl.t_left = t_left;
             rl.clear = c->red + 1 + (1 - k);
             if (check) TRY(dev(hw::launch_check2(bl, a, c->stream)));
-            TRY(eval2(c, a, staged ? 0 : -1, true, &bl));
+            const bool fill = fills_ghosts(c, bl);
+            TRY(eval2(c, a, staged ? 0 : -1, true, bl, fill));
             TRY(update(c, 1, a, a, b, nullptr, nullptr, src1, &bl, rl));
-            TRY(eval2(c, b, staged ? 1 : -1, false, &bl));
+            TRY(eval2(c, b, staged ? 1 : -1, false, bl, fill));
             TRY(update(c, 2, a, b, s2, nullptr, nullptr, src2, &bl));
-            TRY(eval2(c, s2, staged ? 2 : -1, false, &bl));
+            TRY(eval2(c, s2, staged ? 2 : -1, false, bl, fill));
             TRY(update(c, 3, a, s2, b, nullptr, nullptr, src3, &bl));
             TRY(read_reduce(c, c->red + 1 + k, &r));
             c->red_clean[1 - k] = true;
@@ -1980,12 +1982,18 @@ HWENO_API hweno_status hweno_autotune(hweno_ctx* c, int reps, hweno_tiles* chose
     }
     // `reps` residual evaluations of the current states, each followed by a
     // stage-1 update into the scratch state S[2] (the fluxes may be formed
-    // there); ms per kernel class
+    // there); ms per kernel class.  The launches are those of a step or, for
+    // each group of its instances, of a batched run: the ghost fill, though its
+    // time counts, runs only where it does there
     auto one = [&]() -> hweno_status {
         TRY(reset(c));
-        TRY(eval2(c, si));
-        TRY(dev(hw::launch_dt2(c->bl, c->stream)));
-        return update(c, 1, si, si, 2, nullptr, nullptr);
+        for (int q = 0; q < c->ngroups; ++q) {
+            const hw::BatchL& b = c->ngroups == 2 ? c->blg[q] : c->bl;
+            TRY(eval2(c, si, -1, true, b, !b.forms_ghosts()));
+            TRY(dev(hw::launch_dt2(b, c->stream)));
+            TRY(update(c, 1, si, si, 2, nullptr, nullptr, nullptr, &b));
+        }
+        return HWENO_OK;
     };
     auto measure = [&](double* ms) -> hweno_status {
         TRY(one());                                  // warm-up
@@ -2018,7 +2026,9 @@ HWENO_API hweno_status hweno_autotune(hweno_ctx* c, int reps, hweno_tiles* chose
     for (int q = 0; q < 3; ++q)
         fu[q] = ms[q][hw::KC_FLUX] + ms[q][hw::KC_UPDATE] + ms[q][hw::KC_FLUXUP];
     hw::Tiles best;
-    best.recon = ms[0][hw::KC_RECON] <= ms[1][hw::KC_RECON] ? cand[0].recon : cand[1].recon;
+    // the reconstruction, with the ghost fill where it does not form the cells itself
+    auto rc = [&](int q) { return ms[q][hw::KC_RECON] + ms[q][hw::KC_GHOST]; };
+    best.recon = rc(0) <= rc(1) ? cand[0].recon : cand[1].recon;
     best.grad = grad;
     const int fq = fu[2] < std::min(fu[0], fu[1]) ? 2 : (fu[0] <= fu[1] ? 0 : 1);
     best.flux = cand[fq].flux;
