@@ -69,10 +69,10 @@ FLOPS = {'recon': 7049, 'grad': 3842, 'flux': 560, 'update': 400,
 # HBM bytes per launch from rocprofv3 FETCH_SIZE and WRITE_SIZE (KiB per
 # dispatch) scaled by the factors a 1 GiB device copy gives in the same process
 # (FETCH x 2.0, WRITE x 1.0), per kernel class and tile variant, on this grid
-# and for the kernels as they are now: e.g. recon with 32-cell tiles reads
-# 55.8 MB and writes 439.9 MB per launch.
-TRAFFIC_BYTES = {('recon', 32): 495675392, ('grad', None): 667913216,
-                 ('fluxup', None): 617230336}
+# and for the kernels as they are now: e.g. recon with 32-column tiles reads
+# 55.8 MB and writes 439.9 MB per launch, with 16-column tiles 63.6 and 439.8.
+TRAFFIC_BYTES = {('recon', 16): 503450684, ('recon', 32): 495675392,
+                 ('grad', None): 667913216, ('fluxup', None): 617230336}
 # Algorithmic HBM bytes per cell-stage of the whole path if every input were
 # read once and every output written once (stage average: 256 B residual
 # in/out + the RK bases of stages 2 and 3).
