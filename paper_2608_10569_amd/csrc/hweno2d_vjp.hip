@@ -765,7 +765,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_recon(Grid2 g, AdjIn A, AdjWs W,
     }
     // ---- point cotangents to field cotangents: own two kept, the partner's two
     // in place of its values; sums for the eigenvectors' adjoint ----
-    double a1 = 0.0, a2 = 0.0, a3 = 0.0, a4 = 0.0, a5 = 0.0, a6 = 0.0;
+    PointSums2 pts;
     auto back = [&](auto H, auto Rare) {
 #pragma unroll
         for (int o = 0; o < H.slots; ++o) {
@@ -800,26 +800,18 @@ __global__ __launch_bounds__(256, 2) void k_adj_recon(Grid2 g, AdjIn A, AdjWs W,
 #pragma unroll
                     for (int c = 0; c < 4; ++c) y[c] += P2b[c];
             }
-            const double sm = x[0] + x[3], df = x[3] - x[0], al = sm + x[1];
-            a1 += y[1] * al;
-            a2 += y[2] * al + y[3] * x[2];
-            a3 += y[1] * df;
-            a4 += y[3] * df;
-            a5 += y[3] * sm;
-            a6 += y[3] * x[1];
-            const double s0 = y[0] + e.un * y[1] + e.ut * y[2];
-            const double sa = s0 + e.H * y[3], sd = e.c * (y[1] + e.un * y[3]);
-            const double z1 = s0 + 0.5 * e.q2 * y[3], z2 = y[2] + e.ut * y[3];
+            double z[4];
+            cons2_vjp(e, x, y, pts, z);
             if constexpr (H.value == 0) {
-                va[o] = sa - sd;
-                vb[o] = sa + sd;
-                XP[(9 + o) * 64] = z1;
-                XP[XB + (9 + o) * 64] = z2;
+                va[o] = z[0];
+                vb[o] = z[3];
+                XP[(9 + o) * 64] = z[1];
+                XP[XB + (9 + o) * 64] = z[2];
             } else {
-                va[o] = z1;
-                vb[o] = z2;
-                XP[o * 64] = sa - sd;
-                XP[XB + o * 64] = sa + sd;
+                va[o] = z[1];
+                vb[o] = z[2];
+                XP[o * 64] = z[0];
+                XP[XB + o * 64] = z[3];
             }
         }
     };
@@ -832,8 +824,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_recon(Grid2 g, AdjIn A, AdjWs W,
     }
     __syncthreads();
     // ---- scalar reconstruction, projection row and eigenvector adjoints ----
-    double unb = a1 + e.c * a4, utb = a2, cb = a3 + e.un * a4, q2b = 0.5 * a6;
-    double b1b = 0.0, b2b = 0.0, icb = 0.0;
+    Basis2Bar eb(e, pts);
     double* A0 = sums + tc;
     auto component = [&](int G) { return b == 1 && (G == 1 || G == 2) ? 3 - G : G; };
     auto sel = [](int c, const double* v) {
@@ -870,21 +861,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_recon(Grid2 g, AdjIn A, AdjWs W,
         hweno2d_vjp(a, K, Cb, ab);
         if (b == 0) project2_rowbar<0>(T0, ab, Lb);
         else project2_rowbar<1>(T0, ab, Lb);
-        if (k == 1) {
-            b2b -= Lb[0];
-            b1b += e.un * Lb[1] + e.ut * Lb[2] - Lb[3];
-            unb += e.b1 * Lb[1];
-            utb += e.b1 * Lb[2];
-        } else if (k == 2) {
-            utb -= Lb[0];
-        } else {
-            const double sg = k == 0 ? -1.0 : 1.0, si = sg * e.ic;
-            b2b += 0.5 * Lb[0];
-            unb -= 0.5 * (si * Lb[0] + e.b1 * Lb[1]);
-            icb += 0.5 * sg * (Lb[1] - e.un * Lb[0]);
-            b1b += 0.5 * (Lb[3] - e.un * Lb[1] - e.ut * Lb[2]);
-            utb -= 0.5 * e.b1 * Lb[2];
-        }
+        row2_vjp(e, k, Lb, eb);
 #pragma unroll 1
         for (int ph = 0; ph < 4; ++ph) {
             const int G = (wv + ph) & 3;
@@ -896,25 +873,7 @@ __global__ __launch_bounds__(256, 2) void k_adj_recon(Grid2 g, AdjIn A, AdjWs W,
             __syncthreads();
         }
     }
-    {
-        // back through basis2
-        const double ir = rcp(rbar_), p = K.gm1 * (Et - 0.5 * rbar_ * e.q2);
-        b1b += 0.5 * e.q2 * b2b;
-        q2b += 0.5 * e.b1 * b2b;
-        icb += 2.0 * K.gm1 * e.ic * b1b;
-        cb -= e.ic * e.ic * icb;
-        const double c2b = 0.5 * e.ic * cb;
-        const double pb = ir * a5 + K.gamma * ir * c2b;
-        double irb = (Et + p) * a5 + K.gamma * p * c2b;
-        q2b -= 0.5 * K.gm1 * rbar_ * pb;
-        unb += 2.0 * e.un * q2b;
-        utb += 2.0 * e.ut * q2b;
-        irb += mn * unb + mt * utb;
-        ctr[0] -= 0.5 * K.gm1 * e.q2 * pb + ir * ir * irb;
-        ctr[1] += ir * unb;
-        ctr[2] += ir * utb;
-        ctr[3] += ir * a5 + K.gm1 * pb;
-    }
+    basis2_vjp(K, e, rbar_, mn, mt, Et, pts.a5, eb, ctr);
 #pragma unroll 1
     for (int ph = 0; ph < 4; ++ph) {
         const int G = (wv + ph) & 3;
