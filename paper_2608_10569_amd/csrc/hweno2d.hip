@@ -79,10 +79,9 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
 
 // Block-level reductions: wave shuffles, then LDS across the block's waves;
 // thread 0 issues at most one atomic, and only when it can change the slot.
-// (red_max / red_add with a scratch pointer use the caller's LDS, NT / 64
-// free slots no thread reads or writes until the block ends.)
 template <int NT>
-__device__ __forceinline__ void red_max(unsigned long long* slot, double v, double* sh) {
+__device__ __forceinline__ void red_max(unsigned long long* slot, double v) {
+    __shared__ double sh[NT / 64];
     v = wave_max(v);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -92,28 +91,6 @@ __device__ __forceinline__ void red_max(unsigned long long* slot, double v, doub
         const unsigned long long k = dkey(v);
         if (v > -INFINITY && k > *(volatile HW_GLOBAL unsigned long long*)slot) atomicMax(slot, k);
     }
-}
-template <int NT>
-__device__ __forceinline__ void red_max(unsigned long long* slot, double v) {
-    __shared__ double sh[NT / 64];
-    red_max<NT>(slot, v, sh);
-}
-template <int NT>
-__device__ __forceinline__ void red_add(unsigned long long* slot, unsigned long long v,
-                                        unsigned long long* sh) {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int w = 1; w < NT / 64; ++w) v += sh[w];
-        if (v) atomicAdd(slot, v);
-    }
-}
-template <int NT>
-__device__ __forceinline__ void red_add(unsigned long long* slot, unsigned long long v) {
-    __shared__ unsigned long long sh[NT / 64];
-    red_add<NT>(slot, v, sh);
 }
 // The reductions of an update kernel in one pass: the largest LF coefficient,
 // and with `stage` (a stage update) the least density and pressure and the
@@ -447,7 +424,6 @@ template <int TX, bool VarMu, int FULL, bool GH>
 __global__ __launch_bounds__(256, 3) void k_recon2(Batch bt, int si, int want_alpha, int gst,
                                                  const double* U) {
     constexpr int TY = 64 / TX, TW = TX + 2, TH = TY + 2, PL = TW * TH;
-    constexpr int NP = (PL + 63) / 64;
     // handed-over values: per basis and field of a wavefront, 9 volume values
     // (h = 0) or 6 face values and the moment (h = 1) per cell; the second
     // fields' share reuses the stencil tile's memory
@@ -2027,7 +2003,6 @@ __global__ void k_set_dt(Reduce* r, double dt) {
     }
 }
 
-// Per-instance kernels of a batch: thread p serves the instance in slot p.
 // Places the descriptors of an allocation-free call and resets its reductions:
 // one launch, the descriptors its arguments (three copies from pageable memory
 // and a reset, before).
@@ -2042,6 +2017,7 @@ __global__ __launch_bounds__(256) void k_place2(Place2 a) {
     if (threadIdx.x == 0) reset_reduce((Reduce*)a.g.red);
 }
 
+// Per-instance kernels of a batch: thread p serves the instance in slot p.
 __global__ void k_reset2(const Grid2* __restrict__ gs, int n) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p < n) reset_reduce((Reduce*)gs[p].red);

@@ -469,46 +469,6 @@ __device__ __forceinline__ double flux_speed2c(const Consts& K, const double* U,
     return ac >= bpp ? ac : bpp;
 }
 
-// The same flux with the direction a run-time value (dy: g instead of f);
-// selects instead of branches, so lanes of one wave may take different
-// directions without diverging.
-template <bool VarMu = true>
-__device__ __forceinline__ void flux2_dir(const Consts& K, const double* U, const double* s,
-                                          bool dy, double* f) {
-#pragma clang fp contract(off)
-    const double r = U[0], m = U[1], n = U[2], E = U[3];
-    const double ir = rcp(r);
-    const double u = m * ir, v = n * ir;
-    const double p = K.gm1 * fma(-0.5, fma(m, u, n * v), E);
-    const double mu = viscosity<VarMu>(K, r, p);
-    const Stress t = stresses(mu, s);
-    const double kq = K.gPr * mu;
-    const double un = dy ? v : u;           // velocity along the direction
-    const double tnx = dy ? t.xy : t.xx;    // stress (x, direction)
-    const double tny = dy ? t.yy : t.xy;    // stress (y, direction)
-    const double qd = dy ? s[5] : s[4];
-    f[0] = dy ? n : m;
-    f[1] = fma(m, un, (dy ? 0.0 : p)) - tnx;
-    f[2] = fma(n, un, (dy ? p : 0.0)) - tny;
-    f[3] = fma(E + p, un, -fma(tnx, u, fma(tny, v, kq * qd)));
-}
-
-// The viscous part of flux2_dir's components 1..3 at a volume point, from the
-// velocities, the viscosity and the six gradients s (the reconstruction kernel
-// sums the convective part).
-__device__ __forceinline__ void visc2_dir(const Consts& K, double u, double v, double mu,
-                                          const double* s, bool dy, double* f) {
-#pragma clang fp contract(off)
-    const Stress t = stresses(mu, s);
-    const double kq = K.gPr * mu;
-    const double tnx = dy ? t.xy : t.xx;
-    const double tny = dy ? t.yy : t.xy;
-    const double qd = dy ? s[5] : s[4];
-    f[0] = -tnx;
-    f[1] = -tny;
-    f[2] = -fma(tnx, u, fma(tny, v, kq * qd));
-}
-
 // PP wave-speed bound of eq. (3.3) in direction d, no smaller than |u_d| + c.
 template <int d, bool VarMu = true>
 __device__ __forceinline__ double speed2(const Consts& K, const double* U, const double* s) {
@@ -549,7 +509,9 @@ __device__ __forceinline__ void eig1(const Consts& K, const double* Ub, Eig1& e)
     e.L[2][0] = 0.5 * (b2 - u * ic); e.L[2][1] = 0.5 * (ic - b1 * u);  e.L[2][2] = 0.5 * b1;
 }
 
-// Row k of L and row c of R of the x- (b = 0) or y-Jacobian (b = 1).
+// Row k of L and row c of R of the x- (b = 0) or y-Jacobian (b = 1): what the
+// generated eig2_vjp_* reverse, for the CPU check of those (kernels take the basis
+// of hweno_basis2.h).
 __device__ __forceinline__ void eig2_rows(const Consts& K, const double* Ub, int b, int k,
                                           double* Lrow, double* Rrow) {
     const double ir = rcp(Ub[0]);
