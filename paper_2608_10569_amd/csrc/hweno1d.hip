@@ -6,8 +6,8 @@
 //           reconstruction (eq. (2.9)) or the comparison scheme's gradients
 //           (eq. (2.5)), fluxes (eq. (2.3)), assembly and the stage
 //           combination (eqs. (2.2), (2.12))
-//   ghost, recon, rbar, grad, flux   the residual's HWENO-GR intermediates in
-//           memory, which the reverse mode reads
+//   ghost, recon, rbar, grad   the residual's HWENO-GR intermediates in memory
+//           that the reverse mode reads
 
 #include "hweno_kernels.h"
 
@@ -25,11 +25,6 @@ __device__ __forceinline__ double wmax(double v) {
 __device__ __forceinline__ double wmin(double v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v = fmin(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ __forceinline__ unsigned long long wsum(unsigned long long v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
     return v;
 }
 
@@ -65,87 +60,63 @@ __global__ void k_recon1(Grid1 g, const double* __restrict__ S) {
     const Consts& K = g.K;
     const long long N = g.NX;
     const int i = 1 + blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = i <= g.NX - 2;
-    double amax = -INFINITY;
-    unsigned long long act = 0;
-    if (valid) {
-        double ub[3];
+    if (i > g.NX - 2) return;
+    double ub[3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) ub[c] = S[c * N + i];
-        Eig1 e;
-        eig1(K, ub, e);
-        double P[4][3] = {{0.0}}, vh[3] = {0.0, 0.0, 0.0};
+    for (int c = 0; c < 3; ++c) ub[c] = S[c * N + i];
+    Eig1 e;
+    eig1(K, ub, e);
+    double P[4][3] = {{0.0}};
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            double a[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int k = 0; k < 3; ++k) {
+        double a[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const double l = e.L[k][c];
-                a[0] += l * S[c * N + i - 1];
-                a[1] += l * S[c * N + i];
-                a[2] += l * S[c * N + i + 1];
-                a[3] += l * S[(3 + c) * N + i - 1];
-                a[4] += l * S[(3 + c) * N + i + 1];
-            }
-            double C[5], v[4];
-            hweno1d(a, K, C);
-            eval1d(C, v);
-            const double mo = moment1d(C);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-#pragma unroll
-                for (int p = 0; p < 4; ++p) P[p][c] += e.R[c][k] * v[p];
-                vh[c] += e.R[c][k] * mo;
-            }
+        for (int c = 0; c < 3; ++c) {
+            const double l = e.L[k][c];
+            a[0] += l * S[c * N + i - 1];
+            a[1] += l * S[c * N + i];
+            a[2] += l * S[c * N + i + 1];
+            a[3] += l * S[(3 + c) * N + i - 1];
+            a[4] += l * S[(3 + c) * N + i + 1];
         }
-        // positivity limiter on the four LGL values (all four are rescaled)
-        const double rbar = ub[0];
-        const double pbar = pressure1(K, ub[0], ub[1], ub[2]);
-        const double eps = fmin(fmin(K.eps_pp, rbar), pbar);
-        double rmin = P[0][0];
+        double C[5], v[4];
+        hweno1d(a, K, C);
+        eval1d(C, v);
 #pragma unroll
-        for (int p = 1; p < 4; ++p) rmin = fmin(rmin, P[p][0]);
-        const double th1 = rmin < eps ? (rbar - eps) / (rbar - rmin) : 1.0;
-        double th2 = 1.0;
+        for (int c = 0; c < 3; ++c)
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            P[p][0] = rbar + th1 * (P[p][0] - rbar);
-            const double pt = pressure1(K, P[p][0], P[p][1], P[p][2]);
-            if (pt < eps) th2 = fmin(th2, (pbar - eps) / (pbar - pt));
-        }
-        double su = 0.0, se = 0.0;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                P[p][c] = ub[c] + th2 * (P[p][c] - ub[c]);
-                g.pts[(p * 3 + c) * N + i] = P[p][c];
-            }
-            const double wq = (p == 0 || p == 3) ? LGL_W0 : LGL_W1;
-            const double u = P[p][1] / P[p][0];
-            su += wq * u;
-            se += wq * (P[p][2] / P[p][0] - 0.5 * u * u);
-        }
-        g.wb[0 * N + i] = su;
-        g.wb[1 * N + i] = se;
-        const bool inter = i >= HALO && i < HALO + g.nx;
-        if (inter) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) g.vk[c * N + i] = vh[c];
-#pragma unroll
-            for (int p = 0; p < 4; p += 3) {
-                const double pr = pressure1(K, P[p][0], P[p][1], P[p][2]);
-                amax = fmax(amax, fabs(P[p][1] / P[p][0]) + sqrt(K.gamma * pr / P[p][0]));
-            }
-            act = (th1 < 1.0 || th2 < 1.0) ? 1ull : 0ull;
-        }
+            for (int p = 0; p < 4; ++p) P[p][c] += e.R[c][k] * v[p];
     }
-    amax = wmax(amax);
-    act = wsum(act);
-    if ((threadIdx.x & 63) == 0) {
-        if (amax > -INFINITY) atomicMax(&g.red->alpha_key, dkey(amax));
-        if (act) atomicAdd(&g.red->pp_cells, act);
+    // positivity limiter on the four LGL values (all four are rescaled)
+    const double rbar = ub[0];
+    const double pbar = pressure1(K, ub[0], ub[1], ub[2]);
+    const double eps = fmin(fmin(K.eps_pp, rbar), pbar);
+    double rmin = P[0][0];
+#pragma unroll
+    for (int p = 1; p < 4; ++p) rmin = fmin(rmin, P[p][0]);
+    const double th1 = rmin < eps ? (rbar - eps) / (rbar - rmin) : 1.0;
+    double th2 = 1.0;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        P[p][0] = rbar + th1 * (P[p][0] - rbar);
+        const double pt = pressure1(K, P[p][0], P[p][1], P[p][2]);
+        if (pt < eps) th2 = fmin(th2, (pbar - eps) / (pbar - pt));
     }
+    double su = 0.0, se = 0.0;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            P[p][c] = ub[c] + th2 * (P[p][c] - ub[c]);
+            g.pts[(p * 3 + c) * N + i] = P[p][c];
+        }
+        const double wq = (p == 0 || p == 3) ? LGL_W0 : LGL_W1;
+        const double u = P[p][1] / P[p][0];
+        su += wq * u;
+        se += wq * (P[p][2] / P[p][0] - 0.5 * u * u);
+    }
+    g.wb[0 * N + i] = su;
+    g.wb[1 * N + i] = se;
 }
 
 __device__ __forceinline__ void prim_ue(const Grid1& g, long long i, int p, double* w) {
@@ -175,12 +146,11 @@ __global__ void k_rbar1(Grid1 g) {
     }
 }
 
-// Gradient reconstruction on cells 3 .. NX-4 and the volume-flux quadrature.
+// Gradient reconstruction on cells 3 .. NX-4.
 __global__ void k_grad1(Grid1 g) {
     const int i = 3 + blockIdx.x * blockDim.x + threadIdx.x;
     if (i > g.NX - 4) return;
     const long long N = g.NX;
-    double gr[4][2];
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
         const double* r0 = g.rb + (w * 2 + 0) * N;
@@ -190,51 +160,8 @@ __global__ void k_grad1(Grid1 g) {
         hweno1d(a, grad_consts(g.K), C);
         eval1d(C, v);
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            gr[p][w] = v[p];
-            g.gr[(p * 2 + w) * N + i] = v[p];
-        }
+        for (int p = 0; p < 4; ++p) g.gr[(p * 2 + w) * N + i] = v[p];
     }
-    if (i >= HALO && i < HALO + g.nx) {
-        double acc[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            double U[3], f[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) U[c] = g.pts[(p * 3 + c) * N + i];
-            flux1(g.K, U, gr[p][0], gr[p][1], f);
-            const double wq = (p == 0 || p == 3) ? LGL_W0 : LGL_W1;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) acc[c] += wq * f[c];
-        }
-#pragma unroll
-        for (int c = 0; c < 3; ++c) g.vf[c * N + i] = acc[c];
-    }
-}
-
-// Face fluxes at i + 1/2 for i = HALO-1 .. HALO+nx-1.
-__global__ void k_flux1(Grid1 g) {
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    double beta = -INFINITY;
-    if (f <= g.nx) {
-        const long long N = g.NX;
-        const int i = HALO - 1 + f;
-        double Um[3], Up[3], fm[3], fp[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            Um[c] = g.pts[(3 * 3 + c) * N + i];
-            Up[c] = g.pts[(0 * 3 + c) * N + i + 1];
-        }
-        const double umx = g.gr[(3 * 2 + 0) * N + i], emx = g.gr[(3 * 2 + 1) * N + i];
-        const double upx = g.gr[(0 * 2 + 0) * N + i + 1], epx = g.gr[(0 * 2 + 1) * N + i + 1];
-        flux1(g.K, Um, umx, emx, fm);
-        flux1(g.K, Up, upx, epx, fp);
-        beta = fmax(speed1(g.K, Um, umx, emx), speed1(g.K, Up, upx, epx));
-#pragma unroll
-        for (int c = 0; c < 3; ++c) g.fh[c * N + i] = 0.5 * (fm[c] + fp[c] - beta * (Up[c] - Um[c]));
-    }
-    beta = wmax(beta);
-    if ((threadIdx.x & 63) == 0 && beta > -INFINITY) atomicMax(&g.red->beta_key, dkey(beta));
 }
 
 // ---------------------------------------------------------------------------
@@ -273,7 +200,6 @@ __global__ __launch_bounds__(64) void k_stage1(Grid1 g, Stage1 A) {
     const int lane = threadIdx.x;
     const int i = (int)blockIdx.x * ST_CELLS + lane;
     const bool own = lane >= HALO && lane < HALO + ST_CELLS && i < HALO + g.nx;
-    const bool cellok = i >= 1 && i <= g.NX - 2;
     // step size of stages 2 and 3: stage 2 forms it from the wave speed of
     // stage 1 (every wavefront the same), stage 3 reads it
     double dt = 0.0;
@@ -577,9 +503,6 @@ hipError_t launch_residual1(const Grid1& g, const double* S, hipStream_t st, Tim
     tend(tm, st);
     tbeg(tm, KC_GRAD, st);
     k_grad1<<<nb(g.NX - 6, 128), 128, 0, st>>>(g);
-    tend(tm, st);
-    tbeg(tm, KC_FLUX, st);
-    k_flux1<<<nb(g.nx + 1, 128), 128, 0, st>>>(g);
     tend(tm, st);
     return hipGetLastError();
 }

@@ -127,9 +127,6 @@ struct hweno_ctx {
     int* ssrcu_dev = nullptr;
     int* sstart_dev = nullptr;
     int* sord_dev = nullptr;
-    // allocation-free residual (hweno_residual_noalloc): the descriptors it
-    // copies into the library's static scratch, kept here so that the copies
-    // read host memory that outlives the call
     hw::Timer* tm() { return timer.on ? &timer : nullptr; }
     const Inst& i0() const { return in[0]; }
     int dim() const { return in[0].grid.dim; }
@@ -241,12 +238,9 @@ size_t layout(hweno_ctx* c, char* base) {
         for (int k = 0; k < 5; ++k) c->S1[k] = take(6 * m);
         g.pts = take(12 * m);
         g.wb = take(2 * m);
-        g.vk = take(3 * m);
         g.vn = take(3 * m);
         g.rb = take(4 * m);
         g.gr = take(8 * m);
-        g.fh = take(3 * m);
-        g.vf = take(3 * m);
         g.fr = take(6 * m);
         c->red = reinterpret_cast<hw::Reduce*>(take_bytes(3 * sizeof(hw::Reduce)));
         g.red = (HW_GLOBAL hw::Reduce*)c->red;
@@ -646,8 +640,9 @@ hweno_status ghost(hweno_ctx* c, int si, int stage = -1, const hw::BatchL* b = n
     return dev(hw::launch_ghost1(c->g1, c->S1[si], c->stream, c->tm()));
 }
 
-// Residual at a state whose ghost cells are filled.  b: the 2D launch list to
-// use (the stage sets of keep_stages); default the grid's.
+// Residual at a state whose ghost cells are filled (1D: the intermediates that the
+// reverse mode reads).  b: the 2D launch list to use (the stage sets of
+// keep_stages); default the grid's.
 hweno_status residual(hweno_ctx* c, int si, const hw::BatchL* b = nullptr) {
     if (c->dim() == 2)
         return dev(hw::launch_residual2(b ? *b : c->bl, si, hw::GHOSTS_FILLED, c->stream,
@@ -675,7 +670,7 @@ hweno_status eval2(hweno_ctx* c, int si, int stage, bool alpha, const hw::BatchL
     return dev(hw::launch_residual2(b, si, stage, c->stream, c->tm(), alpha));
 }
 
-// 2D
+// 2D stage update (stage 0: the residual into R and V).
 hweno_status update(hweno_ctx* c, int stage, int i0, int iin, int iout, double* R, double* V,
                     const double* src = nullptr, const hw::BatchL* b = nullptr,
                     const hw::StepRule& rule = hw::StepRule()) {
@@ -1400,7 +1395,8 @@ namespace {
 
 // One attempt of a 1D step of size dt (or by the step rule) from S1[0] into
 // S1[1]: three launches.  U1 lives only inside the second.
-hweno_status attempt1(hweno_ctx* c, bool auto_dt, double dt, double cfl_h, double visc, double t_left, bool check,
+hweno_status attempt1(hweno_ctx* c, bool auto_dt, double dt, double cfl_h, double visc,
+                      double t_left, bool check,
                       const double* const* src, hw::Reduce* r) {
     const int k = c->red_turn;
     c->red_turn = 1 - k;
@@ -1589,7 +1585,6 @@ HWENO_API hweno_status hweno_residual_vjp(hweno_ctx* c, const double* U, const d
     if (!c->ws) return HWENO_E_WORKSPACE;
     if (c->dim() == 1) {   // the step's stage buffer 2 holds U (the state is kept)
         TRY(dev(hw::launch_copy_in1(c->g1, U, c->S1[2], c->stream)));
-        TRY(reset(c));
         TRY(ghost(c, 2));
         TRY(residual(c, 2));
         hw::AdjIn A{Rbar, Vbar, 1.0, 1.0};
@@ -1641,7 +1636,6 @@ HWENO_API hweno_status hweno_rk_step_vjp(hweno_ctx* c, const double* U0, double 
         TRY(dev(hw::launch_stage1(c->g1, sa, c->stream, c->tm())));
         auto vjp_at1 = [&](int si, const double* Rb, const double* Vb, double rs, double vs,
                            double* out, int acc) {
-            TRY(reset(c));
             TRY(ghost(c, si));
             TRY(residual(c, si));
             hw::AdjIn A{Rb, Vb, rs, vs};

@@ -116,12 +116,9 @@ struct Grid1 {
     Side side[2];
     gdouble* pts;  // 12: limited LGL point values (p*3 + c)
     gdouble* wb;   // 2: wbar of (u, e)
-    gdouble* vk;   // 3: modified moment of the current input
     gdouble* vn;   // 3: modified moment of U^n
     gdouble* rb;   // 4: weak moments (w*2 + mom)
     gdouble* gr;   // 8: gradients at the LGL points (p*2 + w)
-    gdouble* fh;   // 3: face flux at i+1/2
-    gdouble* vf;   // 3: volume flux quadrature
     gdouble* fr;   // 6: residual of U^n, from the step's first kernel to its second
     HW_GLOBAL Reduce* red;
 };
@@ -329,7 +326,7 @@ hipError_t launch_set_dt(Reduce* red, double dt, hipStream_t st);
 hipError_t launch_copy_in1(const Grid1& g, const double* U, double* S, hipStream_t st);
 hipError_t launch_copy_out1(const Grid1& g, const double* S, double* U, hipStream_t st);
 hipError_t launch_ghost1(const Grid1& g, double* S, hipStream_t st, Timer* tm);
-// the residual's intermediates (HWENO-GR), for the reverse mode
+// the residual's intermediates (HWENO-GR) that the reverse mode reads
 hipError_t launch_residual1(const Grid1& g, const double* S, hipStream_t st, Timer* tm);
 // A whole 1D stage in one launch (every intermediate in registers).  Stage 0 writes R and Vhat; stage 1 keeps the residual of U^n
 // and its modified moments (g.fr, g.vn), the wave speeds and the input check;
