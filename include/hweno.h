@@ -373,13 +373,13 @@ HWENO_API hweno_status hweno_take_mu_bar(hweno_ctx* ctx, double* mu_bar);
  * start and end of its execution (hipExtLaunchKernel: the dispatch is not
  * counted); classes 4 and 6 record them on the stream around their launches.
  * Classes:
- * 0 ghost fill (small launches form the ghost cells in the reconstruction and
- * run the fill only while this class is recorded), 1 characteristic reconstruction + limiter, 2 weak-derivative
- * moments as a kernel of their own (reverse mode), 3 gradient reconstruction
- * (else with the weak moments) + volume flux, 4 face fluxes, 5 stage
- * update / assembly, 6 a whole batched run (hweno_batch_run), 7 face fluxes
- * fused with the stage update / assembly (tiles.flux = 0); on 1D grids a
- * whole stage, which is one kernel, in class 7. */
+ * 0 ghost fill (small launches form the ghost cells in the reconstruction and run
+ * the fill only while this class is recorded), 1 characteristic reconstruction +
+ * limiter, 2 weak-derivative moments as a kernel of their own (reverse mode),
+ * 3 gradient reconstruction (else with the weak moments) + volume flux, 4 face
+ * fluxes, 5 stage update / assembly, 6 a whole batched run (hweno_batch_run),
+ * 7 face fluxes fused with the stage update / assembly (tiles.flux = 0); on 1D
+ * grids a whole stage, which is one kernel, in class 7. */
 typedef struct hweno_timing {
     double ms[8];                       /* summed elapsed milliseconds */
     unsigned long long launches[8];     /* timed launches */
@@ -454,7 +454,8 @@ typedef struct hweno_tiles {
                        kernel, per tile of 32 cells and the ring around it */
     int flux;       /* faces per block of the face-flux kernels: 64 or 128; 0: no
                        separate flux kernels -- the update kernel forms the fluxes
-                       of each 32 x 8 tile of cells in LDS (same results) */
+                       of each tile of 32 x 8 cells (small launches and mu(T):
+                       32 x 4) in LDS (same results) */
     int order;      /* batch schedule: 0 instances as given, 1 largest first */
     int xcd;        /* 1: each of the 8 XCDs (own L2) takes a contiguous range of a
                        launch's blocks, so neighbouring rows share an L2; 0: launch order */

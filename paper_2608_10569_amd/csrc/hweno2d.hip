@@ -1,22 +1,25 @@
 // 2D HWENO-GR residual and SSP-RK3 stage update (Sec. 3 of arXiv 2608.10569)
 // as a pipeline of HIP kernels over a ghosted structure-of-arrays grid.
 //
-//   ghost            : halo of width 4 (Remark 4.1)
+//   ghost            : halo of width 4 (Remark 4.1; small launches form these
+//                      cells in the reconstruction's loads instead)
 //   recon            : characteristic HWENO in the x- and y-bases (eq. (3.4)),
 //                      positivity limiter on the face values, wbar, hat-v/w,
 //                      CFL wave speed                 [cells of halo ring 3]
-//   rbar             : interface averages, face moments, weak-derivative
-//                      moments (eqs. (3.6)-(3.8))      [halo ring 2]
-//   grad             : gradient HWENO (eq. (3.9)) at 12 face + 9 volume points,
-//                      volume-flux quadratures         [halo ring 1]
-//   rgrad            : rbar + grad in one kernel per tile of cells, the weak
-//                      moments of the tile and its ring kept in LDS (a tile
-//                      choice)
+//   rgrad            : interface averages, face moments, weak-derivative
+//                      moments (eqs. (3.6)-(3.8)) of a tile of cells and the
+//                      ring around it in LDS, then gradient HWENO (eq. (3.9)) at
+//                      12 face + 9 volume points and the volume-flux
+//                      quadratures                     [halo ring 1]
+//   rbar, grad       : the same as two kernels for the reverse mode, which reads
+//                      the weak moments from memory    [halo rings 2, 1]
+//   recon_dr         : HWENO-DR's recon, with the gradients and volume fluxes
 //   flux_x, flux_y   : PP Lax-Friedrichs fluxes at face Gauss points (eq. (3.3))
 //   update           : assembly of eq. (3.2) and the stage combination of the
 //                      SSP-RK3 scheme with modified moments (eq. (2.12))
 //   fluxup           : flux_x + flux_y + update in one kernel per tile of
-//                      cells, the face fluxes kept in LDS (a tile choice)
+//                      cells, the face fluxes kept in LDS (the default; the
+//                      three kernels apart are a tile choice)
 //
 // Every other intermediate lives in HBM, laid out component-major over the
 // ghosted grid so that consecutive lanes touch consecutive cells.

@@ -227,13 +227,17 @@ struct Tiles {
 // reconstruction as it loads them (any other value: the stage of the inflow
 // profiles to take, -1: none).
 constexpr int GHOSTS_FILLED = -2;
-// Up to this many blocks of the reconstruction it forms them: a launch less
-// per stage.  Step of three stages with the fill as a launch and without, us:
-// 64x64 (108 blocks) 114 and 100, 160x160 152 and 138, 500x100 204 and 195,
-// 256x256 (1161 blocks) 241 and 233, 400x400 (2639) 404 and 407, 512x512 690
-// and 699, 1000x500 1317 and 1340: the index arithmetic of every tile costs
-// the reconstruction 3 us at 64x64 and 15 of 136 at 1000x500.
-// HWENO-DR alike: four steps of 500x250 (2032 blocks) 1318 and 1290 us.
+// Up to this many blocks of the reconstruction it forms them: a launch less per
+// stage, against the index arithmetic of every tile (3 us at 64x64, 15 of 136 at
+// 1000x500).  Step of three stages with the fill as a launch and without, us, on
+// tiles of 32 columns: 64x64 (105 blocks) 107.6 and 96.5, 160x160 (498) 154.7 and
+// 142.4, 256x256 (1179) 242.5 and 236.6, 340x340 (1903) 333.7 and 330.9, 500x250
+// (2048) 346.5 and 345.4, 380x380 (2509) 389 and 391, 400x400 (2639) 422 and 420,
+// 512x512 (4403) 704 and 712, 1000x500 (8096) 1317 and 1333.  HWENO-DR: 64x64 101.3
+// and 89.9, 500x250 339.0 and 334.8, 380x380 394.9 and 393.3, 400x400 417 and 421,
+// 512x512 666 and 675.  The line is the largest launch at which both still gain;
+// up to 2639 blocks the plain scheme is even.  Tiles of 16 columns count the same
+// within 3 %.
 constexpr unsigned GHOST_MAX_BLOCKS = 2048;
 
 struct BatchL {
@@ -328,9 +332,10 @@ hipError_t launch_copy_out1(const Grid1& g, const double* S, double* U, hipStrea
 hipError_t launch_ghost1(const Grid1& g, double* S, hipStream_t st, Timer* tm);
 // the residual's intermediates (HWENO-GR) that the reverse mode reads
 hipError_t launch_residual1(const Grid1& g, const double* S, hipStream_t st, Timer* tm);
-// A whole 1D stage in one launch (every intermediate in registers).  Stage 0 writes R and Vhat; stage 1 keeps the residual of U^n
-// and its modified moments (g.fr, g.vn), the wave speeds and the input check;
-// stage 2 forms the step size and U1 from them; stages 2 and 3 write `out`.
+// A whole 1D stage in one launch (every intermediate in registers).  Stage 0 writes
+// R and Vhat; stage 1 keeps the residual of U^n and its modified moments (g.fr,
+// g.vn), the wave speeds and the input check; stage 2 forms the step size and U1
+// from them; stages 2 and 3 write `out`.
 struct Stage1 {
     int stage;
     const double* in;      // stage input, planes of `plane` doubles, cell 0 of the interior at
